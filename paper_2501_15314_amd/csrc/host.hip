@@ -101,6 +101,11 @@ struct sim_s {
   long long tl_cap = 0;  // capacity of the touch lists
   int nactive = 0;       // launch count of ACTIVE (active tiles in launch order)
   int *NZT = nullptr;    // non-empty point tiles in launch order (-1: hole)
+  // coupling term: its workgroups of points, every tile's share of them, the region sums
+  int4 *ITEMS = nullptr;
+  int2 *PARTS = nullptr;
+  double *REGION = nullptr;
+  int nitems = 0;
   int nnz = 0;           // launch count of NZT
   int ntouch = 0;
   BodyDev *BODIES = nullptr;
@@ -429,6 +434,11 @@ size_t layout(sim_s *s, const sim_config *c, int64_t kmax, void *base, const std
   long long tl_cap = 27 * K;  // a point touches at most 3 x 3 x 3 tiles
   int *TCOUNT = cv.arr<int>(nt), *TLSTART = cv.arr<int>(nt + 1), *TLIST = cv.arr<int>(tl_cap);
   int *NZT = cv.arr<int>(nt + 8);
+  // the bfloat16 fast diagonalisation keeps the list kernels (points_grad)
+  const bool cpl = c->precond != SIM_PRECOND_FASTDIAG;
+  int4 *ITEMS = cv.arr<int4>(cpl ? couple_max_items(K, nt) : 0);
+  int2 *PARTS = cv.arr<int2>(cpl ? nt : 0);
+  double *REGION = (double *)cv.take(cpl ? couple_region_bytes(K, nt) : 0);
   BodyDev *BODIES = (BodyDev *)cv.take(sizeof(BodyDev) * MAX_BODIES);
   BodySpan *SPAN = (BodySpan *)cv.take(sizeof(BodySpan) * MAX_BODIES);
   double *BSUM = cv.arr<double>(12LL * MAX_BODIES);
@@ -459,7 +469,7 @@ size_t layout(sim_s *s, const sim_config *c, int64_t kmax, void *base, const std
     s->ACTIVE = ACTIVE; s->SCANTMP = SCANTMP; s->BODIES = BODIES;
     s->SPAN = SPAN; s->BSUM = BSUM; s->VPART = VPART;
     s->TCOUNT = TCOUNT; s->TLSTART = TLSTART; s->TLIST = TLIST;
-    s->tl_cap = tl_cap; s->NZT = NZT;
+    s->tl_cap = tl_cap; s->NZT = NZT; s->ITEMS = ITEMS; s->PARTS = PARTS; s->REGION = REGION;
     s->COARSEFD = COARSEFD;
     s->SUBTAB = SUBTAB;
     s->fastdiag = fdg;
@@ -579,6 +589,13 @@ sim_status place_and_bin(sim_t s, const std::vector<BodyDev> &bd) {
   s->nnz = order_launch_count(nz);  // launch count of NZT (holes included)
   // interpolation launch order of the non-empty point tiles: XCD chunks, fullest first
   CKH(order_active(nz, s->ACTIVE, s->TSTART, s->NZT, st));
+  // the coupling term's workgroups (FILLC, TLSTART and SCANTMP are free here);
+  // their number is read with the touch lists' below
+  int ni = 0;
+  if (!s->fastdiag)
+    CKH(couple_items(nz, s->ACTIVE, s->TSTART, s->FILLC, s->TLSTART, s->SCANTMP, s->ITEMS, s->PARTS, nt, st));
+  if (!s->fastdiag && nz > 0)
+    CKH(hipMemcpyAsync((int *)s->hpin + 2, s->TLSTART + nz, sizeof(int), hipMemcpyDeviceToHost, st));
   // touch lists of the active tiles (tiles reached by some point's support),
   // counted and filled tile by tile in a fixed order; only the tiles within
   // one tile of a non-empty point tile can be reached (candidates, compacted
@@ -600,6 +617,8 @@ sim_status place_and_bin(sim_t s, const std::vector<BodyDev> &bd) {
   CKH(hipStreamSynchronize(st));
   memcpy(&na, s->hpin, sizeof(int));
   memcpy(&M, (int *)s->hpin + 1, sizeof(int));
+  if (!s->fastdiag && nz > 0) memcpy(&ni, (int *)s->hpin + 2, sizeof(int));
+  s->nitems = ni;
   if (M > s->tl_cap) return fail(s, SIM_EDEVICE, "touch list overflow");
   CKH(touch_tiles(s->ker, s->g, s->nt0, s->nt1, s->nt2, na, nullptr, s->ACTIVE, s->TSTART, s->XS, nullptr,
                   s->TLSTART, s->TLIST, st));
@@ -632,6 +651,27 @@ std::vector<BodyDev> body_states_at(sim_t s, double t) {
 // ---------------------------------------------------------------------------
 // Operators on the split layout
 
+Coupling coupling(const sim_s *s) {
+  return {s->ker, s->nt0, s->nt1, s->nt2, s->nitems, s->nactive, s->ITEMS, s->PARTS, s->ACTIVE, s->XS, s->REGION};
+}
+
+// out = alpha W^T G z + beta y and out += alpha D W q, float64.  On the matrix
+// cores (kernels_couple.hip; at 256^3 with 144000 points an S~ product's
+// pair takes 36 + 13 us there, 32 + 68 us from the touch lists) except with
+// the bfloat16 fast diagonalisation: its roundings turn a last-bit change of
+// a right-hand side into one of the size of the solve's tolerance, and the
+// list kernels keep that form's results bit for bit.
+hipError_t points_grad(sim_t s, const double *z, double alpha, const double *y, double beta, double *out) {
+  if (!s->fastdiag) return couple_interp(s->g, coupling(s), z, alpha, y, beta, out, s->st);
+  return interp_grad<double>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, alpha, y, beta, out,
+                             s->st);
+}
+hipError_t points_spread_div(sim_t s, const double *q, double alpha, double *out) {
+  if (!s->fastdiag) return couple_spread(s->g, coupling(s), q, alpha, out, s->st);
+  return band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha,
+                    out, s->st);
+}
+
 // Algorithmic bytes of one whole-grid fast-diagonalisation solve: the input
 // (ti bytes per cell) read and bfloat16 lines written, three bfloat16 passes
 // (y forward, x forward + scale + back, y back), bfloat16 lines read and the
@@ -657,10 +697,14 @@ sim_status schur_matvec(sim_t s, const T *z, TW *w) {
     ProbeExt pr(PR_LAP, s->st, (double)s->N * (sizeof(T) + sizeof(TW)));  // z read, w written
     CKH((lap_apply<T, TW>(s->g, z, w, s->st)));
   }
-  CKH(interp_grad<T>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, 1.0, nullptr, 0.0, s->Q,
-                     s->st, f32));
-  CKH(band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, s->Q,
-                 -1.0 / s->c, w, s->st, f32));
+  if (f32 || s->fastdiag) {
+    CKH(interp_grad<T>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, 1.0, nullptr, 0.0, s->Q,
+                       s->st, f32));
+    CKH(band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, s->Q,
+                   -1.0 / s->c, w, s->st, f32));
+  } else if constexpr (!f32) {
+    CKH(couple_product<T>(s->g, coupling(s), z, -1.0 / s->c, w, s->st));
+  }
   return SIM_OK;
 }
 
@@ -1157,8 +1201,7 @@ sim_status fgmres_any(sim_t s, const double *b, double *x, sim_solve_stats *stt)
 // removes the mean on the fly
 sim_status schur_rhs(sim_t s, bool in_bvec = false, double *bsum = nullptr) {
   if (!in_bvec) CKH(scale_copy(s->BVEC, s->RHSP, s->N, 1.0, s->st));
-  CKH(band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, s->RF,
-                 1.0 / s->c, s->BVEC, s->st));
+  CKH(points_spread_div(s, s->RF, 1.0 / s->c, s->BVEC));
   if (bsum) {
     CKH(dot2(s->BVEC, nullptr, s->N, s->PART, s->st));
     CKH(finalize(s->PART, red_blocks(), 1, bsum, s->st));
@@ -1189,7 +1232,7 @@ sim_status schur_solve_core(sim_t s, sim_solve_stats *stt, bool isolated = false
                                   : fgmres<double>(s, s->BVEC, s->PP, stt, bsum, xsum);
   if (solve_rc != SIM_OK && solve_rc != SIM_ENOTCONV) return solve_rc;
   // Phi' = c^-1 (B p' - RHS_F) = -c^-1 (W^T G p' + RHS_F)
-  CKH(interp_grad<double>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, s->PP, -1.0 / s->c, s->RF, -1.0 / s->c, s->PHIP, s->st));
+  CKH(points_grad(s, s->PP, -1.0 / s->c, s->RF, -1.0 / s->c, s->PHIP));
   CKH(hipEventRecord(e1, s->st));
   CKH(hipEventSynchronize(e1));
   float ms = 0;
@@ -2020,8 +2063,9 @@ sim_status sim_step_adjoint(sim_t s, const double *d_gu, const double *d_gv, con
   double *UB = s->TMP3, *RB = s->RHSU, *F3 = s->USTAR, *PB = s->RHSP, *BB = s->BVEC;
   sim_status rc;
   auto band = [&](bool div, const double *q, double alpha, double *out) {
-    return band_apply(ker, div, g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha, out,
-                      st);
+    return div ? points_spread_div(s, q, alpha, out)
+               : band_apply(ker, false, g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha,
+                            out, st);
   };
   // cotangents of u^{n+1} (masked), p^{n+1}, Phi^{n+1}
   CKH(fill(UB, n3, 0.0, st));
@@ -2054,7 +2098,7 @@ sim_status sim_step_adjoint(sim_t s, const double *d_gu, const double *d_gv, con
   if (src != SIM_OK && src != SIM_ENOTCONV) return src;
   // q2 = W^T G bbar;  d S~ and d(RHS) terms:
   //   Xbar += d((G bbar)^T W Phi') - c^-1 d((G p')^T W (Phibar' + q2))
-  CKH(interp_grad<double>(ker, g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, BB, 1.0, nullptr, 0.0, A3, st));
+  CKH(points_grad(s, BB, 1.0, nullptr, 0.0, A3));
   CKH(grad_apply(g, BB, F3, 1.0, nullptr, st));
   CKH(interp_dx(ker, g, K, s->XS, F3, s->PHIP, 1.0, A4, st));
   CKH(scale3(K, A1, 1.0, A3, 1.0, A1, st));
@@ -2155,8 +2199,9 @@ sim_status sim_step_adjoint_two_way(sim_t s, const double *d_gu, const double *d
   double *UB = s->TMP3, *RB = s->RHSU, *F3 = s->USTAR, *PB = s->RHSP, *PPB = s->PP, *BB = s->BVEC;
   sim_status rc;
   auto band = [&](bool div, const double *q, double alpha, double *out) {
-    return band_apply(ker, div, g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha, out,
-                      st);
+    return div ? points_spread_div(s, q, alpha, out)
+               : band_apply(ker, false, g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha,
+                            out, st);
   };
   // per-body sums of a natural-order point vector: (sum v, sum L~ x v)
   std::vector<double> sums(12 * (size_t)nb);
@@ -2222,7 +2267,7 @@ sim_status sim_step_adjoint_two_way(sim_t s, const double *d_gu, const double *d
     sim_status r1 = fgmres_any(s, PPB, BB, &sst);
     if (r1 != SIM_OK && r1 != SIM_ENOTCONV) return r1;
     if (r1 == SIM_ENOTCONV) src = r1;
-    CKH(interp_grad<double>(ker, g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, BB, 1.0, nullptr, 0.0, A3, st));
+    CKH(points_grad(s, BB, 1.0, nullptr, 0.0, A3));
     CKH(grad_apply(g, BB, F3, 1.0, nullptr, st));
     CKH(interp_dx(ker, g, K, s->XS, F3, phipk, 1.0, A4, st));
     CKH(scale3(K, A1, 1.0, A3, 1.0, A1, st));
@@ -2408,7 +2453,7 @@ sim_status exact_schur_matvec(sim_t s, const double *z, double *w, int *cg_iters
     return SIM_OK;
   };
   // q = B z
-  CKH(interp_grad<double>(s->ker, g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, -1.0, nullptr, 0.0, q, st));
+  CKH(points_grad(s, z, -1.0, nullptr, 0.0, q));
   CKH(scale3(s->K, q, 1.0 / s->c, nullptr, 0.0, y, st));
   if ((rc = applyC(y, ap))) return rc;
   CKH(scale3(s->K, q, 1.0, ap, -1.0, r, st));
@@ -2433,7 +2478,7 @@ sim_status exact_schur_matvec(sim_t s, const double *z, double *w, int *cg_iters
   if (cg_iters) *cg_iters = it;
   if (rr > 1e-26 * q2) return fail(s, SIM_ENOTCONV, "inner conjugate gradients on W^T W did not converge");
   // w += B^T y = D W y
-  CKH(band_apply(s->ker, true, g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, y, 1.0, w, st));
+  CKH(points_spread_div(s, y, 1.0, w));
   return SIM_OK;
 }
 

@@ -253,6 +253,34 @@ hipError_t band_apply(int ker, bool div, const Geo &g, int nt1, int nt2, int nac
                       const int *lstart, const int *list, const double *X, const double *q, double alpha,
                       float *out, hipStream_t s, bool f32 = true);
 
+// ---- coupling term of S~ in float64 (kernels_couple.hip) -----------------------
+// The placed points as its kernels take them: the nitems workgroups of
+// points (couple_items) and every tile's share of them (parts), the sorted
+// positions, the nactive active tiles in launch order, and the region buffer
+// (couple_region_bytes; written and read within a call).
+struct Coupling {
+  int ker, nt0, nt1, nt2, nitems, nactive;
+  const int4 *items;
+  const int2 *parts;
+  const int *active;
+  const double *X;
+  double *region;
+};
+long long couple_max_items(long long K, long long ntiles);
+size_t couple_region_bytes(long long K, long long ntiles);
+// the workgroups of the n non-empty tiles listed in tiles (tile-index order);
+// chunks, first (n + 1) and tmp are work arrays, first[n] the item count
+hipError_t couple_items(int n, const int *tiles, const int *tstart, int *chunks, int *first, int *tmp, int4 *items,
+                        int2 *parts, int ntiles, hipStream_t s);
+// w += alpha D W W^T G z
+template <typename T>
+hipError_t couple_product(const Geo &g, const Coupling &c, const T *z, double alpha, double *w, hipStream_t s);
+// out = alpha W^T G z + beta y (y may be null)
+hipError_t couple_interp(const Geo &g, const Coupling &c, const double *z, double alpha, const double *y, double beta,
+                         double *out, hipStream_t s);
+// out += alpha D W q
+hipError_t couple_spread(const Geo &g, const Coupling &c, const double *q, double alpha, double *out, hipStream_t s);
+
 // ---- reductions / Krylov vector kernels (kernels_krylov.hip) ---------------
 int red_blocks();
 // basis V of type TV (float32 in the FP32-MG form, float64 otherwise); n, stride even

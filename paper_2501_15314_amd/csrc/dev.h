@@ -27,7 +27,7 @@ struct Geo {
   int n0, n1, n2, hn2;
   long long half;   // n0*n1*hn2
   int bc0, bc1, bc2;  // 0 periodic, 1 no-slip wall, 2 free-slip wall (Neumann for cell fields)
-  int march_min_blocks;  // see MARCH_MIN_BLOCKS_DEFAULT
+  int mbx, mby, mch;  // workgroup shape and planes per workgroup of the plane-marching kernels (make_geo)
   double h, h2;     // cell width and its square
 };
 

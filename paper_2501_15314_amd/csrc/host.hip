@@ -406,8 +406,8 @@ size_t layout(sim_s *s, const sim_config *c, int64_t kmax, void *base, const std
   for (int l = 0; l < nlev; ++l) {
     Level L;
     double h = c->len[0] / c->n[0] * (double)(1 << l);
-    L.g = make_geo(dims[3 * l], dims[3 * l + 1], dims[3 * l + 2], c->bc[0], c->bc[1], c->bc[2], h);
-    L.g.march_min_blocks = march_min_blocks_setting();
+    L.g = make_geo(dims[3 * l], dims[3 * l + 1], dims[3 * l + 2], c->bc[0], c->bc[1], c->bc[2], h,
+                   march_min_blocks_setting());
     lv.push_back(L);
   }
   // the momentum residual writes one partial per plane-march workgroup

@@ -62,7 +62,7 @@ struct RowLaunch {
 };
 RowLaunch row_launch(const Geo &g, int nz);  // nz = grid.z (2*n0*ncomp, or n0 for one colour)
 
-Geo make_geo(int n0, int n1, int n2, int bc0, int bc1, int bc2, double h);
+Geo make_geo(int n0, int n1, int n2, int bc0, int bc1, int bc2, double h, int march_min_blocks);
 inline long long geo_cells(const Geo &g) { return 2 * g.half; }
 
 // ---- grid kernels (kernels_grid.hip) ---------------------------------------

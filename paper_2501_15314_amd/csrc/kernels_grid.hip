@@ -16,12 +16,36 @@
 
 namespace ibs {
 
-Geo make_geo(int n0, int n1, int n2, int bc0, int bc1, int bc2, double h) {
+// Workgroup shape of the plane-marching kernels: mbx threads along axis 2
+// (two in-row indices each) by mby rows, at most 256 threads, both dividing
+// the grid, mby even where the grid allows (the restriction pairs rows).
+// 64 or 32 threads along axis 2 where those divide the row; else the largest
+// divisor up to 64, since a short row pays its halo columns and loses the
+// coalescing: L z on 160 x 160 x 240 takes 41.6 us with the power of two that
+// divides the row (4 x 32 threads), 16.8 us with 60 x 4 or 30 x 8; a momentum
+// half sweep 108 and 26 us; a float64 half sweep on 80 x 96 x 112 6.9 us with
+// 4 x 32 and 5.6 us with 28 x 8.
+static void march_tile(Geo &g) {
+  const int q = g.hn2 / 2 > 0 ? g.hn2 / 2 : 1;
+  g.mbx = q % 64 == 0 ? 64 : (q % 32 == 0 ? 32 : (q < 64 ? q : 64));
+  while (q % g.mbx) --g.mbx;
+  g.mby = 256 / g.mbx;
+  while (g.n1 % g.mby || (g.mby % 2 && g.n1 % 2 == 0)) --g.mby;
+}
+
+Geo make_geo(int n0, int n1, int n2, int bc0, int bc1, int bc2, double h, int march_min_blocks) {
   Geo g;
   g.n0 = n0; g.n1 = n1; g.n2 = n2; g.hn2 = n2 / 2;
   g.half = (long long)n0 * n1 * (n2 / 2);
   g.bc0 = bc0; g.bc1 = bc1; g.bc2 = bc2;
-  g.march_min_blocks = MARCH_MIN_BLOCKS_DEFAULT;
+  march_tile(g);
+  // planes per workgroup: MARCH_CH on large grids (long register-window
+  // chains, few halo re-reads), halved until the grid has march_min_blocks
+  // workgroups on coarse multigrid levels, where latency rather than bytes
+  // bounds a sweep
+  const long long xy = (long long)((g.hn2 + 2 * g.mbx - 1) / (2 * g.mbx)) * (g.n1 / g.mby);
+  g.mch = MARCH_CH;
+  while (g.mch > 1 && xy * ((g.n0 + g.mch - 1) / g.mch) < march_min_blocks) g.mch >>= 1;
   g.h = h; g.h2 = h * h;
   return g;
 }

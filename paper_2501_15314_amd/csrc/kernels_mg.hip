@@ -54,7 +54,7 @@ __device__ __forceinline__ T nb_sum(const Geo &g, const T *x, int i, int j, int 
 // sums them over the plane pair, and the pair of rows is combined through
 // LDS; the even-row thread writes the two coarse values (one per colour).
 // The chunk of planes per workgroup is even, so a pair never splits.
-__host__ __device__ inline int restrict_chunk(const Geo &gf) { return march_chunk(gf) < 2 ? 2 : march_chunk(gf); }
+__host__ __device__ inline int restrict_chunk(const Geo &gf) { return gf.mch < 2 ? 2 : gf.mch; }
 
 template <typename T, typename TB>
 __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB *bf, Geo gc, T *bc) {
@@ -139,7 +139,7 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_prolong(Geo gf, T *xf, Geo gc, const T *xc) {
   const int BX = blockDim.x, BY = blockDim.y;
   const int m0 = 2 * (blockIdx.x * BX + threadIdx.x), j = blockIdx.y * BY + threadIdx.y;
-  const int len = march_chunk(gf);
+  const int len = gf.mch;
   const int i0 = blockIdx.z * len, i1 = min(i0 + len, gf.n0);
   auto side = [](int C, int o, int n, int bc) { return (o < 0 || o >= n) ? (bc ? C : (o < 0 ? o + n : o - n)) : o; };
   const int J = j >> 1, Jo = side(J, J + ((j & 1) ? 1 : -1), gc.n1, gc.bc1);

@@ -2,7 +2,7 @@
 //
 // A workgroup owns a tile of BY rows (axis 1) x 2*BX in-row indices m
 // (axis 2, two per thread, accessed as 2-vectors) and marches over a chunk of
-// planes along axis 0 (march_chunk).  The x-neighbours of a cell come from a
+// planes along axis 0 (Geo::mbx, mby, mch).  The x-neighbours of a cell come from a
 // register window over three planes, the y- and z-neighbours from an LDS copy
 // of the current plane with a one-cell halo.  BX divides hn2/2 and BY divides
 // n1, so no workgroup is partial and every halo cell is loaded.
@@ -19,33 +19,13 @@ struct MarchShape {
   dim3 grid, block;
 };
 
-__host__ __device__ inline int pow2_divisor(int n, int cap) {
-  int p = 1;
-  while (p * 2 <= cap && n % (p * 2) == 0) p *= 2;
-  return p;
-}
-
-// Planes per workgroup: MARCH_CH on large grids (long register-window
-// chains, few halo re-reads), halved until the grid has g.march_min_blocks
-// workgroups on coarse multigrid levels, where latency rather than bytes
-// bounds a sweep.
-__host__ __device__ inline int march_chunk(const Geo &g) {
-  const int bx = pow2_divisor(g.hn2 / 2, 64);
-  const int by = pow2_divisor(g.n1, 256 / bx);
-  const long long xy = (long long)(g.hn2 / (2 * bx)) * (g.n1 / by);
-  int ch = MARCH_CH;
-  while (ch > 1 && xy * ((g.n0 + ch - 1) / ch) < g.march_min_blocks) ch >>= 1;
-  return ch;
-}
-
 // ncomp stacks independent component grids along grid.z.
 inline MarchShape march_shape(const Geo &g, int ncomp) {
   MarchShape s;
-  s.bx = pow2_divisor(g.hn2 / 2, 64);
-  s.by = pow2_divisor(g.n1, 256 / s.bx);
+  s.bx = g.mbx;
+  s.by = g.mby;
   s.block = dim3(s.bx, s.by, 1);
-  const int ch = march_chunk(g);
-  int nch = (g.n0 + ch - 1) / ch;
+  int nch = (g.n0 + g.mch - 1) / g.mch;
   s.grid = dim3(g.hn2 / (2 * s.bx), g.n1 / s.by, nch * ncomp);
   return s;
 }
@@ -126,7 +106,7 @@ __device__ __forceinline__ MarchPos march_pos(const Geo &g, bool xcd) {
   p.jbase = mb.y * blockDim.y;
   p.m0 = p.mbase + 2 * threadIdx.x;
   p.j = p.jbase + threadIdx.y;
-  const int len = march_chunk(g);
+  const int len = g.mch;
   int nch = (g.n0 + len - 1) / len;
   p.comp = mb.z / nch;
   int ch = mb.z - p.comp * nch;

@@ -231,4 +231,46 @@ __device__ __forceinline__ TA sum16(TA v) {
   return v;
 }
 
+
+// Exclusive scan of n integers by one workgroup of SCAN1_T threads, four per
+// thread and pass: put(i, value, sum of the values before it) for every i;
+// returns the total.
+constexpr int SCAN1_T = 1024;
+template <class G, class P>
+__device__ __forceinline__ int block_scan(int n, G get, P put) {
+  __shared__ int wsum[SCAN1_T / 64];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int carry = 0;
+  for (int base = 0; base < n; base += 4 * SCAN1_T) {
+    const int i0 = base + 4 * tid;
+    int v[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = i0 + q < n ? get(i0 + q) : 0;
+      sum += v[q];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int ex = carry + incl - sum;
+#pragma unroll
+    for (int w = 0; w < SCAN1_T / 64; ++w) {
+      ex += w < wave ? wsum[w] : 0;
+      carry += wsum[w];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (i0 + q < n) put(i0 + q, v[q], ex);
+      ex += v[q];
+    }
+    __syncthreads();
+  }
+  return carry;
+}
+
 }  // namespace ibs

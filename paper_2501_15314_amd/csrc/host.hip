@@ -190,6 +190,16 @@ struct Carver {
   T *arr(long long n) { return (T *)take(sizeof(T) * (size_t)(n > 0 ? n : 1)); }
 };
 
+// The float64 form runs the coupling term on the matrix cores
+// (kernels_couple.hip: 36 + 13 us for an S~ product's pair at 256^3 with
+// 144000 points; 32 + 68 us from the touch lists).  The forms with float32
+// or bfloat16 arithmetic inside keep the list kernels, bit for bit: their
+// roundings turn a last-bit change of a right-hand side into one near the
+// size of the solve's tolerance.
+bool couple_on_matrix_cores(const sim_config *c) {
+  return c->precision == SIM_PREC_FP64 && c->precond != SIM_PRECOND_FASTDIAG;
+}
+
 bool is_even(int x) { return (x & 1) == 0; }
 
 // IBSCHUR_MARCH_FULL_CHUNKS=1 in the environment at sim_create: every grid,
@@ -434,8 +444,7 @@ size_t layout(sim_s *s, const sim_config *c, int64_t kmax, void *base, const std
   long long tl_cap = 27 * K;  // a point touches at most 3 x 3 x 3 tiles
   int *TCOUNT = cv.arr<int>(nt), *TLSTART = cv.arr<int>(nt + 1), *TLIST = cv.arr<int>(tl_cap);
   int *NZT = cv.arr<int>(nt + 8);
-  // the bfloat16 fast diagonalisation keeps the list kernels (points_grad)
-  const bool cpl = c->precond != SIM_PRECOND_FASTDIAG;
+  const bool cpl = couple_on_matrix_cores(c);
   int4 *ITEMS = cv.arr<int4>(cpl ? couple_max_items(K, nt) : 0);
   int2 *PARTS = cv.arr<int2>(cpl ? nt : 0);
   double *REGION = (double *)cv.take(cpl ? couple_region_bytes(K, nt) : 0);
@@ -579,7 +588,7 @@ sim_status place_and_bin(sim_t s, const std::vector<BodyDev> &bd) {
   CKH(gather3(s->K, s->PERM, s->XN, s->XS, st));
   CKH(gather3(s->K, s->PERM, s->UN, s->US, st));
   // non-empty point tiles (the interpolation work list; their neighbourhoods hold the touch-list candidates)
-  CKH(positive_flags(nt, s->COUNTS, s->FLAGS, st));
+  CKH(positive_flags(nt, s->COUNTS, s->FLAGS, st, couple_on_matrix_cores(&s->cfg) ? s->PARTS : nullptr));
   CKH(scan_exclusive(s->FLAGS, s->FPOS, nt, s->SCANTMP, st));
   CKH(compact(nt, s->FLAGS, s->FPOS, s->ACTIVE, st));
   int nz = 0;
@@ -589,13 +598,10 @@ sim_status place_and_bin(sim_t s, const std::vector<BodyDev> &bd) {
   s->nnz = order_launch_count(nz);  // launch count of NZT (holes included)
   // interpolation launch order of the non-empty point tiles: XCD chunks, fullest first
   CKH(order_active(nz, s->ACTIVE, s->TSTART, s->NZT, st));
-  // the coupling term's workgroups (FILLC, TLSTART and SCANTMP are free here);
-  // their number is read with the touch lists' below
-  int ni = 0;
-  if (!s->fastdiag)
-    CKH(couple_items(nz, s->ACTIVE, s->TSTART, s->FILLC, s->TLSTART, s->SCANTMP, s->ITEMS, s->PARTS, nt, st));
-  if (!s->fastdiag && nz > 0)
-    CKH(hipMemcpyAsync((int *)s->hpin + 2, s->TLSTART + nz, sizeof(int), hipMemcpyDeviceToHost, st));
+  // the coupling term's workgroups; their number is read with the touch lists' below
+  const bool cpl = couple_on_matrix_cores(&s->cfg);
+  if (cpl)
+    CKH(couple_items(nz, s->ACTIVE, s->TSTART, s->ITEMS, s->PARTS, (int *)s->hpin_dev + 2, st));
   // touch lists of the active tiles (tiles reached by some point's support),
   // counted and filled tile by tile in a fixed order; only the tiles within
   // one tile of a non-empty point tile can be reached (candidates, compacted
@@ -617,8 +623,8 @@ sim_status place_and_bin(sim_t s, const std::vector<BodyDev> &bd) {
   CKH(hipStreamSynchronize(st));
   memcpy(&na, s->hpin, sizeof(int));
   memcpy(&M, (int *)s->hpin + 1, sizeof(int));
-  if (!s->fastdiag && nz > 0) memcpy(&ni, (int *)s->hpin + 2, sizeof(int));
-  s->nitems = ni;
+  s->nitems = 0;
+  if (cpl) memcpy(&s->nitems, (int *)s->hpin + 2, sizeof(int));
   if (M > s->tl_cap) return fail(s, SIM_EDEVICE, "touch list overflow");
   CKH(touch_tiles(s->ker, s->g, s->nt0, s->nt1, s->nt2, na, nullptr, s->ACTIVE, s->TSTART, s->XS, nullptr,
                   s->TLSTART, s->TLIST, st));
@@ -655,19 +661,14 @@ Coupling coupling(const sim_s *s) {
   return {s->ker, s->nt0, s->nt1, s->nt2, s->nitems, s->nactive, s->ITEMS, s->PARTS, s->ACTIVE, s->XS, s->REGION};
 }
 
-// out = alpha W^T G z + beta y and out += alpha D W q, float64.  On the matrix
-// cores (kernels_couple.hip; at 256^3 with 144000 points an S~ product's
-// pair takes 36 + 13 us there, 32 + 68 us from the touch lists) except with
-// the bfloat16 fast diagonalisation: its roundings turn a last-bit change of
-// a right-hand side into one of the size of the solve's tolerance, and the
-// list kernels keep that form's results bit for bit.
+// out = alpha W^T G z + beta y and out += alpha D W q, float64
 hipError_t points_grad(sim_t s, const double *z, double alpha, const double *y, double beta, double *out) {
-  if (!s->fastdiag) return couple_interp(s->g, coupling(s), z, alpha, y, beta, out, s->st);
+  if (couple_on_matrix_cores(&s->cfg)) return couple_interp(s->g, coupling(s), z, alpha, y, beta, out, s->st);
   return interp_grad<double>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, alpha, y, beta, out,
                              s->st);
 }
 hipError_t points_spread_div(sim_t s, const double *q, double alpha, double *out) {
-  if (!s->fastdiag) return couple_spread(s->g, coupling(s), q, alpha, out, s->st);
+  if (couple_on_matrix_cores(&s->cfg)) return couple_spread(s->g, coupling(s), q, alpha, out, s->st);
   return band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha,
                     out, s->st);
 }
@@ -697,14 +698,16 @@ sim_status schur_matvec(sim_t s, const T *z, TW *w) {
     ProbeExt pr(PR_LAP, s->st, (double)s->N * (sizeof(T) + sizeof(TW)));  // z read, w written
     CKH((lap_apply<T, TW>(s->g, z, w, s->st)));
   }
-  if (f32 || s->fastdiag) {
-    CKH(interp_grad<T>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, 1.0, nullptr, 0.0, s->Q,
-                       s->st, f32));
-    CKH(band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, s->Q,
-                   -1.0 / s->c, w, s->st, f32));
-  } else if constexpr (!f32) {
-    CKH(couple_product<T>(s->g, coupling(s), z, -1.0 / s->c, w, s->st));
+  if constexpr (std::is_same<T, double>::value) {
+    if (couple_on_matrix_cores(&s->cfg)) {
+      CKH(couple_product(s->g, coupling(s), z, -1.0 / s->c, w, s->st));
+      return SIM_OK;
+    }
   }
+  CKH(interp_grad<T>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, 1.0, nullptr, 0.0, s->Q,
+                     s->st, f32));
+  CKH(band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, s->Q,
+                 -1.0 / s->c, w, s->st, f32));
   return SIM_OK;
 }
 

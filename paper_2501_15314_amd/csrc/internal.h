@@ -243,7 +243,8 @@ hipError_t mark_near(const Geo &g, int nt0, int nt1, int nt2, int n, const int *
 // each chunk): order_launch_count(n) entries, -1 in the holes
 hipError_t order_active(int n, const int *active, const int *lstart, int *out, hipStream_t s);
 int order_launch_count(int n);
-hipError_t positive_flags(int n, const int *counts, int *flags, hipStream_t s);
+// flags = counts > 0; clear (optional) = 0
+hipError_t positive_flags(int n, const int *counts, int *flags, hipStream_t s, int2 *clear = nullptr);
 // band: for the active band tiles, out += alpha D (W q)   (div = true, cell field)
 //                          or out += alpha W q       (div = false, face field)
 hipError_t band_apply(int ker, bool div, const Geo &g, int nt1, int nt2, int nactive, const int *active,
@@ -268,13 +269,12 @@ struct Coupling {
 };
 long long couple_max_items(long long K, long long ntiles);
 size_t couple_region_bytes(long long K, long long ntiles);
-// the workgroups of the n non-empty tiles listed in tiles (tile-index order);
-// chunks, first (n + 1) and tmp are work arrays, first[n] the item count
-hipError_t couple_items(int n, const int *tiles, const int *tstart, int *chunks, int *first, int *tmp, int4 *items,
-                        int2 *parts, int ntiles, hipStream_t s);
+// the workgroups of the n non-empty tiles listed in tiles (tile-index order),
+// their count in *total; parts holds count 0 for every tile before
+hipError_t couple_items(int n, const int *tiles, const int *tstart, int4 *items, int2 *parts, int *total,
+                        hipStream_t s);
 // w += alpha D W W^T G z
-template <typename T>
-hipError_t couple_product(const Geo &g, const Coupling &c, const T *z, double alpha, double *w, hipStream_t s);
+hipError_t couple_product(const Geo &g, const Coupling &c, const double *z, double alpha, double *w, hipStream_t s);
 // out = alpha W^T G z + beta y (y may be null)
 hipError_t couple_interp(const Geo &g, const Coupling &c, const double *z, double alpha, const double *y, double beta,
                          double *out, hipStream_t s);

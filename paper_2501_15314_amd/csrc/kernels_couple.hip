@@ -30,8 +30,12 @@
 // hold it (those of two tiles per axis), in a fixed order.  No atomics; every
 // sum has a fixed order, so results repeat bitwise.
 //
-// Bound by load latency and instruction issue, not bytes (144000 points in a
-// 256^3 grid: about 12 MB per product).
+// Bound by load latency and instruction issue, not bytes: 144000 points in a
+// 256^3 grid (about 25 MB) take 36 us for the product and 13 us for the
+// region sums, 300 points in 32^3 5.9 + 4.6 us; from the touch lists, which
+// stage a point about six times, 32 + 68 us and 7.3 + 6.7 us.  Points are
+// split into workgroups of 64 and not looped over: 55 us with one workgroup
+// per tile.
 #include <hip/hip_ext.h>
 
 #include "internal.h"
@@ -69,49 +73,47 @@ enum { CP_PRODUCT = 0, CP_INTERP = 1, CP_SPREAD = 2 };
 
 // The workgroups' work: at most CPTS points of one tile each, tiles in index
 // order, a tile's points cut into even shares of whole 16-point groups.
-// chunks[q] is the workgroup count of the q-th non-empty tile; first[] its
-// exclusive scan.  item = (tile, first point, end, 0); parts[tile] = (first
-// item, count), count 0 for tiles without points.
-__device__ __forceinline__ int couple_share(int np, int nc) { return (((np + nc - 1) / nc) + 15) & ~15; }
-__global__ void k_couple_count(int n, const int *tiles, const int *tstart, int *chunks) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  const int t = tiles[q];
-  chunks[q] = (tstart[t + 1] - tstart[t] + CPTS - 1) / CPTS;
+// item = (tile, first point, end, 0); parts[tile] = (first item, count), set
+// for the listed tiles (the others hold count 0).  One workgroup; the item
+// count is written to *total.
+__global__ void __launch_bounds__(SCAN1_T) k_couple_items(int n, const int *tiles, const int *tstart, int4 *items,
+                                                          int2 *parts, int *total) {
+  const int sum = block_scan(
+      n,
+      [&](int q) {
+        const int t = tiles[q];
+        return (tstart[t + 1] - tstart[t] + CPTS - 1) / CPTS;
+      },
+      [&](int q, int nc, int f) {
+        const int t = tiles[q], s0 = tstart[t], s1 = tstart[t + 1];
+        const int share = ((s1 - s0 + nc - 1) / nc + 15) & ~15;
+        for (int c = 0; c < nc; ++c)
+          items[f + c] = make_int4(t, min(s0 + c * share, s1), min(s0 + (c + 1) * share, s1), 0);
+        parts[t] = make_int2(f, nc);
+      });
+  if (threadIdx.x == 0) *total = sum;
 }
-__global__ void k_couple_items(int n, const int *tiles, const int *tstart, const int *first, int4 *items, int2 *parts) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  const int t = tiles[q], s0 = tstart[t], s1 = tstart[t + 1], f = first[q], nc = first[q + 1] - f;
-  const int share = couple_share(s1 - s0, nc);
-  for (int c = 0; c < nc; ++c)
-    items[f + c] = make_int4(t, min(s0 + c * share, s1), min(s0 + (c + 1) * share, s1), 0);
-  parts[t] = make_int2(f, nc);
-}
-hipError_t couple_items(int n, const int *tiles, const int *tstart, int *chunks, int *first, int *tmp, int4 *items,
-                        int2 *parts, int ntiles, hipStream_t s) {
-  // no points: no items, every count 0
-  hipError_t e = fill_i32((int *)parts, 2LL * ntiles, 0, s);
-  if (e != hipSuccess || n == 0) return e;
-  const dim3 gr((n + 255) / 256), bl(256);
-  hipLaunchKernelGGL(k_couple_count, gr, bl, 0, s, n, tiles, tstart, chunks);
-  if ((e = scan_exclusive(chunks, first, n, tmp, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_couple_items, gr, bl, 0, s, n, tiles, tstart, first, items, parts);
+hipError_t couple_items(int n, const int *tiles, const int *tstart, int4 *items, int2 *parts, int *total,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(k_couple_items, dim3(1), dim3(SCAN1_T), 0, s, n, tiles, tstart, items, parts, total);
   return hipGetLastError();
 }
-// a tile's share of CPTS + 1 points is 48, so extra workgroups need points of their own
 long long couple_max_items(long long K, long long ntiles) { return (K < ntiles ? K : ntiles) + K / CPTS; }
+// The region buffer holds at most CBATCH items (64 MiB); a product over more
+// items (points scattered over that many tiles) runs in batches of as many.
+constexpr int CBATCH = 16384;
 size_t couple_region_bytes(long long K, long long ntiles) {
-  return sizeof(double) * CR3 * (size_t)couple_max_items(K, ntiles);
+  const long long m = couple_max_items(K, ntiles);
+  return sizeof(double) * CR3 * (size_t)(m < CBATCH ? m : CBATCH);
 }
 
-//   CP_PRODUCT: region = D W W^T G z (times h), z of type T
+//   CP_PRODUCT: region = D W W^T G z (times h), z a cell field
 //   CP_INTERP:  out = alpha W^T G z + beta y
 //   CP_SPREAD:  region = D W q (times h)
-template <int KER, int MODE, typename T>
+template <int KER, int MODE>
 __global__ void __launch_bounds__(256, 4)
-k_couple(Geo g, double ih, int nt1, int nt2, int nitems, const int4 *items,
-         const double *X, const T *z, const double *q, double *region, double alpha, const double *y, double beta, double *out) {
+k_couple(Geo g, double ih, int nt1, int nt2, int nitems, const int4 *__restrict__ items,
+         const double *X, const double *z, const double *q, double *region, double alpha, const double *y, double beta, double *out) {
   constexpr int W = KerWidth<KER>::W;
   __shared__ double reg[MODE == CP_SPREAD ? 1 : CR * CRS];
   __shared__ __align__(16) double wts[CPTS * CPS];
@@ -133,7 +135,7 @@ k_couple(Geo g, double ih, int nt1, int nt2, int nitems, const int4 *items,
   const double xs = sp < np ? X[3 * s0 + tid] : 0.0;
   double qv = 0.0;
   if (MODE == CP_SPREAD) qv = sp < np ? q[3 * s0 + tid] : 0.0;
-  T zv[CR3 / 256];
+  double zv[CR3 / 256];
   if (MODE != CP_SPREAD) {
     // the region: two rows of eight z cells per 16 lanes; cells outside a
     // wall box hold 0 (no support reaches them).  A region reaches at most
@@ -153,8 +155,8 @@ k_couple(Geo g, double ih, int nt1, int nt2, int nitems, const int4 *items,
       bool ok = okjk;
       if (g.bc0) ok = ok && (unsigned)i < (unsigned)g.n0;
       else i += (i < 0 ? g.n0 : 0) - (i >= g.n0 ? g.n0 : 0);
-      const T *zc = z + (((i + j + k) & 1) ? g.half : 0);
-      zv[u] = ok ? zc[(unsigned)i * plane + ojk] : T(0);
+      const double *zc = z + (((i + j + k) & 1) ? g.half : 0);
+      zv[u] = ok ? zc[(unsigned)i * plane + ojk] : 0.0;
     }
   }
   if (sp < np16) {
@@ -306,7 +308,7 @@ k_couple(Geo g, double ih, int nt1, int nt2, int nitems, const int4 *items,
 // a cell c = 0..3 of tile T lies in the regions of T (at c + 2) and of T - 1
 // (at c + 6, c < 2) or T + 1 (at c - 2, c >= 2); tiles without points and
 // past a wall have none.  One wavefront per tile.
-__global__ void __launch_bounds__(256) k_region_add(Geo g, int nt0, int nt1, int nt2, int nactive,
+__global__ void __launch_bounds__(256) k_region_add(Geo g, int nt0, int nt1, int nt2, int lo, int hi, int nactive,
                                                     const int *__restrict__ active, const int2 *__restrict__ parts,
                                                     const double *__restrict__ region, double alpha, double *__restrict__ out) {
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -331,7 +333,10 @@ __global__ void __launch_bounds__(256) k_region_add(Geo g, int nt0, int nt1, int
 #pragma unroll
   for (int o = 0; o < 8; ++o) {
     const int a0 = tn[0][o >> 2], a1 = tn[1][(o >> 1) & 1], a2 = tn[2][o & 1];
-    pt[o] = (a0 | a1 | a2) >= 0 ? parts[(a0 * nt1 + a1) * nt2 + a2] : make_int2(0, 0);
+    const int2 p = (a0 | a1 | a2) >= 0 ? parts[(a0 * nt1 + a1) * nt2 + a2] : make_int2(0, 0);
+    // the tile's items of this batch, [lo, hi)
+    const int f = max(p.x, lo);
+    pt[o] = make_int2(f - lo, min(p.x + p.y, hi) - f);
   }
   // each tile's first two regions are loaded before any is added
   double v[8], v1[8];
@@ -352,56 +357,58 @@ __global__ void __launch_bounds__(256) k_region_add(Geo g, int nt0, int nt1, int
   out[e] = old + alpha * sum;
 }
 
-template <int MODE, typename T>
-static void launch_couple(const Geo &g, const Coupling &c, const T *z, const double *q, double alpha, const double *y,
-                          double beta, double *out, hipStream_t s) {
+// items [lo, hi) of one batch (all of them for an interpolation)
+template <int MODE>
+static void launch_couple(const Geo &g, const Coupling &c, int lo, int hi, const double *z, const double *q, double alpha,
+                          const double *y, double beta, double *out, hipStream_t s) {
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
-  const dim3 gr(8 * ((c.nitems + 7) / 8)), bl(256);
+  const dim3 gr(8 * ((hi - lo + 7) / 8)), bl(256);
   if (c.ker == KER_PESKIN4)
-    hipExtLaunchKernelGGL((k_couple<KER_PESKIN4, MODE, T>), gr, bl, 0, s, e0, e1, 0, g, 1.0 / g.h, c.nt1, c.nt2, c.nitems,
-                          c.items, c.X, z, q, c.region, alpha, y, beta, out);
+    hipExtLaunchKernelGGL((k_couple<KER_PESKIN4, MODE>), gr, bl, 0, s, e0, e1, 0, g, 1.0 / g.h, c.nt1, c.nt2, hi - lo,
+                          c.items + lo, c.X, z, q, c.region, alpha, y, beta, out);
   else
-    hipExtLaunchKernelGGL((k_couple<KER_ROMA3, MODE, T>), gr, bl, 0, s, e0, e1, 0, g, 1.0 / g.h, c.nt1, c.nt2, c.nitems,
-                          c.items, c.X, z, q, c.region, alpha, y, beta, out);
+    hipExtLaunchKernelGGL((k_couple<KER_ROMA3, MODE>), gr, bl, 0, s, e0, e1, 0, g, 1.0 / g.h, c.nt1, c.nt2, hi - lo,
+                          c.items + lo, c.X, z, q, c.region, alpha, y, beta, out);
 }
-static void launch_region_add(const Geo &g, const Coupling &c, double alpha, double *out, hipStream_t s) {
+static void launch_region_add(const Geo &g, const Coupling &c, int lo, int hi, double alpha, double *out,
+                              hipStream_t s) {
   // the active tiles' cells read and written
   ProbeExt probe_(PR_BAND_DIV, s, (double)probe_band_cells() * 2 * sizeof(double));
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
-  hipExtLaunchKernelGGL(k_region_add, dim3((c.nactive + 3) / 4), dim3(256), 0, s, e0, e1, 0, g, c.nt0, c.nt1, c.nt2,
-                        c.nactive, c.active, c.parts, c.region, alpha / g.h, out);
+  hipExtLaunchKernelGGL(k_region_add, dim3((c.nactive + 3) / 4), dim3(256), 0, s, e0, e1, 0, g, c.nt0, c.nt1, c.nt2, lo,
+                        hi, c.nactive, c.active, c.parts, c.region, alpha / g.h, out);
 }
 
-template <typename T>
-hipError_t couple_product(const Geo &g, const Coupling &c, const T *z, double alpha, double *w, hipStream_t s) {
-  if (c.nitems == 0) return hipSuccess;
-  {
-    // positions and the cells of the support band read
-    ProbeExt probe_(PR_INTERP_GRAD, s, (double)probe_points() * 24 + (double)probe_band_cells() * sizeof(T));
-    launch_couple<CP_PRODUCT, T>(g, c, z, nullptr, 0.0, nullptr, 0.0, nullptr, s);
+hipError_t couple_product(const Geo &g, const Coupling &c, const double *z, double alpha, double *w, hipStream_t s) {
+  for (int lo = 0; lo < c.nitems; lo += CBATCH) {
+    const int hi = c.nitems - lo < CBATCH ? c.nitems : lo + CBATCH;
+    {
+      // positions and the cells of the support band read
+      ProbeExt probe_(PR_INTERP_GRAD, s, (double)probe_points() * 24 + (double)probe_band_cells() * sizeof(double));
+      launch_couple<CP_PRODUCT>(g, c, lo, hi, z, nullptr, 0.0, nullptr, 0.0, nullptr, s);
+    }
+    launch_region_add(g, c, lo, hi, alpha, w, s);
   }
-  launch_region_add(g, c, alpha, w, s);
   return hipGetLastError();
 }
-template hipError_t couple_product<float>(const Geo &, const Coupling &, const float *, double, double *, hipStream_t);
-template hipError_t couple_product<double>(const Geo &, const Coupling &, const double *, double, double *, hipStream_t);
-
 hipError_t couple_interp(const Geo &g, const Coupling &c, const double *z, double alpha, const double *y, double beta,
                          double *out, hipStream_t s) {
   if (c.nitems == 0) return hipSuccess;
   // positions read, results written (and y read), the cells of the support band
   ProbeExt probe_(PR_INTERP_GRAD, s,
                   (double)probe_points() * (y ? 72 : 48) + (double)probe_band_cells() * sizeof(double));
-  launch_couple<CP_INTERP, double>(g, c, z, nullptr, alpha, y, beta, out, s);
+  launch_couple<CP_INTERP>(g, c, 0, c.nitems, z, nullptr, alpha, y, beta, out, s);
   return hipGetLastError();
 }
 
 hipError_t couple_spread(const Geo &g, const Coupling &c, const double *q, double alpha, double *out, hipStream_t s) {
-  if (c.nitems == 0) return hipSuccess;
-  launch_couple<CP_SPREAD, double>(g, c, nullptr, q, 0.0, nullptr, 0.0, nullptr, s);
-  launch_region_add(g, c, alpha, out, s);
+  for (int lo = 0; lo < c.nitems; lo += CBATCH) {
+    const int hi = c.nitems - lo < CBATCH ? c.nitems : lo + CBATCH;
+    launch_couple<CP_SPREAD>(g, c, lo, hi, nullptr, q, 0.0, nullptr, 0.0, nullptr, s);
+    launch_region_add(g, c, lo, hi, alpha, out, s);
+  }
   return hipGetLastError();
 }
 

@@ -115,46 +115,13 @@ __global__ void k_scan3(int *out, int n, const int *bsum, int nb) {
   if (i < n) out[i] += bsum[i / SCAN_CHUNK];
   if (i == 0) out[n] = bsum[nb];
 }
-// The whole scan in one workgroup, 4096 items a pass, for the tile counts of
-// grids up to 128^3: a pass takes about a microsecond, the three launches
-// above about eight, whatever the size.
-constexpr int SCAN1_T = 1024, SCAN1_MAX = 8 * 4 * SCAN1_T;
+// The whole scan in one workgroup, 4096 items a pass: a pass takes about two
+// microseconds, the three launches above about eight together, so up to two
+// passes (the tile counts of grids up to 80^3).
+constexpr int SCAN1_MAX = 2 * 4 * SCAN1_T;
 __global__ void __launch_bounds__(SCAN1_T) k_scan_one(const int *in, int *out, int n) {
-  __shared__ int wsum[SCAN1_T / 64];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  int carry = 0;
-  for (int base = 0; base < n; base += 4 * SCAN1_T) {
-    const int i0 = base + 4 * tid;
-    int v[4], sum = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      v[q] = i0 + q < n ? in[i0 + q] : 0;
-      sum += v[q];
-    }
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
-    }
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    int before = carry, total = 0;
-#pragma unroll
-    for (int w = 0; w < SCAN1_T / 64; ++w) {
-      before += w < wave ? wsum[w] : 0;
-      total += wsum[w];
-    }
-    int ex = before + incl - sum;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (i0 + q < n) out[i0 + q] = ex;
-      ex += v[q];
-    }
-    carry += total;
-    __syncthreads();
-  }
-  if (tid == 0) out[n] = carry;
+  const int total = block_scan(n, [&](int i) { return in[i]; }, [&](int i, int, int ex) { out[i] = ex; });
+  if (threadIdx.x == 0) out[n] = total;
 }
 hipError_t scan_exclusive(const int *in, int *out, int n, int *tmp, hipStream_t s) {
   if (n <= SCAN1_MAX) {
@@ -578,12 +545,14 @@ hipError_t order_active(int n, const int *active, const int *lstart, int *out, h
   return hipGetLastError();
 }
 
-__global__ void k_positive(int n, const int *counts, int *flags) {
+__global__ void k_positive(int n, const int *counts, int *flags, int2 *clear) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) flags[t] = counts[t] > 0;
+  if (t >= n) return;
+  flags[t] = counts[t] > 0;
+  if (clear) clear[t] = make_int2(0, 0);
 }
-hipError_t positive_flags(int n, const int *counts, int *flags, hipStream_t s) {
-  hipLaunchKernelGGL(k_positive, dim3(nblk(n, 256)), dim3(256), 0, s, n, counts, flags);
+hipError_t positive_flags(int n, const int *counts, int *flags, hipStream_t s, int2 *clear) {
+  hipLaunchKernelGGL(k_positive, dim3(nblk(n, 256)), dim3(256), 0, s, n, counts, flags, clear);
   return hipGetLastError();
 }
 

@@ -82,3 +82,20 @@ def test_product_between_walls(bc):
     z = rng.standard_normal(S.g.n)
     assert rel(sim.apply("schur", z).cpu().numpy(), S.matvec(z)) < 1e-12
     sim.close()
+
+
+def test_scattered_points_run_in_batches():
+    """60000 points scattered over 24576 tiles: more workgroups than the
+    region buffer holds at once (16384)."""
+    rng = np.random.default_rng(9)
+    n, h = (128, 128, 96), 1.0 / 128
+    X = rng.uniform(0.0, 1.0, (60000, 3)) * np.array(n) * h
+    cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=P3, nu=0.02, dt=0.005, lump_c=1.0, mg_coarsest=8)
+    sim = Sim(cfg, len(X))
+    sim.set_bodies([wl.Body(center=np.zeros(3), vel=np.zeros(3), omega=np.zeros(3), radius=1.0, n_points=len(X))], X)
+    g = omac.Grid(n, h, P3)
+    S = oschur.SchurSystem(g, odelta.regularization_matrix(g, X, cfg.delta), cfg.lump_c)
+    z, rf = rng.standard_normal(n), rng.standard_normal((len(X), 3))
+    assert rel(sim.apply("schur", z).cpu().numpy(), S.matvec(z)) < 1e-12
+    assert rel(sim.apply("schur_rhs", z, rf).cpu().numpy(), S.rhs(z, rf)) < 1e-12
+    sim.close()

@@ -138,7 +138,7 @@ struct sim_s {
   // bfloat16 scratch grids
   bool fastdiag = false;
   bool fdx = false;                // exact float64 fast diagonalisation (preconditioner)
-  double *FDXQ = nullptr;          // its eigenbases and eigenvalues (fdx_blob_pack)
+  double *FDXQ = nullptr;          // its eigenbases and eigenvalues (fdx_blob_build)
   double *FDX1 = nullptr, *FDX2 = nullptr;  // two natural-layout float64 work grids
   bool coarse_mfma = false;  // exact coarse solve on the matrix cores
   unsigned char *FDQ = nullptr;  // packed eigenbases (fd_blob_pack)
@@ -679,11 +679,9 @@ hipError_t points_spread_div(sim_t s, const double *q, double alpha, double *out
 // output (to bytes per cell) written.
 double fd_bytes(const sim_s *s, size_t ti, size_t to) { return (double)s->N * (ti + 2 + 3 * 4 + 2 + to); }
 
-// Algorithmic bytes of one exact float64 fast-diagonalisation solve: the
-// split-layout input read and written in natural order, six mode products
-// each reading and writing the grid, the natural-order result read and
-// written in split order (16 passes of 8 bytes per cell).
-double fdx_bytes(const sim_s *s) { return (double)s->N * 16 * 8; }
+// Algorithmic bytes of one exact float64 fast-diagonalisation solve: six mode
+// products, each reading and writing the grid (12 passes of 8 bytes per cell).
+double fdx_bytes(const sim_s *s) { return (double)s->N * 12 * 8; }
 
 // w = S~ z = L z + c^-1 G^T W W^T G z  (= L z - c^-1 D W (W^T G z)), in
 // float64.  With TW = float (the products of the float32 FGMRES cycle, z in
@@ -1796,9 +1794,8 @@ sim_status sim_create(const sim_config *cfg, void *d_workspace, size_t bytes, in
     }
     if (s->fdx) {
       const int fn[3] = {cfg->n[0], cfg->n[1], cfg->n[2]};
-      std::vector<double> qd((size_t)coarse_fd_size(fn)), blob(fdx_blob_doubles(fn));
-      coarse_fd_build(fn, cbc, s->g.h, qd.data());
-      fdx_blob_pack(fn, qd.data(), blob.data());
+      std::vector<double> blob(fdx_blob_doubles(fn));
+      fdx_blob_build(fn, cbc, s->g.h, blob.data());
       if (hipMemcpy(s->FDXQ, blob.data(), sizeof(double) * blob.size(), hipMemcpyHostToDevice) != hipSuccess) {
         release_handle(s);
         return SIM_EDEVICE;

@@ -150,12 +150,12 @@ hipError_t fd_precond(const Geo &g, const TI *v, T *z, unsigned short *w1, unsig
                       float vscale, hipStream_t s);
 size_t fd_blob_bytes(const int n[3]);
 // z = L^+ v exactly by fast diagonalisation in float64 (split layout in and
-// out); w1, w2: natural-layout float64 scratch grids; blob: fdx_blob_pack of
-// coarse_fd_build's eigen-decomposition of the grid (device copy)
+// out); w1, w2: natural-layout float64 scratch grids; blob: fdx_blob_build of
+// the grid (device copy)
 hipError_t fdx_precond(const Geo &g, const double *v, double *z, double *w1, double *w2, const double *blob,
                        hipStream_t s);
 size_t fdx_blob_doubles(const int n[3]);
-void fdx_blob_pack(const int n[3], const double *q, double *blob);
+void fdx_blob_build(const int n[3], const int bc[3], double h, double *blob);
 void fd_blob_pack(const int n[3], const double *qd, unsigned char *out);
 
 void coarse_fd_build(const int n[3], const int bc[3], double h, double *out);

@@ -58,69 +58,108 @@ __host__ __device__ inline int restrict_chunk(const Geo &gf) { return gf.mch < 2
 
 template <typename T, typename TB>
 __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB *bf, Geo gc, T *bc) {
-  __shared__ T tile[MARCH_TILE];
+  __shared__ T tile[2][MARCH_TILE];
   __shared__ T pair[256][2];
   const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
-  const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + BX * ty;
-  const int m0 = 2 * (blockIdx.x * BX + tx), j = blockIdx.y * BY + ty;
-  const int len = restrict_chunk(gf);
-  const int i0 = blockIdx.z * len, i1 = min(i0 + len, gf.n0);
+  MarchPos p;
+  p.tx = threadIdx.x;
+  p.ty = threadIdx.y;
+  p.m0 = 2 * (blockIdx.x * BX + p.tx);
+  p.j = blockIdx.y * BY + p.ty;
+  const int tid = p.tx + BX * p.ty, len = restrict_chunk(gf);
+  p.i0 = blockIdx.z * len;
+  p.i1 = min(p.i0 + len, gf.n0);
   const T *red = xf, *blk = xf + gf.half;
-  const int mbase = blockIdx.x * BX * 2, jbase = blockIdx.y * BY;
-  auto row = [&](int i, int jj) { return ((long long)i * gf.n1 + jj) * gf.hn2; };
-  auto bval = [&](int i, int jj, int mm) -> T { return blk[row(i, jj) + mm]; };
-  auto bwin = [&](int i) -> V2<T> {
-    V2<T> v;
-    v.x = T(0);
-    v.y = T(0);
-    const int ii = mwrap(i, gf.n0, gf.bc0);
-    if (ii < 0) return v;
-    return ld2<T>(blk + row(ii, j) + m0);
-  };
+  const long long PC = (long long)gc.n1 * gc.hn2;
+  MarchOff at = march_off(gf, p.i0, p.i1);
+  const unsigned rw = p.j * gf.hn2 + p.m0;
+  // coarse row J at in-row index K / 2 (K = m0 is even): the same place in both colour planes
+  const unsigned cw = (unsigned)((p.j >> 1) * gc.hn2 + (p.m0 >> 1)) * sizeof(T);
+  const MarchEdge e = march_edge(gf, p, BX, BY, [&](int q) { tile[0][q] = tile[1][q] = T(0); });
+  const unsigned eoff = (unsigned)(e.jr * gf.hn2 + e.mr) * sizeof(T), coff = (unsigned)(p.j * gf.hn2 + e.mc) * sizeof(T);
   const T ih2 = (T)(1.0 / gf.h2);
+  // number of neighbours inside the grid, for the parities of even (i0) and odd planes
+  const int s0 = p.j & 1;
+  T nt[2][2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) nt[f][u] = (T)(6 - diag_jk(gf, p.j, 2 * (p.m0 + u) + (f ? 1 - s0 : s0), false, 0));
+  const int z0 = gf.bc0 ? 0 : -2, z1 = gf.bc0 ? gf.n0 - 1 : -2;  // planes at a wall of axis 0
+  struct Ops {
+    V2<T> hr, x, b, w;
+    T hc;
+  };
+  auto fetch = [&](Ops &o) {
+    const T *bp = blk + at.nxt;
+    o.hr = ld2<T>(bp, eoff);
+    o.hc = ldo(bp, coff);
+    o.x = ld2<T>(red + at.nxt, rw * (unsigned)sizeof(T));
+    o.b = ld2<T>(bf + at.nxt, rw * (unsigned)sizeof(TB));
+    o.w = ld2<T>(blk + at.win, rw * (unsigned)sizeof(T));
+  };
   T acc[2] = {T(0), T(0)};
-  V2<T> prev = bwin(i0 - 1), cur = bwin(i0);
-  for (int i = i0; i < i1; ++i) {
-    V2<T> next = bwin(i + 1);
-    tile[(ty + 1) * W2 + 2 * tx + 1] = cur.x;
-    tile[(ty + 1) * W2 + 2 * tx + 2] = cur.y;
-    tile_halo(tile, gf, i, jbase, mbase, BX, BY, bval);
+  // the coarse values of the plane pair that ends at plane i: this row and,
+  // from LDS, its partner (written by odd rows, read after the next barrier)
+  auto emit = [&](int i) {
+    if (p.ty & 1) return;
+    const T v0 = (acc[0] + pair[tid + BX][0]) * (T)0.125;
+    const T v1 = (acc[1] + pair[tid + BX][1]) * (T)0.125;
+    const int I = i >> 1;
+    const bool odd = (I + (p.j >> 1)) & 1;  // colour of (I, J, K)
+    T *o = bc + I * PC;
+    *(T *)((char *)o + cw) = odd ? v1 : v0;
+    *(T *)((char *)(o + gc.half) + cw) = odd ? v0 : v1;
+  };
+  // plane i (f = i & 1): as in k_sweep
+  auto step = [&](int i, int f, const V2<T> &wp, const V2<T> &wc, V2<T> &wn, const Ops &o, Ops &on) {
+    march_next(at, i);
+    fetch(on);
+    T *t = tile[f];
+    T *trow = t + (p.ty + 1) * W2 + 2 * p.tx;
+    trow[1] = wc.x;
+    trow[2] = wc.y;
+    if (e.rslot >= 0) {
+      t[e.rslot] = o.hr.x;
+      t[e.rslot + 1] = o.hr.y;
+    }
+    if (e.cslot >= 0) t[e.cslot] = o.hc;
+    if (e.thin && e.mthin >= 0) trow[3] = blk[at.cur + p.j * gf.hn2 + e.mthin];
     __syncthreads();
-    const long long r = row(i, j) + m0;
-    const V2<T> xr = ld2<T>(red + r);
-    const V2<T> br = ld2<T>(bf + r);
-    const int s = (i + j) & 1;
+    wn = i == z1 ? V2<T>{T(0), T(0)} : o.w;
+    if (f == 0) {
+      if (i > p.i0) emit(i - 1);
+      acc[0] = acc[1] = T(0);
+    }
+    const int s = f ? 1 - s0 : s0;
+    const bool edge = i == z0 || i == z1;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int k = 2 * (m0 + u) + s, col = 2 * tx + 1 + u;
-      const T *trow = tile + (ty + 1) * W2;
-      const T sum = (u ? prev.y : prev.x) + (u ? next.y : next.x) + tile[ty * W2 + col] + tile[(ty + 2) * W2 + col] +
-                    trow[col - 1 + s] + trow[col + s];
-      const T xv = u ? xr.y : xr.x, bv = u ? br.y : br.x;
-      acc[u] += pc_resid(bv, xv, sum, cell_nnb(gf, i, j, k), ih2);
+      const T sum = (u ? wp.y : wp.x) + (u ? wn.y : wn.x) + trow[u + 1 - W2] + trow[u + 1 + W2] + trow[u + s] +
+                    trow[u + 1 + s];
+      const T nn = edge ? nt[f][u] - T(1) : nt[f][u];
+      acc[u] += fma(-fma(nn, u ? o.x.y : o.x.x, -sum), ih2, u ? o.b.y : o.b.x);  // pc_resid
     }
-    if (i & 1) {
-      // plane pair done: add the partner row and write the coarse values
+    if (f == 1 && (p.ty & 1)) {
       pair[tid][0] = acc[0];
       pair[tid][1] = acc[1];
     }
-    __syncthreads();
-    if ((i & 1) && !(ty & 1)) {
-      const T v0 = (acc[0] + pair[tid + BX][0]) * (T)0.125;
-      const T v1 = (acc[1] + pair[tid + BX][1]) * (T)0.125;
-      const int I = i >> 1, J = j >> 1, K = m0;  // K even: colour of (I, J, K) is (I + J) & 1
-      const long long cr = ((long long)I * gc.n1 + J) * gc.hn2 + (K >> 1);
-      const int c0 = (I + J) & 1;
-      bc[(long long)c0 * gc.half + cr] = v0;
-      bc[(long long)(1 - c0) * gc.half + cr] = v1;
-    }
-    if (i & 1) {
-      acc[0] = T(0);
-      acc[1] = T(0);
-    }
-    prev = cur;
-    cur = next;
+  };
+  V2<T> w0 = ld2<T>(blk + march_prev(gf, at, p.i0), rw * (unsigned)sizeof(T));
+  V2<T> w1 = ld2<T>(blk + at.cur, rw * (unsigned)sizeof(T)), w2, w3;
+  Ops oa, ob;
+  fetch(oa);
+  if (p.i0 == z0) w0 = V2<T>{T(0), T(0)};
+  for (int i = p.i0;;) {  // i0 and i1 are even
+    step(i, 0, w0, w1, w2, oa, ob);
+    step(i + 1, 1, w1, w2, w3, ob, oa);
+    if ((i += 2) >= p.i1) break;
+    step(i, 0, w2, w3, w0, oa, ob);
+    step(i + 1, 1, w3, w0, w1, ob, oa);
+    if ((i += 2) >= p.i1) break;
   }
+  __syncthreads();
+  emit(p.i1 - 1);
 }
 
 // x_f += P x_c on the red fine cells only (the following black half sweep
@@ -130,80 +169,114 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
 // periodic axes wrap).
 //
 // Plane march over the fine grid: a thread owns the red cells at in-row
-// m0, m0+1 of fine row (i, j).  Along axis 0 the two coarse planes in use,
-// (i-1)>>1 and (i+1)>>1, are held in registers (each coarse plane is read
-// once per march); per plane the thread keeps its two coarse rows (parent and
-// neighbour along axis 1) at the four coarse K = m0-1 .. m0+2 that both
-// parities of the fine row need.
+// m0, m0+1 of fine row (i, j).  A coarse plane serves four fine planes, two of
+// each parity; its blend over axes 2 and 1 is formed once per parity when the
+// plane enters the march (plane_blend: from rows J (parent) and Jo at the four
+// coarse K = m0-1 .. m0+2) and kept, so that a fine plane takes one blend of
+// two kept values per cell.  The next coarse plane and the fine rows of the
+// next pair of planes are loaded before a pair is computed.
 template <typename T>
 __global__ void __launch_bounds__(256) k_prolong(Geo gf, T *xf, Geo gc, const T *xc) {
   const int BX = blockDim.x, BY = blockDim.y;
   const int m0 = 2 * (blockIdx.x * BX + threadIdx.x), j = blockIdx.y * BY + threadIdx.y;
   const int len = gf.mch;
   const int i0 = blockIdx.z * len, i1 = min(i0 + len, gf.n0);
-  auto side = [](int C, int o, int n, int bc) { return (o < 0 || o >= n) ? (bc ? C : (o < 0 ? o + n : o - n)) : o; };
-  const int J = j >> 1, Jo = side(J, J + ((j & 1) ? 1 : -1), gc.n1, gc.bc1);
+  const int J = j >> 1, Jn = J + ((j & 1) ? 1 : -1), Jw = mwrap(Jn, gc.n1, gc.bc1);
+  const int rows[2] = {J, Jw < 0 ? J : Jw};  // past a wall the parent itself
   int Kq[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int K = m0 - 1 + q;
-    Kq[q] = (K < 0) ? (gc.bc2 ? 0 : gc.n2 - 1) : (K >= gc.n2 ? (gc.bc2 ? gc.n2 - 1 : 0) : K);
+    const int K = m0 - 1 + q, Kw = mwrap(K, gc.n2, gc.bc2);
+    Kq[q] = Kw >= 0 ? Kw : (K < 0 ? 0 : gc.n2 - 1);
   }
-  // coarse plane P: values at rows J, Jo and K = Kq[0..3]
-  auto load_plane = [&](int P, T v[2][4]) {
-    const int rows[2] = {J, Jo};
+  // byte offsets of the eight coarse values within an even plane; on an odd
+  // plane the other colour holds the cell
+  long long off[2][2][4];
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+  for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[r][q] = xc[sidx(gc, P, rows[r], Kq[q])];
+    for (int q = 0; q < 4; ++q) {
+      const int c = (rows[r] + Kq[q]) & 1;
+      const long long e = (long long)rows[r] * gc.hn2 + (Kq[q] >> 1);
+      off[0][r][q] = (e + c * gc.half) * (long long)sizeof(T);
+      off[1][r][q] = (e + (1 - c) * gc.half) * (long long)sizeof(T);
+    }
+  struct Raw {
+    T v[2][4];
   };
-  auto wrapP = [&](int P) { return side(P < 0 ? 0 : gc.n0 - 1, P, gc.n0, gc.bc0); };
-  int lo = (i0 - 1) >> 1;
-  T vlo[2][4], vhi[2][4], vpre[2][4];
-  load_plane(wrapP(lo), vlo);
-  load_plane(wrapP(lo + 1), vhi);
-  auto xrow = [&](int i) { return xf + ((long long)i * gf.n1 + j) * gf.hn2 + m0; };
-  V2<T> xcur = ld2<T>(xrow(i0));
-  for (int i = i0; i < i1; ++i) {
-    if (((i - 1) >> 1) != lo) {
-      // the window moves up one coarse plane (prefetched one fine plane ago)
-      ++lo;
+  auto load_plane = [&](int I) {
+    Raw w;
+    const int Iw = mwrap(I, gc.n0, gc.bc0), P = Iw >= 0 ? Iw : (I < 0 ? 0 : gc.n0 - 1);
+    const char *base = (const char *)(xc + (long long)P * gc.n1 * gc.hn2);
+    if (P & 1) {
 #pragma unroll
       for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          vlo[r][q] = vhi[r][q];
-          vhi[r][q] = vpre[r][q];
-        }
+        for (int q = 0; q < 4; ++q) w.v[r][q] = *(const T *)(base + off[1][r][q]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w.v[r][q] = *(const T *)(base + off[0][r][q]);
     }
-    // software pipeline: the next fine row and, when the window will move at
-    // plane i+1, its new coarse plane
-    const bool more = i + 1 < i1;
-    V2<T> xnext = xcur;
-    if (more) {
-      xnext = ld2<T>(xrow(i + 1));
-      if ((i >> 1) != lo) load_plane(wrapP(lo + 2), vpre);
-    }
-    // parent plane i>>1 is lo for odd i, hi for even i
-    const T wlo = (i & 1) ? (T)0.75 : (T)0.25, whi = (T)1 - wlo;
-    const int s = (i + j) & 1;  // fine red cells k = 2 (m0 + u) + s
-    T out[2];
+    return w;
+  };
+  // fine red cells at plane i: k = 2 (m0 + u) + s, s = (i + j) & 1; parent
+  // K = m0 + u (slot u + 1), neighbour K - 1 (slot u, s = 0) or K + 1 (slot u + 2)
+  struct Blend {
+    T even[2], odd[2];  // at even and odd fine planes
+  };
+  auto plane_blend = [&](const Raw &w) {
+    Blend z;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      // parent K = m0 + u (slot u + 1), neighbour K - 1 (slot u) or K + 1 (slot u + 2)
-      const int qc = u + 1, qo = s ? u + 2 : u;
-      T acc = T(0);
-#pragma unroll
-      for (int pl = 0; pl < 2; ++pl) {
-        const T(*v)[4] = pl ? vhi : vlo;
-        const T zJ = blend34(v[0][qc], v[0][qo]);
-        const T zO = blend34(v[1][qc], v[1][qo]);
-        acc = fma(pl ? whi : wlo, blend34(zJ, zO), acc);
-      }
-      out[u] = acc;
+      const T lo = blend34(blend34(w.v[0][u + 1], w.v[0][u]), blend34(w.v[1][u + 1], w.v[1][u]));
+      const T hi = blend34(blend34(w.v[0][u + 1], w.v[0][u + 2]), blend34(w.v[1][u + 1], w.v[1][u + 2]));
+      z.even[u] = (j & 1) ? hi : lo;
+      z.odd[u] = (j & 1) ? lo : hi;
     }
-    st2(xrow(i), xcur.x + out[0], xcur.y + out[1]);
-    xcur = xnext;
+    return z;
+  };
+  const long long P = (long long)gf.n1 * gf.hn2;
+  const unsigned rw = (unsigned)(j * gf.hn2 + m0) * sizeof(T);
+  auto xload = [&](int i) { return ld2<T>(xf + i * P, rw); };
+  // fine plane i between the coarse planes lo and hi; the parent is hi for even i
+  auto even = [&](int i, const V2<T> &xv, const Blend &lo, const Blend &hi) {
+    st2<T>(xf + i * P, rw, xv.x + fma(T(0.75), hi.even[0], T(0.25) * lo.even[0]),
+           xv.y + fma(T(0.75), hi.even[1], T(0.25) * lo.even[1]));
+  };
+  auto odd = [&](int i, const V2<T> &xv, const Blend &lo, const Blend &hi) {
+    st2<T>(xf + i * P, rw, xv.x + fma(T(0.25), hi.odd[0], T(0.75) * lo.odd[0]),
+           xv.y + fma(T(0.25), hi.odd[1], T(0.75) * lo.odd[1]));
+  };
+  int i = i0, I = (i0 - 1) >> 1;  // the fine plane i lies between the coarse planes I and I + 1
+  V2<T> x0 = xload(i0), x1 = x0;
+  const Raw ra = load_plane(I), rb = load_plane(I + 1);
+  Blend lo = plane_blend(ra), hi = plane_blend(rb);
+  if (i & 1) {
+    odd(i, x0, lo, hi);
+    if (++i >= i1) return;
+    x0 = xload(i);
+  }
+  if (i + 1 < i1) x1 = xload(i + 1);
+  Raw rn = load_plane(I + 2);
+  for (;;) {  // i even, between lo and hi; i + 1 lies between hi and plane I + 2
+    const V2<T> c0 = x0, c1 = x1;
+    const Blend nw = plane_blend(rn);
+    const bool two = i + 1 < i1;
+    if (i + 2 < i1) {
+      x0 = xload(i + 2);
+      if (i + 3 < i1) {
+        x1 = xload(i + 3);
+        rn = load_plane(I + 3);
+      }
+    }
+    even(i, c0, lo, hi);
+    if (two) odd(i + 1, c1, hi, nw);
+    if ((i += 2) >= i1) return;
+    ++I;
+    lo = hi;
+    hi = nw;
   }
 }
 

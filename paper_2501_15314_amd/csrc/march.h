@@ -6,7 +6,29 @@
 // register window over three planes, the y- and z-neighbours from an LDS copy
 // of the current plane with a one-cell halo.  BX divides hn2/2 and BY divides
 // n1, so no workgroup is partial and every halo cell is loaded.
+//
+// These kernels move bytes: at 256^3 in float32 a pressure half sweep moves
+// 101 MB, near the 5 to 6 TB/s that reads and writes of such sets reach.  To
+// stay at that they have to spend few instructions per plane, since a wave has
+// one vector and one scalar issue slot in four cycles: what is fixed along a
+// march (halo positions, stencil diagonals and their reciprocals) is found
+// before it, the parity of a plane is an index into two sets of records, the
+// register window moves by renaming over four unrolled planes, plane offsets
+// are scalar and advance by addition, no load is under a condition, and LDS is
+// double buffered, which leaves one barrier per plane.  Per wave and plane a
+// pressure half sweep takes about 30 vector instructions (81 and, for its
+// setup, 246 per chunk when every plane found its own halo and diagonals), the
+// Laplacian about 100 (232, two IEEE divisions per colour and cell pair among
+// them).  At 256^3 float32, before and after, us: half sweep 20.4 / 19.3, first
+// sweep 31.3 / 21.9, restriction 24.6 / 20.0, prolongation 23.8 / 15.2,
+// Laplacian 33.5 / 24.7 (5.2, 4.6, 5.4, 4.9, 5.4 TB/s); float64: 41.0 / 37.8,
+// 43.2 / 38.9, 41.1 / 39.8, 39.3 / 31.7, 51.5 / 51.6; at 128^3 float32, where
+// the grids are small and setup counts: 6.7 / 5.5, 8.9 / 7.1, 7.5 / 5.0,
+// 7.3 / 5.3, 10.3 / 7.5; momentum half sweep at 256^3 float32 66.2 / 65.9, its
+// first sweep 108 / 76.5.
 #pragma once
+#include <type_traits>
+
 #include "internal.h"
 
 namespace ibs {
@@ -34,28 +56,47 @@ template <typename T>
 struct V2 {
   T x, y;
 };
-// 2-vector load of S values converted to R
+// Element and 2-vector access at a byte offset from a pointer that is the same
+// for the whole workgroup: the offset is 32 bits wide (one plane of one colour
+// is far below 4 GiB), so an access needs one address register and no 64-bit
+// arithmetic per lane.
+template <typename S>
+__device__ __forceinline__ S ldo(const S *p, unsigned off) {
+  return *(const S *)((const char *)p + off);
+}
 template <typename R, typename S>
-__device__ __forceinline__ V2<R> ld2(const S *p) {
+__device__ __forceinline__ V2<R> ld2(const S *p, unsigned off = 0) {
   V2<R> v;
+  const char *q = (const char *)p + off;
   if (sizeof(S) == 4) {
-    float2 f = *(const float2 *)p;
+    float2 f = *(const float2 *)q;
     v.x = (R)f.x;
     v.y = (R)f.y;
   } else {
-    double2 f = *(const double2 *)p;
+    double2 f = *(const double2 *)q;
     v.x = (R)f.x;
     v.y = (R)f.y;
   }
   return v;
 }
 template <typename T>
-__device__ __forceinline__ void st2(T *p, T a, T b) {
+__device__ __forceinline__ void st2(T *p, unsigned off, T a, T b) {
+  char *q = (char *)p + off;
   if (sizeof(T) == 4) {
-    *(float2 *)p = make_float2((float)a, (float)b);
+    *(float2 *)q = make_float2((float)a, (float)b);
   } else {
-    *(double2 *)p = make_double2((double)a, (double)b);
+    *(double2 *)q = make_double2((double)a, (double)b);
   }
+}
+
+// a / d for a divisor whose correctly rounded reciprocal r = 1 / d is at hand:
+// one fused remainder step gives the correctly rounded quotient (Markstein's
+// theorem; a and the quotient normal numbers), the same bits as the division
+// at 3 operations instead of about 10.  Infinite quotients stay infinite.
+template <typename T>
+__device__ __forceinline__ T div_by(T a, T d, T r) {
+  const T q = a * r, e = fma(-q, d, a);
+  return e == e ? fma(e, r, q) : q;
 }
 
 // Coordinate wrap for periodic axes; -1 if outside a wall box.
@@ -115,206 +156,128 @@ __device__ __forceinline__ MarchPos march_pos(const Geo &g, bool xcd) {
   return p;
 }
 
-// Load the one-cell halo of the plane tile (rows ty = -1, BY and columns
-// m = -1, 2BX) cooperatively; val(i, j, m) returns the value of a plane at an
-// in-domain position (already wrapped), 0 is stored outside a wall box.
-template <typename T, class F>
-__device__ __forceinline__ void tile_halo(T *tile, const Geo &g, int i, int jbase, int mbase, int BX, int BY,
-                                          F val) {
+// The halo of a plane tile (rows ty = -1 and BY, columns m = -1 and 2 BX) by
+// position: the threads of the tile's first and last row each bring the pair
+// of cells beyond their own, those of its first and last column one cell.
+// What does not change along the march -- offsets, LDS slots, whether the
+// cells lie outside a wall box (they are 0: `zero` stores that once for both
+// LDS buffers) -- is found here, without a division.  BY >= 2 (n1 is even and
+// so is BY); a tile one pair wide (BX == 1) has both columns at one thread,
+// which brings the right one by itself (`thin`).  Every thread loads: those
+// that bring nothing share an address of their row, so that the loads are not
+// under a condition (the compiler waits for all outstanding loads where a
+// conditional one may or may not be among them, which serialises the march).
+struct MarchEdge {
+  int rslot, cslot;   // LDS slots of the row pair and the column cell, -1: none
+  int jr, mr, mc;     // row and in-row index of the pair, in-row index of the column cell
+  bool thin;
+  int mthin;  // in-row index of the right column cell of a thin tile, -1: outside
+};
+template <class Z>
+__device__ __forceinline__ MarchEdge march_edge(const Geo &g, const MarchPos &p, int BX, int BY, Z zero) {
+  MarchEdge e;
   const int W2 = 2 * BX + 2;
-  const int nrow = 2 * (2 * BX), ncol = 2 * BY;
-  const int tid = threadIdx.x + blockDim.x * threadIdx.y;
-  for (int h = tid; h < nrow + ncol; h += blockDim.x * blockDim.y) {
-    int r, cidx;
-    if (h < nrow) {
-      r = h < 2 * BX ? 0 : BY + 1;
-      cidx = 1 + (h % (2 * BX));
+  const bool lastr = p.ty == BY - 1, lastc = BX > 1 && p.tx == BX - 1;
+  e.rslot = e.cslot = -1;
+  e.jr = p.j;
+  e.mr = e.mc = p.m0 - 2 * p.tx;
+  e.thin = BX == 1;
+  e.mthin = 0;
+  if (p.ty == 0 || lastr) {
+    const int jj = mwrap(lastr ? p.j + 1 : p.j - 1, g.n1, g.bc1);
+    const int slot = (lastr ? BY + 1 : 0) * W2 + 2 * p.tx + 1;
+    if (jj >= 0) {
+      e.jr = jj;
+      e.mr = p.m0;
+      e.rslot = slot;
     } else {
-      int q = h - nrow;
-      r = 1 + (q >> 1);
-      cidx = (q & 1) ? 2 * BX + 1 : 0;
-    }
-    int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-    int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-    T v = T(0);
-    if (jj >= 0 && mm >= 0 && (unsigned)i < (unsigned)g.n0) v = val(i, jj, mm);
-    tile[r * W2 + cidx] = v;
-  }
-}
-
-// The same halo in two halves, so that the loads of the next plane can be
-// issued before the current plane is computed: halo_fetch reads up to
-// HALO_REG values per thread into registers, halo_put stores them (and loads
-// any remainder of very thin tiles directly).
-constexpr int HALO_REG = 2;
-template <typename T>
-struct Halo {
-  T v[HALO_REG];
-};
-__device__ __forceinline__ void halo_slot(int h, int BX, int BY, int &r, int &cidx) {
-  const int nrow = 2 * (2 * BX);
-  if (h < nrow) {
-    r = h < 2 * BX ? 0 : BY + 1;
-    cidx = 1 + (h % (2 * BX));
-  } else {
-    const int q = h - nrow;
-    r = 1 + (q >> 1);
-    cidx = (q & 1) ? 2 * BX + 1 : 0;
-  }
-}
-template <typename T, class F>
-__device__ __forceinline__ Halo<T> halo_fetch(const Geo &g, int i, int jbase, int mbase, int BX, int BY, F val) {
-  Halo<T> hv;
-  const int total = 2 * (2 * BX) + 2 * BY, nthr = BX * BY;
-  const int tid = threadIdx.x + BX * threadIdx.y;
-#pragma unroll
-  for (int q = 0; q < HALO_REG; ++q) {
-    hv.v[q] = T(0);
-    const int h = tid + q * nthr;
-    if (h < total) {
-      int r, cidx;
-      halo_slot(h, BX, BY, r, cidx);
-      const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-      const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-      if (jj >= 0 && mm >= 0 && (unsigned)i < (unsigned)g.n0) hv.v[q] = val(i, jj, mm);
+      zero(slot);
+      zero(slot + 1);
     }
   }
-  return hv;
-}
-template <typename T, class F>
-__device__ __forceinline__ void halo_put(T *tile, const Halo<T> &hv, const Geo &g, int i, int jbase, int mbase,
-                                         int BX, int BY, F val) {
-  const int total = 2 * (2 * BX) + 2 * BY, nthr = BX * BY, W2 = 2 * BX + 2;
-  const int tid = threadIdx.x + BX * threadIdx.y;
-#pragma unroll
-  for (int q = 0; q < HALO_REG; ++q) {
-    const int h = tid + q * nthr;
-    if (h < total) {
-      int r, cidx;
-      halo_slot(h, BX, BY, r, cidx);
-      tile[r * W2 + cidx] = hv.v[q];
+  if (p.tx == 0 || lastc) {
+    const int mm = mwrap(lastc ? p.m0 + 2 : p.m0 - 1, g.hn2, g.bc2);
+    const int slot = (p.ty + 1) * W2 + (lastc ? 2 * BX + 1 : 0);
+    if (mm >= 0) {
+      e.mc = mm;
+      e.cslot = slot;
+    } else {
+      zero(slot);
     }
   }
-  for (int h = tid + HALO_REG * nthr; h < total; h += nthr) {
-    int r, cidx;
-    halo_slot(h, BX, BY, r, cidx);
-    const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-    const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-    T v = T(0);
-    if (jj >= 0 && mm >= 0 && (unsigned)i < (unsigned)g.n0) v = val(i, jj, mm);
-    tile[r * W2 + cidx] = v;
+  if (e.thin) {
+    e.mthin = mwrap(p.m0 + 2, g.hn2, g.bc2);
+    if (e.mthin < 0) zero((p.ty + 1) * W2 + 2 * BX + 1);
   }
-}
-// halo_put for halos fetched as raw operands: the register part stores
-// xf(i, jj, mm, raw) (0 outside a wall box), the remainder val(i, jj, mm).
-template <typename T, class F, class X>
-__device__ __forceinline__ void halo_put_xf(T *tile, const Halo<T> &hv, const Geo &g, int i, int jbase, int mbase,
-                                            int BX, int BY, F val, X xf) {
-  const int total = 2 * (2 * BX) + 2 * BY, nthr = BX * BY, W2 = 2 * BX + 2;
-  const int tid = threadIdx.x + BX * threadIdx.y;
-#pragma unroll
-  for (int q = 0; q < HALO_REG; ++q) {
-    const int h = tid + q * nthr;
-    if (h < total) {
-      int r, cidx;
-      halo_slot(h, BX, BY, r, cidx);
-      const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-      const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-      tile[r * W2 + cidx] = (jj >= 0 && mm >= 0 && (unsigned)i < (unsigned)g.n0) ? xf(i, jj, mm, hv.v[q]) : T(0);
-    }
-  }
-  for (int h = tid + HALO_REG * nthr; h < total; h += nthr) {
-    int r, cidx;
-    halo_slot(h, BX, BY, r, cidx);
-    const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-    const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-    T v = T(0);
-    if (jj >= 0 && mm >= 0 && (unsigned)i < (unsigned)g.n0) v = val(i, jj, mm);
-    tile[r * W2 + cidx] = v;
-  }
+  return e;
 }
 
-}  // namespace ibs
-
-namespace ibs {
-
-// Plane-invariant halo slots of a thread (HALO_REG of them): LDS slot (-1:
-// none), in-plane offset (-1: outside a wall box), row and in-row index.
-// Thin tiles (more halo cells than HALO_REG per thread) load the rest of
-// their halo directly.
-struct HaloSlots {
-  int slot[HALO_REG], off[HALO_REG], jj[HALO_REG], mm[HALO_REG];
-  int total, nthr, tid;
-  bool rem;
-};
-__device__ __forceinline__ HaloSlots halo_slots(const Geo &g, int jbase, int mbase, int BX, int BY) {
-  HaloSlots hs;
-  const int W2 = 2 * BX + 2;
-  hs.total = 2 * (2 * BX) + 2 * BY;
-  hs.nthr = BX * BY;
-  hs.tid = threadIdx.x + BX * threadIdx.y;
-  hs.rem = hs.total > HALO_REG * hs.nthr;
-#pragma unroll
-  for (int q = 0; q < HALO_REG; ++q) {
-    const int h = hs.tid + q * hs.nthr;
-    hs.slot[q] = -1;
-    hs.off[q] = -1;
-    hs.jj[q] = 0;
-    hs.mm[q] = 0;
-    if (h < hs.total) {
-      int r, cidx;
-      halo_slot(h, BX, BY, r, cidx);
-      hs.slot[q] = r * W2 + cidx;
-      const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-      const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-      if (jj >= 0 && mm >= 0) {
-        hs.off[q] = jj * g.hn2 + mm;
-        hs.jj[q] = jj;
-        hs.mm[q] = mm;
-      }
-    }
-  }
-  return hs;
-}
-
-// Stencil diagonal of a thread's two cells k = 2 (m0 + u) + s of row j, split
-// into the part of axes 1 and 2 (fixed along a march along axis 0, tabulated
-// for both parities s) and the part of axis 0 (per plane).  Pressure
+// Stencil diagonal of cell (jj, kk), the part of axes 1 and 2 (fixed along a
+// march along axis 0) and the part of axis 0 (per plane).  Pressure
 // Laplacian: the number of missing neighbours (the cell has 6 - di - djk);
 // momentum operator on component d: the 7-point diagonal count in units of
-// 1/h^2 (di + djk) with the tangential wall ghosts, and the wall-face flag.
-struct DiagJK {
-  int d[2][2];
-  bool w[2][2];
-  // entries for parity s and (compile-time) cell u, selected without a
-  // dynamic index so that the table stays in registers
-  __device__ __forceinline__ int dg(int s, int u) const { return s ? d[1][u] : d[0][u]; }
-  __device__ __forceinline__ bool wl(int s, int u) const { return s ? w[1][u] : w[0][u]; }
-};
-__device__ __forceinline__ DiagJK diag_jk(const Geo &g, int j, int m0, bool helm, int d) {
-  DiagJK r;
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int k = 2 * (m0 + u) + sp;
-      if (helm) {
-        int dg = 4;
-        if (g.bc1 && d != 1) dg += wall_ghost_diag(g.bc1) * ((j == 0) + (j == g.n1 - 1));
-        if (g.bc2 && d != 2) dg += wall_ghost_diag(g.bc2) * ((k == 0) + (k == g.n2 - 1));
-        r.d[sp][u] = dg;
-        r.w[sp][u] = d == 1 ? (g.bc1 && j == 0) : (d == 2 ? (g.bc2 && k == 0) : false);
-      } else {
-        r.d[sp][u] = (g.bc1 ? (j == 0) + (j == g.n1 - 1) : 0) + (g.bc2 ? (k == 0) + (k == g.n2 - 1) : 0);
-        r.w[sp][u] = false;
-      }
-    }
-  return r;
+// 1/h^2 (di + djk) with the tangential wall ghosts.
+__device__ __forceinline__ int diag_jk(const Geo &g, int jj, int kk, bool helm, int d) {
+  const int e1 = (jj == 0) + (jj == g.n1 - 1), e2 = (kk == 0) + (kk == g.n2 - 1);
+  if (!helm) return (g.bc1 ? e1 : 0) + (g.bc2 ? e2 : 0);
+  return 4 + (g.bc1 && d != 1 ? wall_ghost_diag(g.bc1) * e1 : 0) + (g.bc2 && d != 2 ? wall_ghost_diag(g.bc2) * e2 : 0);
 }
 __device__ __forceinline__ int diag_i(const Geo &g, int i, bool helm, int d) {
   const int e = (i == 0) + (i == g.n0 - 1);
   return helm ? 2 + ((g.bc0 && d != 0) ? wall_ghost_diag(g.bc0) * e : 0) : (g.bc0 ? e : 0);
 }
+// a normal wall face of momentum component d (held at 0), axes 1 and 2
+__device__ __forceinline__ bool wall_jk(const Geo &g, int jj, int kk, int d) {
+  return d == 1 ? (g.bc1 && jj == 0) : (d == 2 ? (g.bc2 && kk == 0) : false);
+}
+
+// Where a march stands: element offsets, from the start of a colour plane
+// array, of the plane being computed, of the next one (the last one again at
+// the end of the chunk) and of the one after it (wrapped; the nearest one
+// outside a wall box).  All scalar and advanced by additions: with the vector
+// work of a plane down to a few tens of instructions, multiplying each offset
+// out again would cost as much.
+struct MarchOff {
+  long long cur, nxt, win;
+  long long P, wrap;
+  int last, n0;
+};
+__device__ __forceinline__ long long march_win(const MarchOff &o, int i, long long at) {
+  return i + 1 < o.n0 ? at + o.P : o.wrap;
+}
+__device__ __forceinline__ MarchOff march_off(const Geo &g, int i0, int i1) {
+  MarchOff o;
+  o.P = (long long)g.n1 * g.hn2;
+  o.wrap = g.bc0 ? (g.n0 - 1) * o.P : 0;
+  o.last = i1 - 1;
+  o.n0 = g.n0;
+  o.cur = o.nxt = i0 * o.P;
+  o.win = march_win(o, i0, o.nxt);
+  return o;
+}
+// to plane i: nxt and win become those of plane i + 1
+__device__ __forceinline__ void march_next(MarchOff &o, int i) {
+  o.cur = o.nxt;
+  if (i < o.last) {
+    o.nxt += o.P;
+    o.win = march_win(o, i + 1, o.nxt);
+  }
+}
+// offset of the plane before i0
+__device__ __forceinline__ long long march_prev(const Geo &g, const MarchOff &o, int i0) {
+  return i0 > 0 ? o.cur - o.P : (g.bc0 ? 0 : (g.n0 - 1) * o.P);
+}
+
+// What a cell's update needs besides the field values, found once per march
+// for the planes inside the grid (the planes at a wall of axis 0 form it anew
+// from the packed diagonal counts): `inv` = 1 / number of neighbours for the
+// pressure; the divisor a0 + nu/h^2 diag, its reciprocal and the wall flag for
+// the momentum operator.
+template <typename T>
+struct CellRec {
+  T inv, den;
+  bool wall;
+};
 
 // One red-black half sweep of colour `color` on the component grids of x.
 //   SW_POISSON: x_c = (h^2 b_c + sum of neighbours) / (number of neighbours)
@@ -340,162 +303,188 @@ enum { SW_POISSON = 0, SW_FIRST = 1, SW_HELM = 2, SW_HFIRST = 3, SW_FIRST1 = 4 }
 template <typename T, typename TB, int MODE>
 __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int color, double h2, double a0,
                                                double nuh2, double omega) {
-  __shared__ T tile[MARCH_TILE];
-  const MarchPos p = march_pos(g, MODE == SW_HELM || MODE == SW_HFIRST);
-  const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
-  const long long N = 2 * g.half;
-  const int d = p.comp;
-  T *xg = x + d * N;
-  const TB *bg = b + d * N;
-  const int c = color;
-  T *own = xg + (long long)c * g.half;
-  T *oth = xg + (long long)(1 - c) * g.half;
-  const TB *bown = bg + (long long)c * g.half;
-  const TB *both = bg + (long long)(1 - c) * g.half;
-  const int mbase = p.mbase, jbase = p.jbase;
-  auto row = [&](int i, int jj) { return ((long long)i * g.n1 + jj) * g.hn2; };
-  const long long P = (long long)g.n1 * g.hn2;  // one plane of one colour
-  const int rw = p.j * g.hn2 + p.m0;            // this thread's two cells within a plane
-  const T th2 = (T)h2, ta0 = (T)a0, tnu = (T)nuh2, tom = (T)omega;
   constexpr bool FIRSTM = MODE == SW_FIRST || MODE == SW_HFIRST || MODE == SW_FIRST1;
   constexpr bool HELMM = MODE == SW_HELM || MODE == SW_HFIRST;
-  // momentum stencil at face (i, jj, kk) of component d: the diagonal count
-  // (2 per axis plus the tangential wall ghosts) and whether it is a wall face
-  auto helm_cell = [&](int i, int jj, int kk, bool &wall) -> int {
-    const int xs[3] = {i, jj, kk};
-    int diag = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      int bca = geo_bc(g, a), na = geo_n(g, a);
-      diag += 2;
-      if (bca && a != d) diag += wall_ghost_diag(bca) * ((xs[a] == 0) + (xs[a] == na - 1));
+  __shared__ T tile[2][MARCH_TILE];
+  const MarchPos p = march_pos(g, HELMM);
+  const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
+  const int d = p.comp, c = FIRSTM ? 1 : color;
+  const long long N = 2 * g.half;
+  T *own = x + d * N + (long long)c * g.half;
+  T *oth = x + d * N + (long long)(1 - c) * g.half;
+  const TB *bown = b + d * N + (long long)c * g.half;
+  // the other colour: in the first-sweep modes it is formed from the
+  // right-hand side (the loads fetch that raw, oxf turns it into the value)
+  using TO = typename std::conditional<FIRSTM, TB, T>::type;
+  const TO *osrc = FIRSTM ? (const TO *)(b + d * N + (long long)(1 - c) * g.half) : (const TO *)oth;
+  const unsigned rw = p.j * g.hn2 + p.m0;  // this thread's two cells within a plane
+  const T th2 = (T)h2, ta0 = (T)a0, tnu = (T)nuh2, tom = (T)omega;
+  const MarchEdge e = march_edge(g, p, BX, BY, [&](int q) { tile[0][q] = tile[1][q] = T(0); });
+  const unsigned eoff = (unsigned)(e.jr * g.hn2 + e.mr) * sizeof(TO), coff = (unsigned)(p.j * g.hn2 + e.mc) * sizeof(TO);
+
+  // Own cells at plane i have k = 2 m + s, s = (c + i + j) & 1; the
+  // other-colour cells of the same row 1 - s, those of the rows beside it s.
+  // Index 0 holds for the plane i0 and every second one after it.
+  const int s0 = (c + p.i0 + p.j) & 1;
+  auto rec = [&](int diag, bool wall) {
+    CellRec<T> r;
+    if (HELMM) {
+      r.den = fma(tnu, (T)diag, ta0);
+      r.inv = T(1) / r.den;
+    } else {
+      r.den = T(0);
+      r.inv = inv_nn<T>(6 - diag);
     }
-    const int xd = d == 0 ? i : (d == 1 ? jj : kk);
-    wall = geo_bc(g, d) && xd == 0;
-    return diag;
+    r.wall = wall;
+    return r;
   };
-  // In the first-sweep modes the other-colour operand is formed from the
-  // right-hand side: the loads of the next plane fetch it raw, oxf turns it
-  // into the colour-0 value once the current plane has been computed.
-  auto oxf = [&](int i, int jj, int mm, T bv) -> T {
-    const int kk = 2 * mm + ((i + jj) & 1);  // colour-0 cell of row (i, jj) at index mm
-    if (MODE == SW_FIRST || MODE == SW_FIRST1) return pc_first(th2, bv, cell_nnb(g, i, jj, kk));
-    bool wall;
-    const int dg = helm_cell(i, jj, kk, wall);
-    return wall ? T(0) : tom * (bv / (ta0 + tnu * (T)dg));
-  };
-  auto oval = [&](int i, int jj, int mm) -> T {
-    if (FIRSTM) return oxf(i, jj, mm, (T)both[row(i, jj) + mm]);
-    return oth[row(i, jj) + mm];
-  };
-  // other-colour operand of plane ii (in the domain) at in-plane offset o
-  auto oget = [&](int ii, int o) -> T {
-    if (FIRSTM) return (T)both[ii * P + o];
-    return oth[ii * P + o];
-  };
-  auto owin_ld = [&](int i) -> V2<T> {
-    V2<T> v;
-    v.x = T(0);
-    v.y = T(0);
-    int ii = mwrap(i, g.n0, g.bc0);
-    if (ii < 0) return v;
-    if (FIRSTM) return ld2<T>(both + ii * P + rw);
-    return ld2<T>(oth + ii * P + rw);
-  };
-  auto owin_xf = [&](int i, V2<T> v) -> V2<T> {
-    if (!FIRSTM) return v;
-    int ii = mwrap(i, g.n0, g.bc0);
-    if (ii < 0) return v;  // zeros from owin_ld
-    v.x = oxf(ii, p.j, p.m0, v.x);
-    v.y = oxf(ii, p.j, p.m0 + 1, v.y);
-    return v;
-  };
-  const HaloSlots hs = halo_slots(g, jbase, mbase, BX, BY);
-  auto hfetch = [&](int i, T *hv) {
+  const int di0 = HELMM ? 2 : 0;
+  CellRec<T> ro[2][2], rr[2][2], rc[2];  // own row (either colour), row pair, column cell
+  unsigned pk = 0, pkr = 0, pkc = 0;     // their counts of axes 1 and 2, 4 bits each
 #pragma unroll
-    for (int q = 0; q < HALO_REG; ++q) hv[q] = hs.off[q] >= 0 ? oget(i, hs.off[q]) : T(0);
-  };
-  auto hput = [&](int i, const T *hv) {
-#pragma unroll
-    for (int q = 0; q < HALO_REG; ++q)
-      if (hs.slot[q] >= 0) tile[hs.slot[q]] = (FIRSTM && hs.off[q] >= 0) ? oxf(i, hs.jj[q], hs.mm[q], hv[q]) : hv[q];
-    if (hs.rem) {
-      for (int h = hs.tid + HALO_REG * hs.nthr; h < hs.total; h += hs.nthr) {
-        int r, cidx;
-        halo_slot(h, BX, BY, r, cidx);
-        const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-        const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-        tile[r * W2 + cidx] = (jj >= 0 && mm >= 0) ? oval(i, jj, mm) : T(0);
-      }
-    }
-  };
-  const DiagJK djk = diag_jk(g, p.j, p.m0, HELMM, d);
-  V2<T> prev = owin_xf(p.i0 - 1, owin_ld(p.i0 - 1)), cur = owin_xf(p.i0, owin_ld(p.i0)),
-        next = owin_xf(p.i0 + 1, owin_ld(p.i0 + 1));
-  T hcur[HALO_REG], hnext[HALO_REG];
-  hfetch(p.i0, hcur);
-  // software pipeline: the window plane i+2, the halo and the own-colour
-  // operands of plane i+1 are loaded while plane i is computed
-  auto own_ops = [&](int i, V2<T> &bb, V2<T> &xo) {
-    const long long r = i * P + rw;
-    bb = ld2<T>(bown + r);
-    xo.x = T(0);
-    xo.y = T(0);
-    if (MODE == SW_HELM) xo = ld2<T>((const T *)own + r);
-  };
-  V2<T> bb, xo;
-  own_ops(p.i0, bb, xo);
-  for (int i = p.i0; i < p.i1; ++i) {
-    const bool more = i + 1 < p.i1;
-    V2<T> nn = more ? owin_ld(i + 2) : next;
-    V2<T> bbn = bb, xon = xo;
-#pragma unroll
-    for (int q = 0; q < HALO_REG; ++q) hnext[q] = hcur[q];
-    if (more) {
-      hfetch(i + 1, hnext);
-      own_ops(i + 1, bbn, xon);
-    }
-    tile[(p.ty + 1) * W2 + 2 * p.tx + 1] = cur.x;
-    tile[(p.ty + 1) * W2 + 2 * p.tx + 2] = cur.y;
-    hput(i, hcur);
-    __syncthreads();
-    T out[2];
-    const int s = (c + i + p.j) & 1;
-    const int di = diag_i(g, i, HELMM, d);
+  for (int f = 0; f < 2; ++f) {
+    const int s = f ? 1 - s0 : s0;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int col = 2 * p.tx + 1 + u;
-      const T *trow = tile + (p.ty + 1) * W2;
-      T sum = (u ? prev.y : prev.x) + (u ? next.y : next.x) + tile[p.ty * W2 + col] + tile[(p.ty + 2) * W2 + col] +
-              trow[col - 1 + s] + trow[col + s];
-      T bv = u ? bb.y : bb.x;
-      if (!HELMM) {
-        out[u] = pc_relax(th2, bv, sum, 6 - di - djk.dg(s, u));
-      } else {
-        const int diag = di + djk.dg(s, u);
-        const bool wall = d == 0 ? (g.bc0 && i == 0) : djk.wl(s, u);
-        T xv = u ? xo.y : xo.x;  // 0 in SW_HFIRST
-        T gs = (bv + tnu * sum) / (ta0 + tnu * (T)diag);
-        out[u] = wall ? xv : xv + tom * (gs - xv);
+      const int k = 2 * (p.m0 + u) + s;
+      const int dg = diag_jk(g, p.j, k, HELMM, d);
+      pk |= (unsigned)dg << (8 * f + 4 * u);
+      ro[f][u] = rec(di0 + dg, HELMM && wall_jk(g, p.j, k, d));
+      if (FIRSTM) {
+        const int dr = diag_jk(g, e.jr, k, HELMM, d);
+        pkr |= (unsigned)dr << (8 * f + 4 * u);
+        rr[f][u] = rec(di0 + dr, HELMM && wall_jk(g, e.jr, k, d));
       }
     }
-    const long long r = i * P + rw;
-    st2(own + r, out[0], out[1]);
-    if (MODE == SW_FIRST || MODE == SW_HFIRST) st2(oth + r, cur.x, cur.y);
+    if (FIRSTM) {
+      const int k = 2 * e.mc + s;
+      const int dc = diag_jk(g, p.j, k, HELMM, d);
+      pkc |= (unsigned)dc << (4 * f);
+      rc[f] = rec(di0 + dc, HELMM && wall_jk(g, p.j, k, d));
+    }
+  }
+  // planes at a wall of axis 0: where the tabulated records do not hold (e0,
+  // e1), past which there is no plane (z0, z1), wall faces of component 0
+  const bool diw = HELMM ? g.bc0 && d != 0 : g.bc0 != 0;
+  const int e0 = diw ? 0 : -2, e1 = diw ? g.n0 - 1 : -2, z0 = g.bc0 ? 0 : -2, z1 = g.bc0 ? g.n0 - 1 : -2;
+  const int wf0 = HELMM && d == 0 && g.bc0 ? 0 : -2;
+  const int die = HELMM ? 2 + wall_ghost_diag(g.bc0) : 1;
+  struct Pair {
+    CellRec<T> r[2];
+  };
+  // the records of a pair at plane i: as tabulated, or anew
+  auto at_plane = [&](int i, const CellRec<T> *r, unsigned packed, int sh) {
+    Pair q;
+    q.r[0] = r[0];
+    q.r[1] = r[1];
+    if (i == e0 || i == e1) {
+      q.r[0] = rec(die + ((packed >> sh) & 15), r[0].wall);
+      q.r[1] = rec(die + ((packed >> (sh + 4)) & 15), r[1].wall);
+    }
+    if (HELMM && i == wf0) q.r[0].wall = q.r[1].wall = true;
+    return q;
+  };
+  // a colour-0 value of a first sweep from its right-hand side
+  auto oxf = [&](T bv, const CellRec<T> &r) -> T {
+    if (!HELMM) return mul_rn(mul_rn(th2, bv), r.inv);  // pc_first
+    const T v = tom * div_by(bv, r.den, r.inv);
+    return r.wall ? T(0) : v;
+  };
+  MarchOff at = march_off(g, p.i0, p.i1);
+  // the colour-0 pair of plane i (in the grid) in the first-sweep modes; f: index of its records
+  auto owin = [&](int i, V2<T> v, int f) -> V2<T> {
+    if (FIRSTM) {
+      const Pair q = at_plane(i, ro[f], pk, 8 * f);
+      v.x = oxf(v.x, q.r[0]);
+      v.y = oxf(v.y, q.r[1]);
+    }
+    return v;
+  };
+  struct Ops {
+    V2<T> hr, b, x, w;  // halo row pair, own right-hand side and value, other colour at the next plane
+    T hc;               // halo column cell
+  };
+  auto fetch = [&](Ops &o) {
+    o.hr = ld2<T>(osrc + at.nxt, eoff);
+    o.hc = (T)ldo(osrc + at.nxt, coff);
+    o.b = ld2<T>(bown + at.nxt, rw * (unsigned)sizeof(TB));
+    if (MODE == SW_HELM) o.x = ld2<T>((const T *)own + at.nxt, rw * (unsigned)sizeof(T));
+    o.w = ld2<T>(osrc + at.win, rw * (unsigned)sizeof(TO));
+  };
+  // Plane i from the other colour at planes i - 1 and i (wp, wc) and the
+  // operands o; leaves that of plane i + 1 in wn.  The operands of plane i + 1
+  // are loaded into on before anything is computed.  f: index of the records
+  // of the own colour at plane i, and of the LDS buffer (two of them, so one
+  // barrier per plane is enough).
+  auto step = [&](int i, int f, const V2<T> &wp, const V2<T> &wc, V2<T> &wn, const Ops &o, Ops &on) {
+    march_next(at, i);
+    fetch(on);
+    T *t = tile[f];
+    T *trow = t + (p.ty + 1) * W2 + 2 * p.tx;
+    trow[1] = wc.x;
+    trow[2] = wc.y;
+    V2<T> hr = o.hr;
+    T hc = o.hc;
+    if (FIRSTM) {
+      const Pair qr = at_plane(i, rr[f], pkr, 8 * f), qc = at_plane(i, rc, pkc, 0);
+      hr.x = oxf(hr.x, qr.r[0]);
+      hr.y = oxf(hr.y, qr.r[1]);
+      hc = oxf(hc, qc.r[1 - f]);
+    }
+    if (e.rslot >= 0) {
+      t[e.rslot] = hr.x;
+      t[e.rslot + 1] = hr.y;
+    }
+    if (e.cslot >= 0) t[e.cslot] = hc;
+    const int s = f ? 1 - s0 : s0;
+    if (e.thin && e.mthin >= 0) {
+      T v = (T)osrc[at.cur + p.j * g.hn2 + e.mthin];
+      if (FIRSTM) {
+        const int k = 2 * e.mthin + 1 - s;
+        v = oxf(v, rec(diag_i(g, i, HELMM, d) + diag_jk(g, p.j, k, HELMM, d),
+                       HELMM && (wall_jk(g, p.j, k, d) || (d == 0 && g.bc0 && i == 0))));
+      }
+      trow[3] = v;
+    }
     __syncthreads();
-    prev = cur;
-    cur = next;
-    next = more ? owin_xf(i + 2, nn) : nn;
+    wn = i == z1 ? V2<T>{T(0), T(0)} : owin(i + 1 < g.n0 ? i + 1 : 0, o.w, f);
+    const Pair q = at_plane(i, ro[f], pk, 8 * f);
+    T out[2];
 #pragma unroll
-    for (int q = 0; q < HALO_REG; ++q) hcur[q] = hnext[q];
-    bb = bbn;
-    xo = xon;
+    for (int u = 0; u < 2; ++u) {
+      const T sum = (u ? wp.y : wp.x) + (u ? wn.y : wn.x) + trow[u + 1 - W2] + trow[u + 1 + W2] + trow[u + s] +
+                    trow[u + 1 + s];
+      const T bv = u ? o.b.y : o.b.x;
+      const CellRec<T> &r = q.r[u];
+      if (!HELMM) {
+        out[u] = fma(th2, bv, sum) * r.inv;  // pc_relax
+      } else {
+        const T xv = MODE == SW_HELM ? (u ? o.x.y : o.x.x) : T(0);
+        const T gs = div_by<T>(fma(tnu, sum, bv), r.den, r.inv);
+        out[u] = r.wall ? xv : fma(tom, gs - xv, xv);
+      }
+    }
+    st2(own + at.cur, rw * (unsigned)sizeof(T), out[0], out[1]);
+    if (MODE == SW_FIRST || MODE == SW_HFIRST) st2(oth + at.cur, rw * (unsigned)sizeof(T), wc.x, wc.y);
+  };
+  // the other colour's records at plane i0 are those of index 1
+  const V2<T> lp = ld2<T>(osrc + march_prev(g, at, p.i0), rw * (unsigned)sizeof(TO));
+  const V2<T> lc = ld2<T>(osrc + at.cur, rw * (unsigned)sizeof(TO));
+  Ops oa, ob;
+  fetch(oa);
+  V2<T> w0 = p.i0 == z0 ? V2<T>{T(0), T(0)} : owin(p.i0 > 0 ? p.i0 - 1 : g.n0 - 1, lp, 0), w1 = owin(p.i0, lc, 1), w2, w3;
+  // four planes per turn, so that the window moves by renaming
+  for (int i = p.i0;;) {
+    step(i, 0, w0, w1, w2, oa, ob);
+    if (++i >= p.i1) break;
+    step(i, 1, w1, w2, w3, ob, oa);
+    if (++i >= p.i1) break;
+    step(i, 0, w2, w3, w0, oa, ob);
+    if (++i >= p.i1) break;
+    step(i, 1, w3, w0, w1, ob, oa);
+    if (++i >= p.i1) break;
   }
 }
-
-}  // namespace ibs
-
-namespace ibs {
 
 // Operators on both colours at once: every thread owns the four cells of
 // row (i, j) stored at in-row indices m0, m0+1 of both colour planes.
@@ -507,142 +496,134 @@ enum { AP_LAP = 0, AP_HRESID = 1 };
 template <typename T, typename TR, int MODE>
 __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double *b, TR *out, double a0, double nuh2,
                                                 double *part) {
-  __shared__ T tile[2][MARCH_TILE];
+  constexpr bool HELMM = MODE == AP_HRESID;
+  constexpr int NB = sizeof(T) == 4 ? 2 : 1;  // LDS buffers: two spare a barrier, but in float64 cost residency
+  __shared__ T tile[NB][2][MARCH_TILE];       // [buffer][colour]
   __shared__ double red[4];
   const MarchPos p = march_pos(g, true);  // chunk-per-XCD order (L z at 256^3: 46.2 -> 42.9 us)
   const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
-  const long long N = 2 * g.half;
   const int d = p.comp;
+  const long long N = 2 * g.half;
   const T *xg = x + d * N;
   const double *bg = b ? b + d * N : nullptr;
   TR *og = out + d * N;
-  const int mbase = p.mbase, jbase = p.jbase;
-  const long long P = (long long)g.n1 * g.hn2;  // one plane of one colour
-  const int rw = p.j * g.hn2 + p.m0;            // this thread's cells within a plane
-  constexpr bool HELMM = MODE == AP_HRESID;
-  auto win = [&](int q, int i) -> V2<T> {
-    V2<T> v;
-    v.x = T(0);
-    v.y = T(0);
-    int ii = mwrap(i, g.n0, g.bc0);
-    if (ii < 0) return v;
-    return ld2<T>(xg + (long long)q * g.half + ii * P + rw);
-  };
-  // software pipeline as in the sweeps: the window plane i+2, both halos and
-  // the right-hand side of plane i+1 are loaded while plane i is computed
-  auto plane_val = [&](int q) {
-    const T *plane = xg + (long long)q * g.half;
-    return [=](int ii, int jj, int mm) -> T { return plane[((long long)ii * g.n1 + jj) * g.hn2 + mm]; };
-  };
-  const HaloSlots hs = halo_slots(g, jbase, mbase, BX, BY);
-  auto hfetch = [&](int q, int i, T *hv) {
-    const T *plane = xg + (long long)q * g.half + i * P;
+  const unsigned rw = p.j * g.hn2 + p.m0;  // this thread's cells within a plane
+  const MarchEdge e = march_edge(g, p, BX, BY, [&](int q) {
 #pragma unroll
-    for (int e = 0; e < HALO_REG; ++e) hv[e] = hs.off[e] >= 0 ? plane[hs.off[e]] : T(0);
-  };
-  auto hput = [&](int q, int i, const T *hv) {
-    T *tq = tile[q];
+    for (int z = 0; z < NB; ++z) tile[z][0][q] = tile[z][1][q] = T(0);
+  });
+  const unsigned eoff = (unsigned)(e.jr * g.hn2 + e.mr) * sizeof(T), coff = (unsigned)(p.j * g.hn2 + e.mc) * sizeof(T);
+  // coefficient of the cell itself, inside the grid: for parity index f and
+  // cell u (the cells of colour 0 at plane i0 have k = 2 m + s0)
+  const int s0 = (p.i0 + p.j) & 1, di0 = HELMM ? 2 : 0;
+  const double rh2 = 1.0 / g.h2;
+  auto coef = [&](int diag) { return HELMM ? fma(nuh2, (double)diag, a0) : (double)(6 - diag); };
+  double ca[2][2];
+  bool wl[2][2];
+  unsigned pk = 0;
 #pragma unroll
-    for (int e = 0; e < HALO_REG; ++e)
-      if (hs.slot[e] >= 0) tq[hs.slot[e]] = hv[e];
-    if (hs.rem) {
-      auto val = plane_val(q);
-      for (int h = hs.tid + HALO_REG * hs.nthr; h < hs.total; h += hs.nthr) {
-        int r, cidx;
-        halo_slot(h, BX, BY, r, cidx);
-        const int jj = mwrap(jbase + r - 1, g.n1, g.bc1);
-        const int mm = mwrap(mbase + cidx - 1, g.hn2, g.bc2);
-        tq[r * W2 + cidx] = (jj >= 0 && mm >= 0) ? val(i, jj, mm) : T(0);
-      }
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k = 2 * (p.m0 + u) + (f ? 1 - s0 : s0);
+      const int dg = diag_jk(g, p.j, k, HELMM, d);
+      pk |= (unsigned)dg << (8 * f + 4 * u);
+      ca[f][u] = coef(di0 + dg);
+      wl[f][u] = HELMM && wall_jk(g, p.j, k, d);
     }
+  struct Win {
+    V2<T> q[2];
   };
-  auto rhs = [&](int i, V2<double> *bb) {
+  MarchOff at = march_off(g, p.i0, p.i1);
+  auto win_ld = [&](long long off) {
+    Win r;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) r.q[q] = ld2<T>(xg + q * g.half + off, rw * (unsigned)sizeof(T));
+    return r;
+  };
+  Win none;
+  none.q[0] = none.q[1] = V2<T>{T(0), T(0)};
+  const bool diw = HELMM ? g.bc0 && d != 0 : g.bc0 != 0;
+  const int e0 = diw ? 0 : -2, e1 = diw ? g.n0 - 1 : -2, z0 = g.bc0 ? 0 : -2, z1 = g.bc0 ? g.n0 - 1 : -2;
+  const int wf0 = HELMM && d == 0 && g.bc0 ? 0 : -2;
+  const int die = HELMM ? 2 + wall_ghost_diag(g.bc0) : 1;
+  struct Ops {
+    V2<T> hr[2];
+    T hc[2];
+    V2<double> b[2];
+    Win w;
+  };
+  auto fetch = [&](Ops &o) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      bb[q].x = 0.0;
-      bb[q].y = 0.0;
-      if (MODE == AP_HRESID) bb[q] = ld2<double>(bg + (long long)q * g.half + i * P + rw);
+      const T *xp = xg + q * g.half + at.nxt;
+      o.hr[q] = ld2<T>(xp, eoff);
+      o.hc[q] = ldo(xp, coff);
+      if (MODE == AP_HRESID) o.b[q] = ld2<double>(bg + q * g.half + at.nxt, rw * (unsigned)sizeof(double));
     }
+    o.w = win_ld(at.win);
   };
-  const DiagJK djk = diag_jk(g, p.j, p.m0, HELMM, d);
-  V2<T> prv[2], cur[2], nxt[2];
-  T hcur[2][HALO_REG];
-  V2<double> bbc[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    prv[q] = win(q, p.i0 - 1);
-    cur[q] = win(q, p.i0);
-    nxt[q] = win(q, p.i0 + 1);
-    hfetch(q, p.i0, hcur[q]);
-  }
-  rhs(p.i0, bbc);
   double acc = 0.0;
-  for (int i = p.i0; i < p.i1; ++i) {
-    const bool more = i + 1 < p.i1;
-    V2<T> nn[2];
-    T hnext[2][HALO_REG];
-    V2<double> bbn[2];
+  // as in k_sweep; f: parity index of colour 0 at plane i, and the LDS buffer
+  auto step = [&](int i, int f, const Win &wp, const Win &wc, Win &wn, const Ops &o, Ops &on) {
+    march_next(at, i);
+    fetch(on);
+    const int rowb = (p.ty + 1) * W2 + 2 * p.tx;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      nn[q] = more ? win(q, i + 2) : nxt[q];
-      if (more) {
-        hfetch(q, i + 1, hnext[q]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < HALO_REG; ++e) hnext[q][e] = hcur[q][e];
+      T *t = tile[f % NB][q];
+      t[rowb + 1] = wc.q[q].x;
+      t[rowb + 2] = wc.q[q].y;
+      if (e.rslot >= 0) {
+        t[e.rslot] = o.hr[q].x;
+        t[e.rslot + 1] = o.hr[q].y;
       }
-    }
-    if (more) rhs(i + 1, bbn);
-    else {
-      bbn[0] = bbc[0];
-      bbn[1] = bbc[1];
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      T *tq = tile[q];
-      tq[(p.ty + 1) * W2 + 2 * p.tx + 1] = cur[q].x;
-      tq[(p.ty + 1) * W2 + 2 * p.tx + 2] = cur[q].y;
-      hput(q, i, hcur[q]);
+      if (e.cslot >= 0) t[e.cslot] = o.hc[q];
+      if (e.thin && e.mthin >= 0) t[rowb + 3] = xg[q * g.half + at.cur + p.j * g.hn2 + e.mthin];
     }
     __syncthreads();
-    const long long r = i * P + rw;
-    const int di = diag_i(g, i, HELMM, d);
+    wn = i == z1 ? none : o.w;
+    const bool edge = i == e0 || i == e1;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const T *to = tile[1 - q];
-      const int s = (q + i + p.j) & 1;
-      const V2<double> bb = bbc[q];
-      double o[2];
+      const int fq = f ^ q;
+      const T *trow = tile[f % NB][1 - q] + rowb;
+      const int s = fq ? 1 - s0 : s0;
+      double r[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int col = 2 * p.tx + 1 + u;
-        const T *trow = to + (p.ty + 1) * W2;
-        double sum = (double)(u ? prv[1 - q].y : prv[1 - q].x) + (double)(u ? nxt[1 - q].y : nxt[1 - q].x) +
-                     (double)to[p.ty * W2 + col] + (double)to[(p.ty + 2) * W2 + col] + (double)trow[col - 1 + s] +
-                     (double)trow[col + s];
-        double xv = (double)(u ? cur[q].y : cur[q].x);
+        const double sum = (double)(u ? wp.q[1 - q].y : wp.q[1 - q].x) + (double)(u ? wn.q[1 - q].y : wn.q[1 - q].x) +
+                           (double)trow[u + 1 - W2] + (double)trow[u + 1 + W2] + (double)trow[u + s] +
+                           (double)trow[u + 1 + s];
+        const double xv = (double)(u ? wc.q[q].y : wc.q[q].x);
+        double cc = ca[fq][u];
+        if (edge) cc = coef(die + ((pk >> (8 * fq + 4 * u)) & 15));
         if (MODE == AP_LAP) {
-          o[u] = ((double)(6 - di - djk.dg(s, u)) * xv - sum) / g.h2;
+          r[u] = div_by<double>(fma(cc, xv, -sum), g.h2, rh2);
         } else {
-          const int diag = di + djk.dg(s, u);
-          const bool wall = d == 0 ? (g.bc0 && i == 0) : djk.wl(s, u);
-          double rv = (u ? bb.y : bb.x) - ((a0 + nuh2 * diag) * xv - nuh2 * sum);
-          o[u] = wall ? 0.0 : rv;
-          acc += o[u] * o[u];
+          const bool wall = i == wf0 || wl[fq][u];
+          const double rv = (u ? o.b[q].y : o.b[q].x) - fma(cc, xv, -mul_rn(nuh2, sum));
+          r[u] = wall ? 0.0 : rv;
+          acc = fma(r[u], r[u], acc);
         }
       }
-      st2(og + (long long)q * g.half + r, (TR)o[0], (TR)o[1]);
+      st2(og + q * g.half + at.cur, rw * (unsigned)sizeof(TR), (TR)r[0], (TR)r[1]);
     }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      prv[q] = cur[q];
-      cur[q] = nxt[q];
-      nxt[q] = nn[q];
-#pragma unroll
-      for (int e = 0; e < HALO_REG; ++e) hcur[q][e] = hnext[q][e];
-      bbc[q] = bbn[q];
-    }
+    if (NB == 1) __syncthreads();
+  };
+  Win w0 = win_ld(march_prev(g, at, p.i0)), w1 = win_ld(at.cur), w2, w3;
+  Ops oa, ob;
+  fetch(oa);
+  if (p.i0 == z0) w0 = none;
+  for (int i = p.i0;;) {
+    step(i, 0, w0, w1, w2, oa, ob);
+    if (++i >= p.i1) break;
+    step(i, 1, w1, w2, w3, ob, oa);
+    if (++i >= p.i1) break;
+    step(i, 0, w2, w3, w0, oa, ob);
+    if (++i >= p.i1) break;
+    step(i, 1, w3, w0, w1, ob, oa);
+    if (++i >= p.i1) break;
   }
   if (MODE == AP_HRESID) {
     const int tid = threadIdx.x + blockDim.x * threadIdx.y;

@@ -60,3 +60,21 @@ def test_solve_on_ragged_multigrid_levels(n, coarsest):
     assert rel(p.cpu().numpy(), p_ref) < 1e-10
     assert rel(phi.cpu().numpy(), phi_ref) < 1e-10
     sim.close()
+
+
+@pytest.mark.parametrize("bc", [MIXED, MIXED[::-1], (wl.BC_PERIODIC,) * 3])
+def test_stencils_on_tiles_one_pair_wide(bc):
+    # n2 / 4 = 67 is prime and above a wavefront: a workgroup is one pair of
+    # cells wide and its threads bring both halo columns of their row
+    n, h = (16, 20, 268), 1.0 / 16
+    cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=bc, nu=0.02, dt=0.01, precision=wl.PREC_FP64,
+                    precond=wl.PRECOND_FASTDIAG_EXACT, helm_rtol=1e-12)
+    sim = Sim(cfg, 0)
+    g = omac.Grid(n, h, bc)
+    rng = np.random.default_rng(67)
+    x = rng.standard_normal(n)
+    assert rel(sim.apply("laplacian", x).cpu().numpy().ravel(), omac.laplacian(g) @ x.ravel()) < 1e-13
+    r = rng.standard_normal((3,) + n) * g.face_dof_mask()
+    u = sim.apply("helm_solve", r).cpu().numpy()
+    assert rel(omac.helmholtz(g, cfg.nu, cfg.dt) @ u.ravel(), r.ravel()) < 2.0 * cfg.helm_rtol
+    sim.close()

@@ -194,7 +194,9 @@ template <int KER> __device__ __forceinline__ int support_start(double x, double
 // the float64 square root and its refinement.
 template <int KER, typename TA = double>
 __device__ __forceinline__ int axis_weights(double x, double inv_h, bool face, TA w[4]) {
-  double s = x * inv_h - (face ? 0.0 : 0.5);
+  // the fused form written out: every kernel that spreads or interpolates has
+  // to round s alike, or W and its transpose part company
+  const double s = fma(x, inv_h, face ? -0.0 : -0.5);
   if (KER == KER_PESKIN4) {
     double fl = floor(s);
     TA f = (TA)(s - fl);
@@ -223,15 +225,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-// Sum over groups of 16 lanes (lanes 16q .. 16q+15), fixed order.
-template <typename TA>
-__device__ __forceinline__ TA sum16(TA v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-
 // Exclusive scan of n integers by one workgroup of SCAN1_T threads, four per
 // thread and pass: put(i, value, sum of the values before it) for every i;
 // returns the total.

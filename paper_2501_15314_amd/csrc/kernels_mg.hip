@@ -339,13 +339,33 @@ hipError_t mg_prolong(const Geo &gf, T *xf, const Geo &gc, const T *xc, hipStrea
 // k_prolong in the same order (pc_first, pc_relax, pc_resid, blend34), so a
 // tile level gives the bits of the march kernels.
 //
-// Region coordinates r in [0, R) of a tile at grid origin o with halo H stand
-// for the unwrapped grid coordinate u = o - H + r.  A wall axis has no cells
-// outside [0, n) (their LDS slots hold 0, which a neighbour sum then adds as
-// the missing neighbour); a periodic axis wraps.  Origins and halos are even
-// and n is even, so the colour of a cell is the parity of r0 + r1 + r2.
+// Region coordinates r of a tile at grid origin o with halo H stand for the
+// unwrapped grid coordinate u = o - H + r.  A wall axis has no cells outside
+// [0, n) (their LDS slots hold 0, which a neighbour sum then adds as the
+// missing neighbour); a periodic axis wraps.  Origins and halos are even and n
+// is even, so the colour of a cell is the parity of r0 + r1 + r2.
+//
+// Layout.  The region holds each colour by itself, row by row like the grid:
+// (r0, r1) a row of 8 entries per colour, cells r2 = 2 m + parity.  Along axis
+// 2 the halo is 4 whatever the sweeps, which puts every pair of entries on an
+// even in-row index of the grid.  A thread owns half a row, 4 entries of both
+// colours, for the whole kernel: their right-hand sides, values and reciprocal
+// neighbour counts (0 for a cell outside the grid) stay in registers, and
+// from LDS it reads four vectors and one value per half sweep, on consecutive
+// addresses for consecutive threads.  No cell is tested: what the rows' ends
+// hold beyond the halo's reach is wrong but never used.
+//
+// Bounded by latency where the tiles are fewer than the compute units (32^3),
+// else by vector instructions and LDS.  Against one thread per cell column,
+// every cell testing box, walls and count for itself and reading its six
+// neighbours and b from LDS: descent at 64^3 10.5 -> 6.4 us, at 32^3 6.9 ->
+// 4.3 (float64 13.1 -> 8.6, 8.1 -> 4.7), ascent 7.7 -> 6.3 and 6.1 -> 5.0 (8.7
+// -> 8.4, 6.1 -> 5.9).
 constexpr int TL_TS = 8;  // tile edge in cells
-constexpr int TL_THREADS = 512;  // at most, per tile workgroup (tile_threads: whole region columns)
+constexpr int TL_H2 = 4;  // halo along axis 2
+constexpr int TL_ROW = (TL_TS + 2 * TL_H2) / 2;                                         // entries of a row per colour
+__host__ __device__ constexpr int tile_edge(int sweeps) { return TL_TS + 4 * sweeps; }  // region edge, axes 0 and 1
+__host__ __device__ constexpr int tile_threads(int R) { return 2 * R * R; }
 
 struct TileAxes {
   int o[3], n[3], bc[3];
@@ -374,93 +394,112 @@ __device__ __forceinline__ TileAxes tile_axes(const Geo &g, int scale) {
   return t;
 }
 
-// A thread's share of the sweeps over an LDS region of edge R: half a row,
-// (r0, r1) = the row, cells r2 in [s0, s0 + R/2) (2 R^2 <= TL_THREADS threads
-// take part), with what the row's cells share: whether the row lies in the
-// grid, the neighbours its axes 0 and 1 leave (nn01) and its LDS base.  LDS
-// rows are R + 1 entries apart, so the rows that the lanes of a wavefront
-// work on fall in different banks.
-template <int R>
-struct TileRow {
-  static constexpr int SEG = R / 2;  // even: a segment starts on an even r2
-  int r0, r1, s0, u0, u1, nn01, qrow;
-  bool live;
+template <typename T>
+struct alignas(16) Quad {
+  T v[4];
 };
-template <int R>
-__device__ __forceinline__ TileRow<R> tile_row(const TileAxes &ax, int H) {
-  static_assert(2 * R * R <= TL_THREADS && (R / 2) % 2 == 0, "two threads per row, even segments");
-  TileRow<R> w;
+
+// A thread's half row of the region: its place, the offsets of its two pairs
+// of entries in a colour plane of the grid, and what its cells share.
+template <typename T, int R>
+struct TileRow {
+  int r0, r1, h, par;  // par: (r0 + r1) & 1
+  int q;               // LDS slot of its first entry
+  int nn01;            // neighbours that axes 0 and 1 leave
+  bool live;           // the row lies in the grid
+  bool tile;           // the row is one of the tile's own
+  long long off[2];
+  T inv[2][4];  // 1 / neighbours per colour and entry, 0 outside the grid
+
+  __device__ __forceinline__ bool box(int lo) const {
+    return live && r0 >= lo && r0 < R - lo && r1 >= lo && r1 < R - lo;
+  }
+  // unwrapped axis-2 coordinate of entry e of colour c
+  __device__ __forceinline__ int u2(const TileAxes &ax, int c, int e) const {
+    return ax.o[2] - TL_H2 + 2 * (4 * h + e) + ((c + par) & 1);
+  }
+};
+template <typename T, int R>
+__device__ __forceinline__ TileRow<T, R> tile_row(const Geo &g, const TileAxes &ax) {
+  constexpr int H = (R - TL_TS) / 2;
+  TileRow<T, R> w;
   const int tid = threadIdx.x, row = tid >> 1;
+  w.h = tid & 1;
   w.r0 = row / R;
-  w.r1 = row % R;
-  w.s0 = (tid & 1) * TileRow<R>::SEG;
-  w.u0 = ax.o[0] - H + w.r0;
-  w.u1 = ax.o[1] - H + w.r1;
-  w.live = row < R * R && ax.inside(0, w.u0) && ax.inside(1, w.u1);
-  w.nn01 = 6 - ax.walls(0, w.u0) - ax.walls(1, w.u1);
-  w.qrow = (w.r0 * R + w.r1) * (R + 1);
+  w.r1 = row - w.r0 * R;
+  w.par = (w.r0 + w.r1) & 1;
+  w.q = TL_ROW * row + 4 * w.h;
+  const int u0 = ax.o[0] - H + w.r0, u1 = ax.o[1] - H + w.r1;
+  w.live = ax.inside(0, u0) && ax.inside(1, u1);
+  w.tile = w.r0 >= H && w.r0 < H + TL_TS && w.r1 >= H && w.r1 < H + TL_TS;
+  w.nn01 = 6 - ax.walls(0, u0) - ax.walls(1, u1);
+  // outside a wall box (nothing used there) the first row, the first pair
+  const long long line = w.live ? ((long long)ax.wrap(0, u0) * g.n1 + ax.wrap(1, u1)) * g.hn2 : 0;
+#pragma unroll
+  for (int z = 0; z < 2; ++z) {
+    const int m = (ax.o[2] - TL_H2) / 2 + 4 * w.h + 2 * z;
+    const int mw = m + (m < 0 ? g.hn2 : 0) - (m >= g.hn2 ? g.hn2 : 0);
+    w.off[z] = line + (ax.inside(2, 2 * m) ? mw : 0);
+  }
+  const T i0 = w.live ? inv_nn<T>(w.nn01) : T(0);
+  const bool edge = ax.bc[2] && (ax.o[2] == 0 || ax.o[2] + TL_TS == ax.n[2]);
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w.inv[c][e] = i0;
+  if (edge) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int u2 = w.u2(ax, c, e);
+        w.inv[c][e] = w.live && ax.inside(2, u2) ? inv_nn<T>(w.nn01 - ax.walls(2, u2)) : T(0);
+      }
+  }
   return w;
 }
-
-// The loads of a region of edge R: a tile kernel runs KP = TL_THREADS / R^2
-// threads per column (r1, r2) of the region, thread tid taking planes
-// r0 = tid / R^2 + KP m, so that everything but the plane is fixed per
-// thread and consecutive threads read consecutive cells of a row.
-template <int R>
-struct TileCols {
-  static constexpr int KP = TL_THREADS / (R * R);
-  static constexpr int NT = KP * R * R;  // threads of the launch
-  static constexpr int NL = R / KP;      // planes per thread
-  static_assert(KP >= 2 && R % KP == 0 && NL <= 32, "whole columns, two threads per sweep row, one bit per plane");
-};
-__host__ __device__ constexpr int tile_threads(int R) { return (TL_THREADS / (R * R)) * R * R; }
-// a thread's column: its region and grid coordinates along axes 1 and 2
-struct TileCol {
-  int r1, r2, rb, u1, u2, par, w12, plane;
-  bool in12;
-  long long base0, base1;  // split-layout offset of the column in plane 0, per colour of its cell there
-};
-template <int R>
-__device__ __forceinline__ TileCol tile_col(const Geo &g, const TileAxes &ax, int H) {
-  TileCol c;
-  const int tid = threadIdx.x;
-  c.r2 = tid % R;
-  c.r1 = (tid / R) % R;
-  c.rb = tid / (R * R);
-  c.u1 = ax.o[1] - H + c.r1;
-  c.u2 = ax.o[2] - H + c.r2;
-  c.in12 = ax.inside(1, c.u1) && ax.inside(2, c.u2);
-  const int gj = ax.wrap(1, c.u1), gk = ax.wrap(2, c.u2);
-  c.par = (gj + gk) & 1;
-  c.w12 = ax.walls(1, c.u1) + ax.walls(2, c.u2);
-  c.plane = g.n1 * g.hn2;
-  c.base0 = gj * g.hn2 + (gk >> 1);
-  c.base1 = c.base0 + g.half;
-  return c;
+// the four entries of one colour from the grid (p: that colour's plane)
+template <typename T, typename S>
+__device__ __forceinline__ Quad<T> tile_load(const S *p, const long long off[2]) {
+  const V2<T> a = ld2<T>(p + off[0]), b = ld2<T>(p + off[1]);
+  return Quad<T>{{a.x, a.y, b.x, b.y}};
 }
-// split-layout index of the cell of column c in grid plane gi
-__device__ __forceinline__ long long tile_cidx(const TileCol &c, int gi) {
-  return (((gi + c.par) & 1) ? c.base1 : c.base0) + gi * c.plane;
-}
-
-// one red-black half sweep of colour c over the cells of the box [LO, R-LO)^3
-// of an LDS region of edge R (x, b by region index)
-template <typename T, int R, int LO>
-__device__ __forceinline__ void tile_sweep(T *sx, const T *sb, const TileAxes &ax, const TileRow<R> &w, int H, int c,
-                                           T th2) {
-  if (w.live && w.r0 >= LO && w.r0 < R - LO && w.r1 >= LO && w.r1 < R - LO) {
-    const int p = (c + w.r0 + w.r1) & 1;
+// the sums of the neighbours of the thread's four cells of colour c: own row's
+// other-colour entries from registers, the rows beside and the one entry
+// beyond from LDS (o: the other colour)
+template <typename T, int R>
+__device__ __forceinline__ Quad<T> tile_sums(const T *o, const TileRow<T, R> &w, int c, const Quad<T> &x) {
+  const Quad<T> xm = *(const Quad<T> *)(o + w.q - TL_ROW * R), xp = *(const Quad<T> *)(o + w.q + TL_ROW * R);
+  const Quad<T> ym = *(const Quad<T> *)(o + w.q - TL_ROW), yp = *(const Quad<T> *)(o + w.q + TL_ROW);
+  const bool s = (c + w.par) & 1;
+  const T far = o[w.q + (s ? 4 : -1)];
+  const T z[5] = {s ? x.v[0] : far, s ? x.v[1] : x.v[0], s ? x.v[2] : x.v[1], s ? x.v[3] : x.v[2], s ? far : x.v[3]};
+  Quad<T> r;
 #pragma unroll
-    for (int m = 0; m < R / 4; ++m) {
-      const int r2 = w.s0 + 2 * m + p, u2 = ax.o[2] - H + r2;
-      if (r2 < LO || r2 >= R - LO || !ax.inside(2, u2)) continue;
-      const int q = w.qrow + r2;
-      constexpr int DJ = R + 1, DI = R * (R + 1);
-      const T sum = sx[q - DI] + sx[q + DI] + sx[q - DJ] + sx[q + DJ] + sx[q - 1] + sx[q + 1];
-      sx[q] = pc_relax(th2, sb[q], sum, w.nn01 - ax.walls(2, u2));
-    }
+  for (int e = 0; e < 4; ++e) r.v[e] = xm.v[e] + xp.v[e] + ym.v[e] + yp.v[e] + z[e] + z[e + 1];
+  return r;
+}
+// one red-black half sweep of colour c over the rows of the box [lo, R - lo)^2
+template <typename T, int R>
+__device__ __forceinline__ void tile_sweep(T (*sx)[TL_ROW * R * R], const TileRow<T, R> &w, int c, int lo,
+                                           const Quad<T> b[2], Quad<T> x[2], T th2) {
+  if (w.box(lo)) {
+    const Quad<T> sum = tile_sums<T, R>(sx[1 - c], w, c, x[1 - c]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[c].v[e] = fma(th2, b[c].v[e], sum.v[e]) * w.inv[c][e];  // pc_relax
+    *(Quad<T> *)(sx[c] + w.q) = x[c];
   }
   __syncthreads();
+}
+// the tile's own cells of both colours: two entries of each half row
+template <typename T, int R>
+__device__ __forceinline__ void tile_store(const Geo &g, const TileRow<T, R> &w, const Quad<T> x[2], T *out) {
+  if (!w.tile) return;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    T *p = out + c * g.half + (w.h ? w.off[0] : w.off[1]);
+    st2<T>(p, 0, w.h ? x[c].v[0] : x[c].v[2], w.h ? x[c].v[1] : x[c].v[3]);
+  }
 }
 
 // Descent of one tile: PRE red-black sweeps from x = 0 (red then black), x of
@@ -469,73 +508,50 @@ __device__ __forceinline__ void tile_sweep(T *sx, const T *sb, const TileAxes &a
 // black ones were relaxed last and have none).  The halo is 2 PRE: the first
 // red values need only their own b, every later half sweep shrinks the box.
 template <typename T, typename TB, int PRE>
-__global__ void __launch_bounds__(TL_THREADS) k_tile_down(Geo g, T *x, const TB *b, Geo gc, T *bc) {
-  constexpr int H = 2 * PRE, R = TL_TS + 2 * H, R3 = R * R * (R + 1);
-  constexpr int DJ = R + 1, DI = R * (R + 1);
-  constexpr int TC = TL_TS / 2;
-  __shared__ T sx[R3];
-  __shared__ T sb[R3];
+__global__ void __launch_bounds__(tile_threads(tile_edge(PRE))) k_tile_down(Geo g, T *x, const TB *b, Geo gc, T *bc) {
+  constexpr int R = tile_edge(PRE), H = 2 * PRE, TC = TL_TS / 2;
+  __shared__ __attribute__((aligned(16))) T sx[2][TL_ROW * R * R];
+  __shared__ __attribute__((aligned(16))) T rs[TL_TS * TL_TS * TC];  // red residuals [row][coarse K]
   const TileAxes ax = tile_axes(g, 1);
-  const TileRow<R> w = tile_row<R>(ax, H);
+  const TileRow<T, R> w = tile_row<T, R>(g, ax);
   const int tid = threadIdx.x;
   const T th2 = (T)g.h2, ih2 = (T)(1.0 / g.h2);
-  // b over the region, column by column (every load of a thread issued
-  // before the first is used; a cell outside the grid loads element 0 and
-  // keeps 0); the red cells take their first-sweep values on the way
-  using CL = TileCols<R>;
-  {
-    const TileCol c = tile_col<R>(g, ax, H);
-    TB bl[CL::NL];
-    unsigned ok = 0;
+  Quad<T> bb[2], xx[2];
 #pragma unroll
-    for (int m = 0; m < CL::NL; ++m) {
-      const int u0 = ax.o[0] - H + c.rb + CL::KP * m;
-      const bool in = c.in12 && ax.inside(0, u0);
-      ok |= (unsigned)in << m;
-      bl[m] = b[in ? tile_cidx(c, ax.wrap(0, u0)) : 0];
-    }
+  for (int c = 0; c < 2; ++c) bb[c] = tile_load<T>(b + c * g.half, w.off);
 #pragma unroll
-    for (int m = 0; m < CL::NL; ++m) {
-      const int r0 = c.rb + CL::KP * m, q = (r0 * R + c.r1) * DJ + c.r2;
-      const bool in = (ok >> m) & 1u;
-      const T bv = in ? (T)bl[m] : T(0);
-      sb[q] = bv;
-      sx[q] = (in && !((r0 + c.r1 + c.r2) & 1)) ? pc_first(th2, bv, 6 - ax.walls(0, ax.o[0] - H + r0) - c.w12)
-                                                : T(0);
-    }
+  for (int e = 0; e < 4; ++e) {
+    xx[0].v[e] = w.inv[0][e] != T(0) ? mul_rn(mul_rn(th2, bb[0].v[e]), w.inv[0][e]) : T(0);  // pc_first
+    xx[1].v[e] = T(0);
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) *(Quad<T> *)(sx[c] + w.q) = xx[c];
+  __syncthreads();
+  tile_sweep<T, R>(sx, w, 1, 1, bb, xx, th2);
+  if (PRE == 2) {
+    tile_sweep<T, R>(sx, w, 0, 2, bb, xx, th2);
+    tile_sweep<T, R>(sx, w, 1, 3, bb, xx, th2);
+  }
+  tile_store<T, R>(g, w, xx, x);
+  // the red residuals of the tile's rows; a row's red cell at entry m is the
+  // child of coarse K = m - TL_H2 / 2 there
+  if (w.tile) {
+    const Quad<T> sum = tile_sums<T, R>(sx[1], w, 0, xx[1]);
+    T r[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      r[e] = pc_resid(bb[0].v[e], xx[0].v[e], sum.v[e], w.nn01 - ax.walls(2, w.u2(ax, 0, e)), ih2);
+    T *p = rs + ((w.r0 - H) * TL_TS + w.r1 - H) * TC + 2 * w.h;
+    st2<T>(p, 0, w.h ? r[0] : r[2], w.h ? r[1] : r[3]);
   }
   __syncthreads();
-  tile_sweep<T, R, 1>(sx, sb, ax, w, H, 1, th2);
-  if (PRE == 2) {
-    tile_sweep<T, R, 2>(sx, sb, ax, w, H, 0, th2);
-    tile_sweep<T, R, 3>(sx, sb, ax, w, H, 1, th2);
-  }
-  // the tile's cells, both colours
-  for (int e = tid; e < TL_TS * TL_TS * TL_TS; e += CL::NT) {
-    const int r2 = H + e % TL_TS, r1 = H + (e / TL_TS) % TL_TS, r0 = H + e / (TL_TS * TL_TS);
-    x[sidx(g, ax.o[0] - H + r0, ax.o[1] - H + r1, ax.o[2] - H + r2)] = sx[(r0 * R + r1) * (R + 1) + r2];
-  }
-  // coarse cell (C0, C1, C2) of the tile: the red child of fine row
-  // (2 C0 + di, 2 C1 + dj) sits at 2 C2 + ((di + dj) & 1); the residuals are
+  // coarse cell (C0, C1, C2) of the tile: the residuals of its four rows,
   // added plane by plane per row, then the two rows, as k_restrict does
   if (tid < TC * TC * TC) {
     const int C2 = tid % TC, C1 = (tid / TC) % TC, C0 = tid / (TC * TC);
-    T acc[2];
-#pragma unroll
-    for (int dj = 0; dj < 2; ++dj) {
-      T a = T(0);
-#pragma unroll
-      for (int di = 0; di < 2; ++di) {
-        const int r0 = H + 2 * C0 + di, r1 = H + 2 * C1 + dj, r2 = H + 2 * C2 + ((di + dj) & 1);
-        const int q = (r0 * R + r1) * (R + 1) + r2;
-        const T sum = sx[q - DI] + sx[q + DI] + sx[q - DJ] + sx[q + DJ] + sx[q - 1] + sx[q + 1];
-        const int nn = 6 - ax.walls(0, ax.o[0] - H + r0) - ax.walls(1, ax.o[1] - H + r1) -
-                       ax.walls(2, ax.o[2] - H + r2);
-        a += pc_resid(sb[q], sx[q], sum, nn, ih2);
-      }
-      acc[dj] = a;
-    }
-    bc[sidx(gc, ax.o[0] / 2 + C0, ax.o[1] / 2 + C1, ax.o[2] / 2 + C2)] = (acc[0] + acc[1]) * (T)0.125;
+    const T *p = rs + (2 * C0 * TL_TS + 2 * C1) * TC + C2;
+    const T a0 = p[0] + p[TL_TS * TC], a1 = p[TC] + p[TL_TS * TC + TC];
+    bc[sidx(gc, ax.o[0] / 2 + C0, ax.o[1] / 2 + C1, ax.o[2] / 2 + C2)] = (a0 + a1) * (T)0.125;
   }
 }
 
@@ -545,112 +561,85 @@ __global__ void __launch_bounds__(TL_THREADS) k_tile_down(Geo g, T *x, const TB 
 // then POST sweeps black then red, and the tile's cells written to xout.
 // xout is not xin: neighbouring tiles still read the halo's old values.  The
 // halo is 2 POST; the coarse block spans the parents and their neighbours of
-// the whole region.
+// the whole region, past a wall the nearest cell (the parent itself).
 template <typename T, typename TB, int POST>
-__global__ void __launch_bounds__(TL_THREADS) k_tile_up(Geo g, const T *xin, T *xout, const TB *b, Geo gc,
-                                                            const T *xc) {
-  constexpr int H = 2 * POST, R = TL_TS + 2 * H, R3 = R * R * (R + 1), DJ = R + 1;
-  constexpr int HC = H / 2 + 1, RC = TL_TS / 2 + 2 * HC, RC3 = RC * RC * RC;
-  __shared__ T sx[R3];
-  __shared__ T sb[R3];
-  __shared__ T sc[RC3];
+__global__ void __launch_bounds__(tile_threads(tile_edge(POST))) k_tile_up(Geo g, const T *xin, T *xout, const TB *b,
+                                                                            Geo gc, const T *xc) {
+  constexpr int R = tile_edge(POST), H = 2 * POST, NT = tile_threads(R);
+  constexpr int RC = R / 2 + 2, RK = TL_ROW + 2, RKP = 12;  // coarse block: RC x RC rows of RK, RKP apart
+  constexpr int NC = (RC * RC * RK + NT - 1) / NT;
+  __shared__ __attribute__((aligned(16))) T sx[2][TL_ROW * R * R];
+  __shared__ __attribute__((aligned(16))) T sc[RC * RC * RKP];
   const TileAxes ax = tile_axes(g, 1), cx = tile_axes(g, 2);
-  const TileRow<R> w = tile_row<R>(ax, H);
+  const TileRow<T, R> w = tile_row<T, R>(g, ax);
   const int tid = threadIdx.x;
   const T th2 = (T)g.h2;
-  // the coarse block, then b and the red x of the region column by column,
-  // every load of a thread issued before the first is used (slots outside
-  // the grid load element 0 and keep 0; black x values are overwritten
-  // unread)
-  using CL = TileCols<R>;
-  constexpr int NC = (RC3 + CL::NT - 1) / CL::NT;
-  static_assert(NC <= 32, "one bit per slot");
-  {
-    T cl[NC];
-    unsigned okc = 0;
+  // the coarse block, b and the red x: every load issued before the first is used
+  T cl[NC];
 #pragma unroll
-    for (int t = 0; t < NC; ++t) {
-      const int e = tid + t * CL::NT;
-      const int c2 = e % RC, c1 = (e / RC) % RC, c0 = e / (RC * RC);
-      const int U0 = cx.o[0] - HC + c0, U1 = cx.o[1] - HC + c1, U2 = cx.o[2] - HC + c2;
-      const bool in = e < RC3 && cx.inside(0, U0) && cx.inside(1, U1) && cx.inside(2, U2);
-      okc |= (unsigned)in << t;
-      cl[t] = xc[in ? sidx(gc, cx.wrap(0, U0), cx.wrap(1, U1), cx.wrap(2, U2)) : 0];
-    }
-    const TileCol c = tile_col<R>(g, ax, H);
-    TB bl[CL::NL];
-    T xl[CL::NL];
-    unsigned ok = 0;
-#pragma unroll
-    for (int m = 0; m < CL::NL; ++m) {
-      const int r0 = c.rb + CL::KP * m, u0 = ax.o[0] - H + r0;
-      const bool in = c.in12 && ax.inside(0, u0);
-      ok |= (unsigned)in << m;
-      const long long q = in ? tile_cidx(c, ax.wrap(0, u0)) : 0;
-      bl[m] = b[q];
-      xl[m] = xin[(in && !((r0 + c.r1 + c.r2) & 1)) ? q : 0];
-    }
-#pragma unroll
-    for (int t = 0; t < NC; ++t) {
-      const int e = tid + t * CL::NT;
-      if (e < RC3) sc[e] = ((okc >> t) & 1u) ? cl[t] : T(0);
-    }
-#pragma unroll
-    for (int m = 0; m < CL::NL; ++m) {
-      const int r0 = c.rb + CL::KP * m, q = (r0 * R + c.r1) * DJ + c.r2;
-      const bool in = (ok >> m) & 1u;
-      sb[q] = in ? (T)bl[m] : T(0);
-      sx[q] = (in && !((r0 + c.r1 + c.r2) & 1)) ? xl[m] : T(0);
-    }
-  }
-  __syncthreads();
-  // prolongation onto the red cells of the thread's half row: the planes
-  // (u0 - 1) >> 1 and the next with weights by the parity of u0, and the
-  // coarse rows J, Jo are the row's; per cell the coarse K and Ko
-  if (w.live) {
-    auto other = [&](int a, int P, int odd) {
-      const int O = P + (odd ? 1 : -1);
-      return (cx.bc[a] && (O < 0 || O >= cx.n[a])) ? P : O;
+  for (int t = 0; t < NC; ++t) {
+    const int e = min(tid + t * NT, RC * RC * RK - 1), row = e / RK, c2 = e - row * RK, c0 = row / RC, c1 = row - c0 * RC;
+    auto at = [&](int a, int u) {
+      const int v = cx.bc[a] ? min(max(u, 0), cx.n[a] - 1) : cx.wrap(a, u);
+      return v;
     };
-    int lo = (w.u0 - 1) >> 1, hi = lo + 1;
-    if (cx.bc[0]) {
-      lo = lo < 0 ? 0 : lo;
-      hi = hi >= cx.n[0] ? cx.n[0] - 1 : hi;
-    }
-    const int J = w.u1 >> 1, Jo = other(1, J, w.u1 & 1);
-    const int b0 = cx.o[0] - HC, b1 = cx.o[1] - HC, b2 = cx.o[2] - HC;
-    const T wlo = (w.u0 & 1) ? (T)0.75 : (T)0.25, whi = (T)1 - wlo;
-    const int plo = ((lo - b0) * RC + (J - b1)) * RC - b2, plo_o = ((lo - b0) * RC + (Jo - b1)) * RC - b2;
-    const int phi = ((hi - b0) * RC + (J - b1)) * RC - b2, phi_o = ((hi - b0) * RC + (Jo - b1)) * RC - b2;
-    const int p = (w.r0 + w.r1) & 1;
+    cl[t] = xc[sidx(gc, at(0, cx.o[0] - H / 2 - 1 + c0), at(1, cx.o[1] - H / 2 - 1 + c1),
+                    at(2, cx.o[2] - TL_H2 / 2 - 1 + c2))];
+  }
+  Quad<T> bb[2], xx[2];
 #pragma unroll
-    for (int m = 0; m < R / 4; ++m) {
-      const int r2 = w.s0 + 2 * m + p, u2 = ax.o[2] - H + r2;
-      if (!ax.inside(2, u2)) continue;
-      const int K = u2 >> 1, Ko = other(2, K, u2 & 1);
-      T acc = T(0);
+  for (int c = 0; c < 2; ++c) bb[c] = tile_load<T>(b + c * g.half, w.off);
+  xx[0] = tile_load<T>(xin, w.off);
 #pragma unroll
-      for (int pl = 0; pl < 2; ++pl) {
-        const int pJ = pl ? phi : plo, pO = pl ? phi_o : plo_o;
-        const T zJ = blend34(sc[pJ + K], sc[pJ + Ko]);
-        const T zO = blend34(sc[pO + K], sc[pO + Ko]);
-        acc = fma(pl ? whi : wlo, blend34(zJ, zO), acc);
-      }
-      const int q = w.qrow + r2;
-      sx[q] = sx[q] + acc;
-    }
+  for (int t = 0; t < NC; ++t) {
+    const int e = tid + t * NT, row = e / RK;
+    if (e < RC * RC * RK) sc[row * RKP + (e - row * RK)] = cl[t];
   }
   __syncthreads();
-  tile_sweep<T, R, 1>(sx, sb, ax, w, H, 1, th2);
-  tile_sweep<T, R, 2>(sx, sb, ax, w, H, 0, th2);
+  // prolongation onto the red cells of the half row: coarse planes
+  // (u0 - 1) >> 1 and the next with weights by the parity of u0 (that of r0),
+  // rows J and Jo; entry m has the parent K = m, its neighbour on the side of
+  // the cell's parity (block slots m + 1 and m or m + 2)
+  {
+    const bool o0 = w.r0 & 1, o1 = w.r1 & 1, o2 = w.par;
+    const int lo = (w.r0 + 1) >> 1, J = (w.r1 >> 1) + 1, Jo = o1 ? J + 1 : J - 1;
+    const T wlo = o0 ? (T)0.75 : (T)0.25, whi = (T)1 - wlo;
+    T acc[4];
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl) {
+      T zz[2][4];
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const T *p = sc + ((lo + pl) * RC + (y ? Jo : J)) * RKP + 4 * w.h;
+        const Quad<T> a = *(const Quad<T> *)p;
+        const T a4 = p[4], a5 = p[5];
+        zz[y][0] = blend34(a.v[1], o2 ? a.v[2] : a.v[0]);
+        zz[y][1] = blend34(a.v[2], o2 ? a.v[3] : a.v[1]);
+        zz[y][2] = blend34(a.v[3], o2 ? a4 : a.v[2]);
+        zz[y][3] = blend34(a4, o2 ? a5 : a.v[3]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const T z = blend34(zz[0][e], zz[1][e]);
+        acc[e] = pl ? fma(whi, z, acc[e]) : wlo * z;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      xx[0].v[e] = w.inv[0][e] != T(0) ? xx[0].v[e] + acc[e] : T(0);
+      xx[1].v[e] = T(0);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) *(Quad<T> *)(sx[c] + w.q) = xx[c];
+  __syncthreads();
+  tile_sweep<T, R>(sx, w, 1, 1, bb, xx, th2);
+  tile_sweep<T, R>(sx, w, 0, 2, bb, xx, th2);
   if (POST == 2) {
-    tile_sweep<T, R, 3>(sx, sb, ax, w, H, 1, th2);
-    tile_sweep<T, R, 4>(sx, sb, ax, w, H, 0, th2);
+    tile_sweep<T, R>(sx, w, 1, 3, bb, xx, th2);
+    tile_sweep<T, R>(sx, w, 0, 4, bb, xx, th2);
   }
-  for (int e = tid; e < TL_TS * TL_TS * TL_TS; e += CL::NT) {
-    const int r2 = H + e % TL_TS, r1 = H + (e / TL_TS) % TL_TS, r0 = H + e / (TL_TS * TL_TS);
-    xout[sidx(g, ax.o[0] - H + r0, ax.o[1] - H + r1, ax.o[2] - H + r2)] = sx[(r0 * R + r1) * (R + 1) + r2];
-  }
+  tile_store<T, R>(g, w, xx, xout);
 }
 
 bool tile_level_fits(const Geo &g, const Geo &gc, int pre, int post) {
@@ -665,10 +654,10 @@ hipError_t mg_tile_down(const Geo &g, T *x, const TB *b, const Geo &gc, T *bc, i
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
   if (pre == 2)
-    hipExtLaunchKernelGGL((k_tile_down<T, TB, 2>), dim3(tile_count(g)), dim3(tile_threads(TL_TS + 8)), 0, s, e0,
+    hipExtLaunchKernelGGL((k_tile_down<T, TB, 2>), dim3(tile_count(g)), dim3(tile_threads(tile_edge(2))), 0, s, e0,
                           e1, 0, g, x, b, gc, bc);
   else
-    hipExtLaunchKernelGGL((k_tile_down<T, TB, 1>), dim3(tile_count(g)), dim3(tile_threads(TL_TS + 4)), 0, s, e0,
+    hipExtLaunchKernelGGL((k_tile_down<T, TB, 1>), dim3(tile_count(g)), dim3(tile_threads(tile_edge(1))), 0, s, e0,
                           e1, 0, g, x, b, gc, bc);
   return hipGetLastError();
 }
@@ -679,10 +668,10 @@ hipError_t mg_tile_up(const Geo &g, const T *xin, T *xout, const TB *b, const Ge
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
   if (post == 2)
-    hipExtLaunchKernelGGL((k_tile_up<T, TB, 2>), dim3(tile_count(g)), dim3(tile_threads(TL_TS + 8)), 0, s, e0,
+    hipExtLaunchKernelGGL((k_tile_up<T, TB, 2>), dim3(tile_count(g)), dim3(tile_threads(tile_edge(2))), 0, s, e0,
                           e1, 0, g, xin, xout, b, gc, xc);
   else
-    hipExtLaunchKernelGGL((k_tile_up<T, TB, 1>), dim3(tile_count(g)), dim3(tile_threads(TL_TS + 4)), 0, s, e0,
+    hipExtLaunchKernelGGL((k_tile_up<T, TB, 1>), dim3(tile_count(g)), dim3(tile_threads(tile_edge(1))), 0, s, e0,
                           e1, 0, g, xin, xout, b, gc, xc);
   return hipGetLastError();
 }

@@ -213,11 +213,10 @@ int march_min_blocks_setting() {
 
 // Multigrid levels of at most this many cells run as tile levels (two
 // launches per level instead of seven: k_tile_down, k_tile_up).  On a 256^3
-// grid that is the 64^3 and 32^3 levels: 10.0 + 7.5 us and 6.8 + 6.2 us per
-// level against seven launches of about 4.5 us (142.5 -> 149.0 solves/s);
-// with the 128^3 level too, the tiles' redundant halo work (an 8^3 tile loads
-// 16^3 cells) outweighs the launches saved there (143.5 solves/s), and the
-// finest levels stream through the march kernels near the bandwidth bound.
+// grid that is the 64^3 and 32^3 levels: 6.4 + 6.3 us and 4.3 + 5.0 us per
+// level against seven launches of 3.5 to 4.5 us.  At 128^3 the tiles' redundant
+// halo work (an 8^3 tile loads 16^3 cells) outweighs the launches saved: eight
+// times the work of the 64^3 level against 38 us for the seven launches.
 // IBSCHUR_MG_TILE_CELLS in the environment at sim_create overrides it
 // (0: no tile levels).
 constexpr long long MG_TILE_CELLS_DEFAULT = 64LL * 64 * 64;
@@ -230,18 +229,22 @@ long long mg_tile_cells_setting() {
 }
 // Whether level l of the hierarchy dims (3 entries per level) runs as a tile
 // level: a V-cycle preconditioner, a next level of half the edges, edges that
-// are multiples of the 8-cell tile, 1 or 2 pre- and post-sweeps, and at most
-// mg_tile_cells_setting() cells.
+// the tile kernels take (tile_edges_fit), 1 or 2 pre- and post-sweeps, and at
+// most mg_tile_cells_setting() cells.
 bool tile_level(const sim_config *c, const std::vector<int> &dims, size_t l) {
   if (c->precond != SIM_PRECOND_VCYCLE || 3 * l + 5 >= dims.size()) return false;
   if (c->mg_pre < 1 || c->mg_pre > 2 || c->mg_post < 1 || c->mg_post > 2) return false;
   long long cells = 1;
   for (int a = 0; a < 3; ++a) {
     const int n = dims[3 * l + a];
-    if (n % 8 != 0 || dims[3 * l + 3 + a] * 2 != n) return false;
+    if (dims[3 * l + 3 + a] * 2 != n) return false;
     cells *= n;
   }
-  return cells <= mg_tile_cells_setting();
+  return tile_edges_fit(dims[3 * l], dims[3 * l + 1], dims[3 * l + 2]) && cells <= mg_tile_cells_setting();
+}
+// whether the tiles of level l are all whole (multiples of the 8-cell edge)
+bool whole_tiles(const std::vector<int> &dims, size_t l) {
+  return dims[3 * l] % 8 == 0 && dims[3 * l + 1] % 8 == 0 && dims[3 * l + 2] % 8 == 0;
 }
 
 // Validate the configuration; fills the level dimensions. Returns "" if ok.
@@ -359,8 +362,9 @@ void fd_flags(const sim_config *c, const std::vector<int> &dims, bool &fdg, bool
   for (int a = 0; a < 3; ++a) fdn[a] = fdg ? c->n[a] : cdims[a];
 }
 
+// cut_tiles: give the tile levels whose last tiles are cut their second x too
 SolveScratch carve_solve(Carver &cv, const sim_config *c, long long K, long long hparts,
-                         const std::vector<int> &dims) {
+                         const std::vector<int> &dims, bool cut_tiles) {
   SolveScratch q;
   const long long N = (long long)c->n[0] * c->n[1] * c->n[2];
   const size_t ts = c->precision == SIM_PREC_FP32MG ? sizeof(float) : sizeof(double);
@@ -379,7 +383,7 @@ SolveScratch carve_solve(Carver &cv, const sim_config *c, long long K, long long
     ++q.nlv;
   }
   for (size_t l = 0; 3 * l < dims.size() && l <= (size_t)SolveScratch::MAX_LEVELS; ++l)
-    if (tile_level(c, dims, l))
+    if (tile_level(c, dims, l) && (cut_tiles || whole_tiles(dims, l)))
       q.lvs[l] = cv.take(ts * (size_t)dims[3 * l] * dims[3 * l + 1] * dims[3 * l + 2]);
   q.Q = cv.arr<double>(3 * K);
   q.RF = cv.arr<double>(3 * K);
@@ -397,6 +401,18 @@ SolveScratch carve_solve(Carver &cv, const sim_config *c, long long K, long long
   q.FDX1 = fdx ? cv.arr<double>(N) : nullptr;
   q.FDX2 = fdx ? cv.arr<double>(N) : nullptr;
   return q;
+}
+
+// A level with cut tiles may run on the march kernels as well, so its second x
+// never costs a solve its place in the static scratch: where the scratch would
+// hold the solve only without them, those levels march.
+SolveScratch carve_solve(Carver &cv, const sim_config *c, long long K, long long hparts,
+                         const std::vector<int> &dims) {
+  Carver with(nullptr), without(nullptr);
+  carve_solve(with, c, K, 0, dims, true);
+  carve_solve(without, c, K, 0, dims, false);
+  const bool cut = with.off <= NOALLOC_SCRATCH_BYTES || without.off > NOALLOC_SCRATCH_BYTES;
+  return carve_solve(cv, c, K, hparts, dims, cut);
 }
 
 // Lay out every array; with base == nullptr only the size is computed.

@@ -115,8 +115,10 @@ template <typename T>
 hipError_t mg_prolong(const Geo &gf, T *xf, const Geo &gc, const T *xc, hipStream_t s);
 // tile levels: the descent of a level (pre sweeps from x = 0, x written, the
 // coarse right-hand side bc) and its ascent (xout = xin + P xc, then post
-// sweeps) in one launch each, for 8^3-divisible grids with gc = g / 2 and
-// 1 or 2 pre / post sweeps (tile_level_fits)
+// sweeps) in one launch each, for grids that the 8^3 tiles take
+// (tile_edges_fit) with gc = g / 2 and 1 or 2 pre / post sweeps
+// (tile_level_fits)
+bool tile_edges_fit(int n0, int n1, int n2);
 bool tile_level_fits(const Geo &g, const Geo &gc, int pre, int post);
 template <typename T, typename TB>
 hipError_t mg_tile_down(const Geo &g, T *x, const TB *b, const Geo &gc, T *bc, int pre, hipStream_t s);

@@ -370,9 +370,8 @@ __host__ __device__ constexpr int tile_threads(int R) { return 2 * R * R; }
 struct TileAxes {
   int o[3], n[3], bc[3];
   __device__ __forceinline__ bool inside(int a, int u) const { return (unsigned)u < (unsigned)n[a] || !bc[a]; }
-  // the grid coordinate of an unwrapped u in [-n, 2n) (a halo is at most n
-  // cells: n is a multiple of 8 on the fine grid and of 4 on the coarse one);
-  // inside a wall box u is its own
+  // the grid coordinate of an unwrapped u in [-n, 2n) (tile_edges_fit); inside
+  // a wall box u is its own
   __device__ __forceinline__ int wrap(int a, int u) const {
     return u + (u < 0 ? n[a] : 0) - (u >= n[a] ? n[a] : 0);
   }
@@ -385,7 +384,7 @@ struct TileAxes {
 // grid gc, whose origin is half the fine one)
 __device__ __forceinline__ TileAxes tile_axes(const Geo &g, int scale) {
   TileAxes t;
-  const int t1 = g.n1 / TL_TS, t2 = g.n2 / TL_TS, b = blockIdx.x;
+  const int t1 = (g.n1 + TL_TS - 1) / TL_TS, t2 = (g.n2 + TL_TS - 1) / TL_TS, b = blockIdx.x;
   const int tile[3] = {b / (t1 * t2), (b / t2) % t1, b % t2};
   t.n[0] = g.n0 / scale; t.n[1] = g.n1 / scale; t.n[2] = g.n2 / scale;
   t.bc[0] = g.bc0; t.bc[1] = g.bc1; t.bc[2] = g.bc2;
@@ -407,7 +406,7 @@ struct TileRow {
   int q;               // LDS slot of its first entry
   int nn01;            // neighbours that axes 0 and 1 leave
   bool live;           // the row lies in the grid
-  bool tile;           // the row is one of the tile's own
+  bool tile;           // its tile cells (two entries per colour) are the tile's own
   long long off[2];
   T inv[2][4];  // 1 / neighbours per colour and entry, 0 outside the grid
 
@@ -431,7 +430,8 @@ __device__ __forceinline__ TileRow<T, R> tile_row(const Geo &g, const TileAxes &
   w.q = TL_ROW * row + 4 * w.h;
   const int u0 = ax.o[0] - H + w.r0, u1 = ax.o[1] - H + w.r1;
   w.live = ax.inside(0, u0) && ax.inside(1, u1);
-  w.tile = w.r0 >= H && w.r0 < H + TL_TS && w.r1 >= H && w.r1 < H + TL_TS;
+  w.tile = w.r0 >= H && w.r0 < H + TL_TS && w.r1 >= H && w.r1 < H + TL_TS && u0 < ax.n[0] && u1 < ax.n[1] &&
+           ax.o[2] + 4 * w.h < ax.n[2];
   w.nn01 = 6 - ax.walls(0, u0) - ax.walls(1, u1);
   // outside a wall box (nothing used there) the first row, the first pair
   const long long line = w.live ? ((long long)ax.wrap(0, u0) * g.n1 + ax.wrap(1, u1)) * g.hn2 : 0;
@@ -442,7 +442,7 @@ __device__ __forceinline__ TileRow<T, R> tile_row(const Geo &g, const TileAxes &
     w.off[z] = line + (ax.inside(2, 2 * m) ? mw : 0);
   }
   const T i0 = w.live ? inv_nn<T>(w.nn01) : T(0);
-  const bool edge = ax.bc[2] && (ax.o[2] == 0 || ax.o[2] + TL_TS == ax.n[2]);
+  const bool edge = ax.bc[2] && (ax.o[2] == 0 || ax.o[2] + TL_TS + TL_H2 >= ax.n[2]);
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -551,7 +551,8 @@ __global__ void __launch_bounds__(tile_threads(tile_edge(PRE))) k_tile_down(Geo 
     const int C2 = tid % TC, C1 = (tid / TC) % TC, C0 = tid / (TC * TC);
     const T *p = rs + (2 * C0 * TL_TS + 2 * C1) * TC + C2;
     const T a0 = p[0] + p[TL_TS * TC], a1 = p[TC] + p[TL_TS * TC + TC];
-    bc[sidx(gc, ax.o[0] / 2 + C0, ax.o[1] / 2 + C1, ax.o[2] / 2 + C2)] = (a0 + a1) * (T)0.125;
+    const int I = ax.o[0] / 2 + C0, J = ax.o[1] / 2 + C1, K = ax.o[2] / 2 + C2;
+    if (I < gc.n0 && J < gc.n1 && K < gc.n2) bc[sidx(gc, I, J, K)] = (a0 + a1) * (T)0.125;
   }
 }
 
@@ -642,11 +643,23 @@ __global__ void __launch_bounds__(tile_threads(tile_edge(POST))) k_tile_up(Geo g
   tile_store<T, R>(g, w, xx, xout);
 }
 
-bool tile_level_fits(const Geo &g, const Geo &gc, int pre, int post) {
-  return g.n0 % TL_TS == 0 && g.n1 % TL_TS == 0 && g.n2 % TL_TS == 0 && gc.n0 * 2 == g.n0 &&
-         gc.n1 * 2 == g.n1 && gc.n2 * 2 == g.n2 && (pre == 1 || pre == 2) && (post == 1 || post == 2);
+// Edges that the tiles take.  The last tiles of an axis may be cut (they store
+// only what lies in the grid); along axis 2 the cut must not split a pair of
+// entries, and neither the region nor its coarse block, which reach 12 and 7
+// cells past the origin of the last tile, may wrap past a second period: 10
+// cells are too few.
+bool tile_edges_fit(int n0, int n1, int n2) {
+  auto rows = [](int n) { return n % 2 == 0 && n >= 8 && n != 10; };
+  return rows(n0) && rows(n1) && n2 % 4 == 0 && n2 >= 8;
 }
-static unsigned tile_count(const Geo &g) { return (unsigned)((g.n0 / TL_TS) * (g.n1 / TL_TS) * (g.n2 / TL_TS)); }
+bool tile_level_fits(const Geo &g, const Geo &gc, int pre, int post) {
+  return tile_edges_fit(g.n0, g.n1, g.n2) && gc.n0 * 2 == g.n0 && gc.n1 * 2 == g.n1 && gc.n2 * 2 == g.n2 &&
+         (pre == 1 || pre == 2) && (post == 1 || post == 2);
+}
+static unsigned tile_count(const Geo &g) {
+  auto cut = [](int n) { return (unsigned)((n + TL_TS - 1) / TL_TS); };
+  return cut(g.n0) * cut(g.n1) * cut(g.n2);
+}
 
 template <typename T, typename TB>
 hipError_t mg_tile_down(const Geo &g, T *x, const TB *b, const Geo &gc, T *bc, int pre, hipStream_t s) {

@@ -78,3 +78,53 @@ def test_stencils_on_tiles_one_pair_wide(bc):
     u = sim.apply("helm_solve", r).cpu().numpy()
     assert rel(omac.helmholtz(g, cfg.nu, cfg.dt) @ u.ravel(), r.ravel()) < 2.0 * cfg.helm_rtol
     sim.close()
+
+
+@pytest.mark.parametrize("precision", [wl.PREC_FP64, wl.PREC_FP32MG])
+@pytest.mark.parametrize("sweeps", [(2, 1), (1, 1), (2, 2)])
+@pytest.mark.parametrize("n,coarsest,bc", [
+    ((20, 24, 28), 14, (wl.BC_PERIODIC,) * 3),                           # cut along axes 0 and 2
+    ((20, 24, 28), 14, MIXED),
+    ((36, 44, 24), 11, MIXED[::-1]),                                      # second level 18 x 22 x 12
+    ((36, 44, 24), 11, (wl.BC_PERIODIC,) * 3),
+    ((28, 16, 20), 14, (wl.BC_NOSLIP,) * 3),
+])
+def test_cut_tile_levels_give_the_same_bits(n, coarsest, bc, sweeps, precision):
+    # tile levels whose last tiles are cut give every cell the operations of
+    # the march kernels in the same order
+    from .gpu_helpers import mg_tile_cells
+    h = 1.0 / 28
+    cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=bc, nu=0.02, dt=0.005, precision=precision, mg_coarsest=coarsest,
+                    mg_pre=sweeps[0], mg_post=sweeps[1], mg_coarse_sweeps=0)
+    b = np.random.default_rng(n[0]).standard_normal(n)
+    b -= b.mean()
+    out = {}
+    for cells in (0, None):
+        with mg_tile_cells(cells):
+            sim = Sim(cfg, 1)
+        sim.probe("tile_down")
+        out[cells] = sim.apply("precond", b).cpu().numpy(), sim.probe_read("tile_down")[0]
+        sim.close()
+    assert out[0][1] == 0 and out[None][1] > 0
+    assert np.array_equal(out[0][0], out[None][0])
+
+
+@pytest.mark.parametrize("restart,tiles", [(29, False), (28, True)])
+def test_cut_tile_levels_leave_the_static_scratch_its_solves(restart, tiles):
+    # 60 x 64 x 64 in float32 with 29 basis vectors fills 63.6 of the 64 MiB of
+    # solve_schur_noalloc; a second x for its cut tile levels (1.05 MiB) would
+    # pass them, so those levels march.  With 28 there is room.
+    n, h, K = (60, 64, 64), 1.0 / 64, 300
+    cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=(wl.BC_PERIODIC,) * 3, nu=0.02, dt=0.005, lump_c=1.0,
+                    precision=wl.PREC_FP32MG, mg_coarsest=16, mg_coarse_sweeps=0, krylov_rtol=1e-6, krylov_restart=restart)
+    radius = 0.15
+    sim = Sim(cfg, K)
+    sim.set_bodies([wl.Body(center=np.array([0.4, 0.5, 0.5]), vel=np.zeros(3), omega=np.zeros(3), radius=radius, n_points=K)],
+                   wl.fibonacci_offsets(K, radius))
+    rp, rf = wl.random_schur_rhs(5, n, K)
+    p, f, _ = sim.solve_schur(rp, rf)
+    sim.probe("tile_down")
+    p1, f1, _ = sim.solve_schur_noalloc(rp, rf)
+    assert (sim.probe_read("tile_down")[0] > 0) == tiles
+    assert np.array_equal(p.cpu().numpy(), p1.cpu().numpy()) and np.array_equal(f.cpu().numpy(), f1.cpu().numpy())
+    sim.close()

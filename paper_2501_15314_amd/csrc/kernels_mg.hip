@@ -11,6 +11,8 @@
 // precision T (float or double) and on the right-hand-side type TB.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "internal.h"
 #include "march.h"
 
@@ -960,62 +962,125 @@ constexpr int FD_MAXN = 32;
 constexpr int FD_CELLS = 4096;
 constexpr int FD_THREADS = 1024;
 
+// Lines along an axis of n elements are read as pairs and kept an odd number of
+// pairs apart, which spreads them over the LDS banks; a grid of at most 4096
+// cells with at most 32 along an axis fills at most FD_PAD places in every
+// such layout (4 x 32 x 32 cells 6144, 3 x 32 x 32 cells 6144).
+constexpr int FD_PAD = 6144;
+__host__ __device__ constexpr int fd_line(int n) { return (((n + 1) / 2) | 1) * 2; }
+
+// Eigenvectors Q_a[m][t] (cell m, mode t) of the three axes rounded to T, by
+// rows along either index and with zeros past the end of a row, and the
+// eigenvalues.
+template <typename T>
+struct alignas(16) FdBasis {
+  T row[2][3][FD_MAXN * fd_line(FD_MAXN)];  // [0]: by mode, over cells; [1]: by cell, over modes
+  T lam[3][FD_MAXN];
+  __device__ __forceinline__ void load(const Geo &g, const double *p, int tid, int nthr) {
+    const int n[3] = {g.n0, g.n1, g.n2};
+    const int q1 = n[0] * n[0], q2 = q1 + n[1] * n[1], q3 = q2 + n[2] * n[2], all = q3 + n[0] + n[1] + n[2];
+    for (int t = tid; t < all; t += nthr) {
+      const T v = (T)p[t];
+      if (t < q3) {
+        const int a = t < q1 ? 0 : (t < q2 ? 1 : 2), na = a == 0 ? n[0] : (a == 1 ? n[1] : n[2]);
+        const int q = t - (a == 0 ? 0 : (a == 1 ? q1 : q2)), r = q / na, c = q - r * na, l = fd_line(na);
+        row[0][a][c * l + r] = v;
+        row[1][a][r * l + c] = v;
+        if (na & 1) {  // the last pair's second weight
+          if (r == na - 1) row[0][a][c * l + na] = T(0);
+          if (c == na - 1) row[1][a][r * l + na] = T(0);
+        }
+      } else {
+        const int q = t - q3, a = q < n[0] ? 0 : (q < n[0] + n[1] ? 1 : 2);
+        lam[a][q - (a == 0 ? 0 : (a == 1 ? n[0] : n[0] + n[1]))] = v;
+      }
+    }
+  }
+};
+// The places of one element in the three layouts with lines along axis a: of
+// the line and of the element.
+struct FdPlace {
+  int line[3], at[3], i[3];
+};
+__device__ __forceinline__ FdPlace fd_place(const Geo &g, int e) {
+  FdPlace p;
+  const int r = e / g.n2;
+  p.i[2] = e - r * g.n2;
+  p.i[0] = r / g.n1;
+  p.i[1] = r - p.i[0] * g.n1;
+  p.line[0] = (p.i[1] * g.n2 + p.i[2]) * fd_line(g.n0);
+  p.line[1] = (p.i[0] * g.n2 + p.i[2]) * fd_line(g.n1);
+  p.line[2] = (p.i[0] * g.n1 + p.i[1]) * fd_line(g.n2);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) p.at[a] = p.line[a] + p.i[a];
+  return p;
+}
+// The grid in A (elements at at[2]) to x, element tid + u nthr in v[u], by way
+// of A and B (whose places past a line's end hold finite values).  The six 1-D
+// transforms: forward along axes 2, 1, 0, the last divided by the sums of the
+// eigenvalues, backward along 0, 1, 2; each leaves its result in lines along
+// the axis of the next.
+template <typename T, int EPT>
+__device__ __forceinline__ void fd_solve(const Geo &g, const FdBasis<T> &fb, T *A, T *B, const FdPlace (&pl)[EPT], int nc,
+                                         int tid, int nthr, T (&v)[EPT]) {
+  typedef T Pair __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int p = 0; p < 6; ++p) {
+    const int a = p < 3 ? 2 - p : p - 3, w = p < 2 ? 1 - p : (p < 4 ? p - 2 : 2);  // axes of this pass and the next
+    const int na = a == 0 ? g.n0 : (a == 1 ? g.n1 : g.n2), np = (na + 1) / 2;
+    const T *rows = p < 3 ? fb.row[0][a] : fb.row[1][a];
+    const T *in = p & 1 ? B : A;
+    T *o = p & 1 ? A : B;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+      if (tid + u * nthr < nc) {
+        const int ia = a == 0 ? pl[u].i[0] : (a == 1 ? pl[u].i[1] : pl[u].i[2]);
+        const Pair *M = (const Pair *)(rows + ia * fd_line(na));
+        const Pair *x = (const Pair *)(in + (a == 0 ? pl[u].line[0] : (a == 1 ? pl[u].line[1] : pl[u].line[2])));
+        T acc = T(0);
+#pragma unroll 4
+        for (int t = 0; t < np; ++t) {
+          const Pair m = M[t], z = x[t];
+          acc = fma(m.x, z.x, acc);
+          acc = fma(m.y, z.y, acc);
+        }
+        if (p == 2) {
+          const T d = fb.lam[0][pl[u].i[0]] + fb.lam[1][pl[u].i[1]] + fb.lam[2][pl[u].i[2]];
+          acc = d > T(0) ? acc / d : T(0);
+        }
+        if (p < 5) o[w == 0 ? pl[u].at[0] : (w == 1 ? pl[u].at[1] : pl[u].at[2])] = acc;
+        v[u] = acc;
+      }
+    }
+    if (p < 5) __syncthreads();
+  }
+}
+
 template <typename T, typename TB>
 __global__ void __launch_bounds__(FD_THREADS) k_coarse_fd(Geo g, const TB *bin, T *xout, const double *fd) {
-  __shared__ T bufA[FD_CELLS];
-  __shared__ T bufB[FD_CELLS];
-  __shared__ T Q[3][FD_MAXN * FD_MAXN];
-  __shared__ T lam[3][FD_MAXN];
-  const int n[3] = {g.n0, g.n1, g.n2};
-  const int nc = g.n0 * g.n1 * g.n2;
-  const int tid = threadIdx.x;
-  {
-    const double *p = fd;
-    for (int a = 0; a < 3; ++a) {
-      for (int q = tid; q < n[a] * n[a]; q += FD_THREADS) Q[a][q] = (T)p[q];
-      p += n[a] * n[a];
-    }
-    for (int a = 0; a < 3; ++a) {
-      for (int q = tid; q < n[a]; q += FD_THREADS) lam[a][q] = (T)p[q];
-      p += n[a];
-    }
+  __shared__ __attribute__((aligned(16))) T bufA[FD_PAD];
+  __shared__ __attribute__((aligned(16))) T bufB[FD_PAD];
+  __shared__ FdBasis<T> basis;
+  constexpr int EPT = FD_CELLS / FD_THREADS;
+  const int nc = g.n0 * g.n1 * g.n2, tid = threadIdx.x;
+  FdPlace pl[EPT];
+  T v[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    pl[u] = fd_place(g, min(tid + u * FD_THREADS, nc - 1));
+    v[u] = (T)bin[sidx(g, pl[u].i[0], pl[u].i[1], pl[u].i[2])];
   }
-  for (int e = tid; e < nc; e += FD_THREADS) {
-    int k = e % g.n2, r = e / g.n2, j = r % g.n1, i = r / g.n1;
-    bufA[e] = (T)bin[sidx(g, i, j, k)];
-  }
+  basis.load(g, fd, tid, FD_THREADS);
+  for (int q = tid; q < FD_PAD; q += FD_THREADS) bufA[q] = bufB[q] = T(0);
   __syncthreads();
-  // one 1-D transform along axis a: out[.., m, ..] = sum_t M[t][m] in[.., t, ..]
-  // (forward, coefficients) or sum_t M[m][t] in[.., t, ..] (backward)
-  auto pass = [&](const T *in, T *out, int a, bool fwd) {
-    const int na = n[a];
-    const int stride = a == 2 ? 1 : (a == 1 ? g.n2 : g.n1 * g.n2);
-    const T *M = Q[a];
-    for (int e = tid; e < nc; e += FD_THREADS) {
-      const int ia = (e / stride) % na;
-      const int base = e - ia * stride;
-      T acc = T(0);
-      for (int t = 0; t < na; ++t) acc += (fwd ? M[t * na + ia] : M[ia * na + t]) * in[base + t * stride];
-      out[e] = acc;
-    }
-    __syncthreads();
-  };
-  pass(bufA, bufB, 2, true);
-  pass(bufB, bufA, 1, true);
-  pass(bufA, bufB, 0, true);
-  for (int e = tid; e < nc; e += FD_THREADS) {
-    int k = e % g.n2, r = e / g.n2, j = r % g.n1, i = r / g.n1;
-    T d = lam[0][i] + lam[1][j] + lam[2][k];
-    bufB[e] = d > T(0) ? bufB[e] / d : T(0);
-  }
+#pragma unroll
+  for (int u = 0; u < EPT; ++u)
+    if (tid + u * FD_THREADS < nc) bufA[pl[u].at[2]] = v[u];
   __syncthreads();
-  pass(bufB, bufA, 0, false);
-  pass(bufA, bufB, 1, false);
-  pass(bufB, bufA, 2, false);
-  for (int e = tid; e < nc; e += FD_THREADS) {
-    int k = e % g.n2, r = e / g.n2, j = r % g.n1, i = r / g.n1;
-    xout[sidx(g, i, j, k)] = bufA[e];
-  }
+  fd_solve<T, EPT>(g, basis, bufA, bufB, pl, nc, tid, FD_THREADS, v);
+#pragma unroll
+  for (int u = 0; u < EPT; ++u)
+    if (tid + u * FD_THREADS < nc) xout[sidx(g, pl[u].i[0], pl[u].i[1], pl[u].i[2])] = v[u];
 }
 
 template <typename T, typename TB>
@@ -1034,302 +1099,211 @@ hipError_t mg_coarse_fd(const Geo &gc, const TB *b, T *x, const double *fd, hipS
 // residual averaged over the eight children, the exact coarse solve (constant
 // mode dropped), trilinear prolongation, `post` black-red pairs.  One launch
 // replaces the eight of the two levels, which are bound by latency.
+//
+// Layout as in the tile kernels: a thread owns four entries of a row in both
+// colours (rows of n2 / 2 entries per colour, in quads), with right-hand side,
+// values and reciprocal neighbour counts in registers; a half sweep reads four
+// vectors and one value from LDS.  A neighbour past a wall is a row of zeros.
+//
+// Bounded by the latency of its phases on one compute unit: 7.1 us inside the
+// kernel in float32 on 16^3 cells (2.0 until the right-hand side is there, 0.25
+// a half sweep, 0.7 residual, 0.4 restriction, 1.6 coarse solve, 0.8
+// prolongation), and the launch.  Before, each cell went by 16-bit index
+// tables read from memory and its six neighbours one by one, and the coarse
+// lines met in the same LDS banks: 13.2 -> 8.2 us, in float64 14.0 -> 10.8;
+// the coarse solve by itself on 10 x 12 x 14 cells in float64 14.6 -> 9.1.
 constexpr int SUB_FINE = 4096;
 constexpr int SUB_COARSE = SUB_FINE / 8;
-constexpr int SUB_ZERO = SUB_FINE + SUB_COARSE;  // an LDS slot that always holds 0
-constexpr int SUB_SLOTS = SUB_FINE / 2 / COARSE_THREADS;  // fine cells of one colour per thread
+constexpr int SUB_PAD = 2 * SUB_COARSE;  // lines of 1 or 3 elements take twice their places
+constexpr int SUB_THREADS = 1024;
+// per colour: rows of quads (n2 / 2 is even, so a row of two entries fills half
+// of its quad and the rows take at most twice the colour's cells) and zeros
+constexpr int SUB_ROWS = SUB_FINE + 4;
 
-// A fine cell of the subcycle with everything its relaxation and residual
-// need that does not change during the kernel: its LDS index q, its
-// neighbour count nn (meta = q | nn << 16, -1 for an absent slot) and the LDS
-// indices of its neighbours in the order -x, +x, -y, +y, -z, +z, two per word
-// (a missing neighbour past a wall points at the zero slot, so it adds 0).
-// Built once per thread, so a half sweep costs six LDS reads and a few adds
-// per cell instead of the index decoding and boundary logic of lds_nb, which
-// bound the single workgroup's four SIMDs.
-struct SubCell {
-  int meta;
-  unsigned nb[3];
-};
-__device__ __forceinline__ SubCell sub_cell(const LvlDim &f, int bc0, int bc1, int bc2, int color, int ec) {
-  SubCell r;
-  const int hn2 = f.n2 >> 1;
-  r.meta = -1;
-  r.nb[0] = r.nb[1] = r.nb[2] = 0;
-  if (ec >= f.n0 * f.n1 * hn2) return r;
-  int kh, rr, i, j;
-  if (f.pow2) {
-    kh = ec & (hn2 - 1);
-    rr = ec >> (f.l2 - 1);
-    j = rr & (f.n1 - 1);
-    i = rr >> f.l1;
-  } else {
-    kh = ec % hn2;
-    rr = ec / hn2;
-    j = rr % f.n1;
-    i = rr / f.n1;
-  }
-  const int k = 2 * kh + ((i + j + color) & 1);
-  auto at = [&](int ii, int jj, int kk) { return f.off + (ii * f.n1 + jj) * f.n2 + kk; };
-  const int t[6] = {nbr(i, -1, f.n0, bc0), nbr(i, 1, f.n0, bc0), nbr(j, -1, f.n1, bc1),
-                    nbr(j, 1, f.n1, bc1),  nbr(k, -1, f.n2, bc2), nbr(k, 1, f.n2, bc2)};
-  int id[6], nn = 0;
+template <typename T, typename TB, int NT>
+__global__ void __launch_bounds__(NT) k_subcycle(Geo gf, Geo gc, const TB *bin, T *xout, const double *fd,
+                                                          int pre, int post) {
+  __shared__ __attribute__((aligned(16))) T sx[2][SUB_ROWS];
+  __shared__ __attribute__((aligned(16))) T fa[SUB_PAD], fb[SUB_PAD];
+  __shared__ FdBasis<T> basis;
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int quads = (gf.hn2 + 3) / 4, RS = 4 * quads, rows = gf.n0 * gf.n1, zero = rows * RS;
+  const int nc = gc.n0 * gc.n1 * gc.n2;
+  // the thread's quad: entries m0 .. m0 + cnt - 1 of row (i, j)
+  const int row = tid / quads, m0 = 4 * (tid - row * quads), i = row / gf.n1, j = row - i * gf.n1;
+  const bool live = row < rows;
+  const int cnt = min(gf.hn2 - m0, 4);  // 2 or 4
+  const int q = row * RS + m0;
+  const long long g0 = live ? (long long)row * gf.hn2 + m0 : 0;
+  const long long off[2] = {g0, cnt == 4 ? g0 + 2 : g0};
+  Quad<T> bb[2], xx[2], inv[2];
 #pragma unroll
-  for (int d = 0; d < 6; ++d) {
-    const int a = d >> 1;
-    id[d] = t[d] < 0 ? SUB_ZERO : (a == 0 ? at(t[d], j, k) : (a == 1 ? at(i, t[d], k) : at(i, j, t[d])));
-    nn += t[d] >= 0;
-  }
+  for (int c = 0; c < 2; ++c) bb[c] = tile_load<T>(bin + c * gf.half, off);
+  basis.load(gc, fd, tid, nthr);
+  for (int e = tid; e < SUB_PAD; e += nthr) fa[e] = fb[e] = T(0);
+  // LDS offsets of the neighbouring quads and of the entries beside the quad
+  auto line = [&](int a, int b) { return a < 0 || b < 0 ? zero : (a * gf.n1 + b) * RS + m0; };
+  const int im = mwrap(i - 1, gf.n0, gf.bc0), ip = mwrap(i + 1, gf.n0, gf.bc0);
+  const int jm = mwrap(j - 1, gf.n1, gf.bc1), jp = mwrap(j + 1, gf.n1, gf.bc1);
+  const int ml = mwrap(m0 - 1, gf.hn2, gf.bc2), mr = mwrap(m0 + cnt, gf.hn2, gf.bc2);
+  const int qxm = line(im, j), qxp = line(ip, j), qym = line(i, jm), qyp = line(i, jp);
+  const int ql = ml < 0 ? zero : row * RS + ml, qr = mr < 0 ? zero : row * RS + mr;
+  const int nn01 = 2 + (im >= 0) + (ip >= 0) + (jm >= 0) + (jp >= 0), par = (i + j) & 1;
+  auto nn = [&](int c, int e) {  // neighbours of entry e of colour c
+    const int k = 2 * (m0 + e) + ((c + par) & 1);
+    return gf.bc2 ? nn01 - (k == 0) - (k == gf.n2 - 1) : nn01;
+  };
 #pragma unroll
-  for (int w = 0; w < 3; ++w) r.nb[w] = (unsigned)id[2 * w] | ((unsigned)id[2 * w + 1] << 16);
-  r.meta = at(i, j, k) | (nn << 16);
-  return r;
-}
-template <typename T>
-__device__ __forceinline__ T sub_nbsum(const T *x, const SubCell &c) {
-  T s = T(0);
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
-  for (int w = 0; w < 3; ++w) {
-    s += x[c.nb[w] & 0xffffu];
-    s += x[c.nb[w] >> 16];
-  }
-  return s;
-}
-
-// The subcycle's per-thread tables, built once per grid (k_subcycle_tables)
-// so that a launch reads them instead of forming them: int4 slot s of thread
-// tid at tab[s * COARSE_THREADS + tid]; slots 0-3 the SubCell of cell (cc,
-// u) = (s >> 1, s & 1), slots 4-7 the prolongation of natural-order fine
-// cell e = tid + (s - 4) COARSE_THREADS: the coarse offsets of the parent and
-// of its neighbour on the child's side along each axis, two 16-bit offsets
-// per word (axis 0 in x, 1 in y, 2 in z; w = 1 for a cell of the grid).
-constexpr int SUB_TAB_SLOTS = 8;
-int subcycle_table_ints() { return 4 * SUB_TAB_SLOTS * COARSE_THREADS; }
-__device__ __forceinline__ int4 sub_prolong_entry(const LvlDim &f, const LvlDim &c, int bc0, int bc1, int bc2, int e) {
-  int4 r = make_int4(0, 0, 0, 0);
-  if (e >= f.n0 * f.n1 * f.n2) return r;
-  int i, j, k;
-  lds_decode(f, e, i, j, k);
-  const int I0 = i >> 1, J0 = j >> 1, K0 = k >> 1;
-  const int I1 = coarse_partner(I0, i & 1, c.n0, bc0);
-  const int J1 = coarse_partner(J0, j & 1, c.n1, bc1);
-  const int K1 = coarse_partner(K0, k & 1, c.n2, bc2);
-  const int s0 = c.n1 * c.n2, s1 = c.n2;
-  r.x = (I0 * s0) | ((I1 * s0) << 16);
-  r.y = (J0 * s1) | ((J1 * s1) << 16);
-  r.z = K0 | (K1 << 16);
-  r.w = 1;
-  return r;
-}
-__device__ __forceinline__ LvlDim sub_dims(const Geo &g, int off) {
-  LvlDim d;
-  d.n0 = g.n0; d.n1 = g.n1; d.n2 = g.n2; d.off = off;
-  d.pow2 = !(g.n0 & (g.n0 - 1)) && !(g.n1 & (g.n1 - 1)) && !(g.n2 & (g.n2 - 1));
-  d.l1 = 31 - __clz(g.n1);
-  d.l2 = 31 - __clz(g.n2);
-  return d;
-}
-__global__ void __launch_bounds__(COARSE_THREADS) k_subcycle_tables(Geo gf, Geo gc, int4 *tab) {
-  const int tid = threadIdx.x, nf = gf.n0 * gf.n1 * gf.n2;
-  const LvlDim f = sub_dims(gf, 0), c = sub_dims(gc, nf);
-#pragma unroll
-  for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-    for (int u = 0; u < SUB_SLOTS; ++u) {
-      const SubCell sc = sub_cell(f, gf.bc0, gf.bc1, gf.bc2, cc, tid + u * COARSE_THREADS);
-      tab[(cc * SUB_SLOTS + u) * COARSE_THREADS + tid] = make_int4(sc.meta, (int)sc.nb[0], (int)sc.nb[1], (int)sc.nb[2]);
-    }
-#pragma unroll
-  for (int r = 0; r < SUB_FINE / COARSE_THREADS; ++r)
-    tab[(2 * SUB_SLOTS + r) * COARSE_THREADS + tid] =
-        sub_prolong_entry(f, c, gf.bc0, gf.bc1, gf.bc2, tid + r * COARSE_THREADS);
-}
-
-template <typename T, typename TB>
-__global__ void __launch_bounds__(COARSE_THREADS) k_subcycle(Geo gf, Geo gc, const TB *bin, T *xout,
-                                                             const double *fd, const int4 *tab, int pre, int post) {
-  __shared__ T sx[SUB_FINE + SUB_COARSE + 1];
-  __shared__ T sb[SUB_FINE + SUB_COARSE];
-  __shared__ T rf[SUB_FINE];  // fine residuals for the restriction
-  __shared__ T fa[SUB_COARSE], fb[SUB_COARSE];
-  __shared__ T Q[3][FD_MAXN * FD_MAXN];
-  __shared__ T lam[3][FD_MAXN];
-  const int tid = threadIdx.x;
-  const int nf = gf.n0 * gf.n1 * gf.n2, nc = gc.n0 * gc.n1 * gc.n2;
-  const LvlDim c = sub_dims(gc, nf);
-  // the right-hand side of the thread's cells and its tables, every load
-  // issued before any is used; slot (cc, u) is the colour-cc cell with
-  // split-layout index cc half + tid + u COARSE_THREADS, so the right-hand
-  // side is read and the result written with coalesced accesses and no
-  // index arithmetic
-  TB bl[2][SUB_SLOTS];
-  SubCell cell[2][SUB_SLOTS];
-  int4 pe[SUB_FINE / COARSE_THREADS];
-#pragma unroll
-  for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-    for (int u = 0; u < SUB_SLOTS; ++u) {
-      const long long ec = tid + u * COARSE_THREADS;
-      bl[cc][u] = ec < gf.half ? bin[(long long)cc * gf.half + ec] : TB(0);
-      const int4 t = tab[(cc * SUB_SLOTS + u) * COARSE_THREADS + tid];
-      cell[cc][u].meta = t.x;
-      cell[cc][u].nb[0] = (unsigned)t.y;
-      cell[cc][u].nb[1] = (unsigned)t.z;
-      cell[cc][u].nb[2] = (unsigned)t.w;
-    }
-#pragma unroll
-  for (int r = 0; r < SUB_FINE / COARSE_THREADS; ++r) pe[r] = tab[(2 * SUB_SLOTS + r) * COARSE_THREADS + tid];
-  {
-    const int n[3] = {gc.n0, gc.n1, gc.n2};
-    const double *p = fd;
-    for (int a = 0; a < 3; ++a) {
-      for (int q = tid; q < n[a] * n[a]; q += COARSE_THREADS) Q[a][q] = (T)p[q];
-      p += n[a] * n[a];
-    }
-    for (int a = 0; a < 3; ++a) {
-      for (int q = tid; q < n[a]; q += COARSE_THREADS) lam[a][q] = (T)p[q];
-      p += n[a];
-    }
-  }
-  if (tid == 0) sx[SUB_ZERO] = T(0);
-#pragma unroll
-  for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-    for (int u = 0; u < SUB_SLOTS; ++u)
-      if (cell[cc][u].meta >= 0) {
-        const int q = cell[cc][u].meta & 0xffff;
-        sb[q] = (T)bl[cc][u];
-        sx[q] = T(0);
-      }
-  __syncthreads();
+    for (int e = 0; e < 4; ++e) inv[c].v[e] = live && e < cnt ? inv_nn<T>(nn(c, e)) : T(0);
   const T h2 = (T)(gf.h * gf.h), ih2 = T(1) / h2;
-  // one half sweep over colour cc (the same operations as lds_smooth)
-  auto smooth = [&](int cc) {
-#pragma unroll
-    for (int u = 0; u < SUB_SLOTS; ++u) {
-      const SubCell &cl = cell[cc][u];
-      if (cl.meta >= 0) {
-        const int q = cl.meta & 0xffff, nn = cl.meta >> 16;
-        const T sum = sub_nbsum(sx, cl);
-        sx[q] = (h2 * sb[q] + sum) * inv_nn<T>(nn);
-      }
-    }
+  auto put = [&](int c, const Quad<T> &v) {
+    if (live) *(Quad<T> *)(sx[c] + q) = v;
   };
-  for (int q = 0; q < pre; ++q) {
-    smooth(0);
+  auto sums = [&](int c, const Quad<T> &x) {
+    const T *o = sx[1 - c];
+    const Quad<T> xm = *(const Quad<T> *)(o + qxm), xp = *(const Quad<T> *)(o + qxp);
+    const Quad<T> ym = *(const Quad<T> *)(o + qym), yp = *(const Quad<T> *)(o + qyp);
+    const bool s = (c + par) & 1;
+    const T far = o[s ? qr : ql];
+    const T x2 = cnt == 2 ? far : x.v[2];  // entry 1 of a half quad meets the row's end
+    const T z0 = s ? x.v[0] : far, z1 = s ? x.v[1] : x.v[0], z2 = s ? x2 : x.v[1], z3 = s ? x.v[3] : x.v[2],
+            z4 = s ? far : x.v[3];
+    Quad<T> r;
+    r.v[0] = xm.v[0] + xp.v[0] + ym.v[0] + yp.v[0] + z0 + z1;
+    r.v[1] = xm.v[1] + xp.v[1] + ym.v[1] + yp.v[1] + z1 + z2;
+    r.v[2] = xm.v[2] + xp.v[2] + ym.v[2] + yp.v[2] + z2 + z3;
+    r.v[3] = xm.v[3] + xp.v[3] + ym.v[3] + yp.v[3] + z3 + z4;
+    return r;
+  };
+  // one half sweep over colour c (the operations of lds_smooth)
+  auto smooth = [&](int c) {
+    if (live) {
+      const Quad<T> sum = sums(c, xx[1 - c]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xx[c].v[e] = fma(h2, bb[c].v[e], sum.v[e]) * inv[c].v[e];
+      put(c, xx[c]);
+    }
     __syncthreads();
+  };
+  // the first half sweep from x = 0
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    xx[0].v[e] = pre > 0 ? mul_rn(mul_rn(h2, bb[0].v[e]), inv[0].v[e]) : T(0);
+    xx[1].v[e] = T(0);
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    put(c, xx[c]);
+    if (tid < 4) sx[c][zero + tid] = T(0);
+  }
+  __syncthreads();
+  for (int p = 0; p < pre; ++p) {
+    if (p) smooth(0);
     smooth(1);
-    __syncthreads();
   }
-  // residual of every fine cell (as lds_resid), then the average over the
-  // eight children of each coarse cell
+  // residual of every fine cell (as lds_resid), left in place of x, then the
+  // average over the eight children of each coarse cell
+  {
+    Quad<T> r[2];
+    if (live) {
 #pragma unroll
-  for (int cc = 0; cc < 2; ++cc)
+      for (int c = 0; c < 2; ++c) {
+        const Quad<T> sum = sums(c, xx[1 - c]);
 #pragma unroll
-    for (int u = 0; u < SUB_SLOTS; ++u) {
-      const SubCell &cl = cell[cc][u];
-      if (cl.meta >= 0) {
-        const int q = cl.meta & 0xffff, nn = cl.meta >> 16;
-        const T sum = sub_nbsum(sx, cl);
-        rf[q] = sb[q] - ((T)nn * sx[q] - sum) * ih2;
+        for (int e = 0; e < 4; ++e) r[c].v[e] = pc_resid(bb[c].v[e], xx[c].v[e], sum.v[e], nn(c, e), ih2);
       }
     }
-  __syncthreads();
-  for (int e = tid; e < nc; e += COARSE_THREADS) {
-    int i, j, k;
-    lds_decode(c, e, i, j, k);
-    T acc = T(0);
-    for (int q = 0; q < 8; ++q)
-      acc += rf[((2 * i + (q >> 2)) * gf.n1 + 2 * j + ((q >> 1) & 1)) * gf.n2 + 2 * k + (q & 1)];
-    fa[e] = acc * (T)0.125;
-  }
-  __syncthreads();
-  // exact coarse solve: the six 1-D eigenbasis transforms and the division;
-  // thread tid owns coarse element tid (nc <= SUB_COARSE <= COARSE_THREADS),
-  // whose index along each axis and line base are formed once
-  static_assert(SUB_COARSE <= COARSE_THREADS, "one coarse element per thread");
-  const int n[3] = {gc.n0, gc.n1, gc.n2};
-  const int cstride[3] = {gc.n1 * gc.n2, gc.n2, 1};
-  int cia[3], cbase[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    cia[a] = (tid / cstride[a]) % n[a];
-    cbase[a] = tid - cia[a] * cstride[a];
-  }
-  auto pass = [&](const T *in, T *out, int a, bool fwd) {
-    if (tid < nc) {
-      const int na = n[a], stride = cstride[a], ia = cia[a], base = cbase[a];
-      const T *M = Q[a];
-      T acc = T(0);
-#pragma unroll 8
-      for (int t = 0; t < na; ++t) acc += (fwd ? M[t * na + ia] : M[ia * na + t]) * in[base + t * stride];
-      out[tid] = acc;
-    }
     __syncthreads();
-  };
-  pass(fa, fb, 2, true);
-  pass(fb, fa, 1, true);
-  pass(fa, fb, 0, true);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) put(c, r[c]);
+  }
+  __syncthreads();
+  const FdPlace pl[1] = {fd_place(gc, min(tid, nc - 1))};
   if (tid < nc) {
-    T d = lam[0][cia[0]] + lam[1][cia[1]] + lam[2][cia[2]];
-    fb[tid] = d > T(0) ? fb[tid] / d : T(0);
-  }
-  __syncthreads();
-  pass(fb, fa, 0, false);
-  pass(fa, fb, 1, false);
-  pass(fb, sx + nf, 2, false);  // the coarse solution, after the fine cells
-  // trilinear prolongation of the coarse solution onto every fine cell (the
-  // coarse offsets of each cell's parents from the tables)
+    T acc = T(0);
 #pragma unroll
-  for (int r = 0; r < SUB_FINE / COARSE_THREADS; ++r) {
-    const int e = tid + r * COARSE_THREADS;
-    if (!pe[r].w) continue;
-    const int I0 = pe[r].x & 0xffff, I1 = pe[r].x >> 16, J0 = pe[r].y & 0xffff, J1 = pe[r].y >> 16;
-    const int K0 = pe[r].z & 0xffff, K1 = pe[r].z >> 16;
-    const T *xc = sx + nf;
-    auto X = [&](int a, int b, int cc) { return xc[a + b + cc]; };
-    const T v0 = (T)0.75 * X(I0, J0, K0) + (T)0.25 * X(I1, J0, K0);
-    const T v1 = (T)0.75 * X(I0, J1, K0) + (T)0.25 * X(I1, J1, K0);
-    const T v2 = (T)0.75 * X(I0, J0, K1) + (T)0.25 * X(I1, J0, K1);
-    const T v3 = (T)0.75 * X(I0, J1, K1) + (T)0.25 * X(I1, J1, K1);
-    const T w0 = (T)0.75 * v0 + (T)0.25 * v1;
-    const T w1 = (T)0.75 * v2 + (T)0.25 * v3;
-    sx[e] += (T)0.75 * w0 + (T)0.25 * w1;
+    for (int z = 0; z < 8; ++z) {
+      const int di = z >> 2, dj = (z >> 1) & 1, dk = z & 1;
+      acc += sx[(di + dj + dk) & 1][((2 * pl[0].i[0] + di) * gf.n1 + 2 * pl[0].i[1] + dj) * RS + pl[0].i[2]];
+    }
+    fa[pl[0].at[2]] = acc * (T)0.125;
   }
   __syncthreads();
-  for (int q = 0; q < post; ++q) {
+  // the exact coarse solution, in natural order into fa
+  T xc[1];
+  fd_solve<T, 1>(gc, basis, fa, fb, pl, nc, tid, nthr, xc);
+  if (tid < nc) fa[tid] = xc[0];
+  __syncthreads();
+  // trilinear prolongation onto the red cells (axis 0, then 1, then 2), and
+  // onto the black ones if no sweep follows, which would relax them first
+  {
+    auto partner = [](int C, int odd, int n, int bc) {
+      const int o = C + (odd ? 1 : -1);
+      return o >= 0 && o < n ? o : (bc ? C : (o < 0 ? o + n : o - n));
+    };
+    const int I0 = live ? i >> 1 : 0, J0 = live ? j >> 1 : 0;
+    const int I1 = partner(I0, i & 1, gc.n0, gc.bc0), J1 = partner(J0, j & 1, gc.n1, gc.bc1);
+    const T *p00 = fa + (I0 * gc.n1 + J0) * gc.n2, *p10 = fa + (I1 * gc.n1 + J0) * gc.n2;
+    const T *p01 = fa + (I0 * gc.n1 + J1) * gc.n2, *p11 = fa + (I1 * gc.n1 + J1) * gc.n2;
+    auto prolong = [&](int c) {
+      const bool s = (c + par) & 1;
+      // entry e: parent K = m0 + e, its neighbour K - 1 (s = 0) or K + 1
+      T w[5];
+#pragma unroll
+      for (int t = 0; t < 5; ++t) {
+        const int k = m0 + t - (s ? 0 : 1);
+        const int kw = k < 0 ? (gc.bc2 ? 0 : gc.n2 - 1) : (k < gc.n2 ? k : (gc.bc2 || k > gc.n2 ? gc.n2 - 1 : 0));
+        w[t] = blend34(blend34(p00[kw], p10[kw]), blend34(p01[kw], p11[kw]));
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const T near = s ? w[e] : w[e + 1], far = s ? w[e + 1] : w[e];
+        xx[c].v[e] += blend34(near, far);
+      }
+      put(c, xx[c]);
+    };
+    prolong(0);
+    if (post == 0) prolong(1);
+  }
+  __syncthreads();
+  for (int p = 0; p < post; ++p) {
     smooth(1);
-    __syncthreads();
     smooth(0);
-    __syncthreads();
   }
+  if (live) {
 #pragma unroll
-  for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-    for (int u = 0; u < SUB_SLOTS; ++u)
-      if (cell[cc][u].meta >= 0)
-        xout[(long long)cc * gf.half + tid + u * COARSE_THREADS] = sx[cell[cc][u].meta & 0xffff];
+    for (int c = 0; c < 2; ++c) {
+      T *o = xout + c * gf.half;
+      st2<T>(o + off[0], 0, xx[c].v[0], xx[c].v[1]);
+      if (cnt == 4) st2<T>(o + off[1], 0, xx[c].v[2], xx[c].v[3]);
+    }
+  }
 }
 
 bool subcycle_fits(const Geo &gf, const Geo &gc) {
   const long long nf = (long long)gf.n0 * gf.n1 * gf.n2;
-  return nf <= SUB_FINE && gc.n0 <= FD_MAXN && gc.n1 <= FD_MAXN && gc.n2 <= FD_MAXN && gc.n0 * 2 == gf.n0 &&
+  return nf <= SUB_FINE && gf.n2 % 4 == 0 && gc.n0 <= FD_MAXN && gc.n1 <= FD_MAXN && gc.n2 <= FD_MAXN && gc.n0 * 2 == gf.n0 &&
          gc.n1 * 2 == gf.n1 && gc.n2 * 2 == gf.n2;
 }
 
 template <typename T, typename TB>
-hipError_t mg_subcycle(const Geo &gf, const Geo &gc, const TB *b, T *x, const double *fd, const int *tab, int pre,
-                       int post, hipStream_t s) {
-  if (!subcycle_fits(gf, gc) || !tab) return hipErrorInvalidValue;
+hipError_t mg_subcycle(const Geo &gf, const Geo &gc, const TB *b, T *x, const double *fd, int pre, int post,
+                       hipStream_t s) {
+  if (!subcycle_fits(gf, gc)) return hipErrorInvalidValue;
+  // a thread per quad of a row, and per coarse cell
+  const int need = std::max(gf.n0 * gf.n1 * ((gf.hn2 + 3) / 4), gc.n0 * gc.n1 * gc.n2), nthr = (need + 63) / 64 * 64;
+  if (nthr > SUB_THREADS) return hipErrorInvalidValue;
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
-  hipExtLaunchKernelGGL((k_subcycle<T, TB>), dim3(1), dim3(COARSE_THREADS), 0, s, e0, e1, 0, gf, gc, b, x, fd,
-                        (const int4 *)tab, pre, post);
-  return hipGetLastError();
-}
-hipError_t mg_subcycle_tables(const Geo &gf, const Geo &gc, int *tab, hipStream_t s) {
-  if (!subcycle_fits(gf, gc) || !tab) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_subcycle_tables, dim3(1), dim3(COARSE_THREADS), 0, s, gf, gc, (int4 *)tab);
+  // half the threads leave the registers that the float64 kernel wants
+  if (nthr <= SUB_THREADS / 2)
+    hipExtLaunchKernelGGL((k_subcycle<T, TB, SUB_THREADS / 2>), dim3(1), dim3(nthr), 0, s, e0, e1, 0, gf, gc, b, x, fd,
+                          pre, post);
+  else
+    hipExtLaunchKernelGGL((k_subcycle<T, TB, SUB_THREADS>), dim3(1), dim3(nthr), 0, s, e0, e1, 0, gf, gc, b, x, fd, pre,
+                          post);
   return hipGetLastError();
 }
 
@@ -1391,8 +1365,8 @@ void coarse_fd_build(const int n[3], const int bc[3], double h, double *out) {
                                          hipStream_t);                                                 \
   template hipError_t mg_coarse<T, TB>(const Geo &, const TB *, T *, int, int, hipStream_t);                   \
   template hipError_t mg_coarse_fd<T, TB>(const Geo &, const TB *, T *, const double *, hipStream_t);   \
-  template hipError_t mg_subcycle<T, TB>(const Geo &, const Geo &, const TB *, T *, const double *, const int *, \
-                                         int, int, hipStream_t);                                               \
+  template hipError_t mg_subcycle<T, TB>(const Geo &, const Geo &, const TB *, T *, const double *, int, int, \
+                                         hipStream_t);                                               \
   template hipError_t mg_tile_down<T, TB>(const Geo &, T *, const TB *, const Geo &, T *, int, hipStream_t);   \
   template hipError_t mg_tile_up<T, TB>(const Geo &, const T *, T *, const TB *, const Geo &, const T *, int, \
                                         hipStream_t);

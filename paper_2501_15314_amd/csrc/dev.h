@@ -109,8 +109,13 @@ __device__ __forceinline__ int cell_nnb(const Geo &g, int i, int j, int k) {
 //   pc_resid:  residual b - (nn x - sum of neighbours) / h^2;
 //   blend34:   3/4 near + 1/4 far, one axis of cell-centred trilinear
 //              interpolation.
-__device__ __forceinline__ float mul_rn(float a, float b) { return __fmul_rn(a, b); }
-__device__ __forceinline__ double mul_rn(double a, double b) { return __dmul_rn(a, b); }
+// a product that no later sum may take in (__fmul_rn is a plain product to the
+// compiler, which fuses it where the sum follows directly)
+template <typename T>
+__device__ __forceinline__ T mul_rn(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 template <typename T>
 __device__ __forceinline__ T pc_first(T h2, T b, int nn) {
   return mul_rn(mul_rn(h2, b), inv_nn<T>(nn));

@@ -737,6 +737,8 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
   auto tb = [&](int l) { return l == 0 ? (double)sizeof(TV) : t; };  // right-hand-side bytes of level l
   auto coarse_bytes = [&](int l) { return cells(l) * (tb(l) + t); };  // b read, x written
   auto first_bytes = [&](int l, bool store_red) { return cells(l) * (tb(l) + (store_red ? t : 0.5 * t)); };
+  // the first black and the red half sweep after it run as one pass
+  auto first_two = [&](int l) { return std::is_same_v<T, float> && c.mg_pre > 1 && mg_first2_fits(s->lv[l].g); };
   auto half_bytes = [&](int l) { return cells(l) * (0.5 * t + 0.5 * tb(l) + 0.5 * t); };
   auto restrict_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
   auto prolong_bytes = [&](int l) { return cells(l) * t + cells(l + 1) * t; };
@@ -756,7 +758,8 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
     double b = nl == 1 ? coarse_bytes(0) : coarse_bytes(lsub);
     for (int l = 0; l < lsub; ++l)
       b += tiled(l) ? tile_down_bytes(l) + tile_up_bytes(l)
-                    : first_bytes(l, c.mg_pre == 1) + 2.0 * (c.mg_pre - 1) * half_bytes(l) + restrict_bytes(l) +
+                    : first_bytes(l, c.mg_pre == 1) + (2.0 * (c.mg_pre - 1) - first_two(l)) * half_bytes(l) +
+                          restrict_bytes(l) +
                           prolong_bytes(l) + 2.0 * c.mg_post * half_bytes(l);
     return b;
   }());
@@ -793,12 +796,18 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
         CKH((mg_tile_down<T, TBl>(g, (T *)s->lv[l].xs, b, s->lv[l + 1].g, (T *)s->lv[l + 1].b, c.mg_pre, st)));
         return SIM_OK;
       }
+      // (first black, then red) in one pass where the level takes it
+      const bool two = first_two(l);
       {
         ProbeExt pr(PR_SMOOTH_FIRST, st, first_bytes(l, store_red));
-        CKH((mg_smooth_first<T, TBl>(g, x, b, store_red, st)));
+        if constexpr (std::is_same_v<T, float>) {
+          if (two) CKH(mg_smooth_first2(g, x, b, st));
+        }
+        if (!two) CKH((mg_smooth_first<T, TBl>(g, x, b, store_red, st)));
       }
       for (int q = 1; q < c.mg_pre; ++q)
         for (int color = 0; color < 2; ++color) {
+          if (two && q == 1 && color == 0) continue;
           ProbeExt pr(PR_SMOOTH, st, half_bytes(l));
           CKH((mg_smooth<T, TBl>(g, x, b, color, st)));
         }

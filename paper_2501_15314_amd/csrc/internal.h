@@ -107,6 +107,11 @@ hipError_t cast_copy(T *y, const double *x, long long n, hipStream_t s);
 // stored only with store_red (else a following half sweep overwrites them)
 template <typename T, typename TB>
 hipError_t mg_smooth_first(const Geo &g, T *x, const TB *b, bool store_red, hipStream_t s);
+// that sweep (black values not stored) and the red half sweep after it in one
+// pass, in float32 on grids that it takes (mg_first2_fits)
+bool mg_first2_fits(const Geo &g);
+template <typename TB>
+hipError_t mg_smooth_first2(const Geo &g, float *x, const TB *b, hipStream_t s);
 template <typename T, typename TB>
 hipError_t mg_smooth(const Geo &g, T *x, const TB *b, int color, hipStream_t s);
 template <typename T, typename TB>

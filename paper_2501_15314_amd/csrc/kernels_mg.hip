@@ -282,6 +282,232 @@ __global__ void __launch_bounds__(256) k_prolong(Geo gf, T *xf, Geo gc, const T 
   }
 }
 
+// The first black half sweep from x = 0 and the red one after it in one pass:
+// from the right-hand side alone, only the red values are stored (the next
+// half sweep forms the black ones anew from them).  The two SW_FIRST1 and
+// SW_POISSON passes it replaces write the black values and read them and half
+// of the right-hand side back: 201 MB at 256^3 in float32 against 101 MB.
+//
+// A workgroup owns whole rows (no halo along axis 2) of which the first and
+// last are a halo whose black values it computes but whose red ones it does not
+// store (the first red values of the row beyond are formed by those threads from
+// a load of their own), and marches over a
+// chunk of planes with the black values one plane ahead of the red ones: at
+// plane k it forms black(k) from the first red values r0(k - 1 .. k + 1) and
+// red(k - 1) from black(k - 2 .. k); neighbours along axis 0 are in registers,
+// the others in LDS (two buffers, one barrier per plane).  A cell outside a
+// wall box has a reciprocal count of 0 and so stays 0.
+//
+// Bounded by the latency of a plane's loads (two planes ahead) and its barrier
+// with two workgroups of 8 wavefronts on a compute unit: float32, before (both
+// passes) and after, us: 128^3 12.5 / 10.1, 256^3 41.2 / 29.9, 384^3 136 / 82.
+// In float64 its registers leave half the wavefronts or spill (256^3: 76.7
+// before, 75.6 one plane ahead, 192 two ahead), so that form keeps two passes.
+// Chunks of 16 planes in one and a third rounds of workgroups took 34.4 us at
+// 256^3, and neighbouring row tiles on one XCD no less than spread ones.
+struct First2Shape {
+  int bx, rows, chunk;
+  dim3 grid;
+};
+constexpr int FIRST2_WAVES = 16;  // wavefronts on a compute unit (its registers)
+// Whole rows of at most 256 entries per colour, and enough rows that a
+// workgroup's wrap at most once.
+bool mg_first2_fits(const Geo &g) { return g.hn2 % 2 == 0 && g.hn2 <= 256 && g.n1 >= 16 && g.n0 >= 4; }
+static First2Shape first2_shape(const Geo &g) {
+  First2Shape s;
+  s.bx = g.hn2 / 2;
+  s.rows = 512 / s.bx;
+  if (s.rows < 8) s.rows = 8;
+  if (s.rows > 16) s.rows = 16;
+  const int ty = (g.n1 + s.rows - 3) / (s.rows - 2);
+  // one round of workgroups on the 256 compute units, if that leaves them a
+  // few planes each: the planes before and after a chunk are computed again
+  const int slots = 256 * (FIRST2_WAVES / ((s.bx * s.rows + 63) / 64)), nch = slots / ty > 0 ? slots / ty : 1;
+  s.chunk = (g.n0 + nch - 1) / nch;
+  if (s.chunk < 2) s.chunk = 2;
+  s.grid = dim3(ty, (g.n0 + s.chunk - 1) / s.chunk);
+  return s;
+}
+
+template <typename T, typename TB, int NT>
+__global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, double h2, int chunk) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  const int BX = blockDim.x, rows = blockDim.y, W = g.hn2 + 2, TS = rows * W;
+  T *lds = (T *)lds_raw;  // [buffer][red, black][rows][W]
+  const int mz = blockIdx.y;
+  const int tx = threadIdx.x, ty = threadIdx.y, m0 = 2 * tx;
+  const int j0 = blockIdx.x * (rows - 2), ju = j0 - 1 + ty, jw = mwrap(ju, g.n1, g.bc1);
+  const bool in = jw >= 0 && jw < g.n1;  // a row far past the last one wraps no more: unused
+  const int j = in ? jw : 0;
+  const bool store = ty > 0 && ty < rows - 1 && ju < g.n1;
+  const int i0 = mz * chunk, i1 = min(i0 + chunk, g.n0);
+  const long long P = (long long)g.n1 * g.hn2;
+  const unsigned rw = j * g.hn2 + m0;
+  const T th2 = (T)h2;
+  const TB *br = b, *bk = b + g.half;
+  // reciprocal counts of the thread's cells by parity of k, inside the grid
+  const int s0 = (i0 + ju) & 1;  // parity of the red cells at plane i0
+  T inv[2][2];
+  unsigned pk = 0;
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dg = diag_jk(g, j, 2 * (m0 + u) + (f ? 1 - s0 : s0), false, 0);
+      pk |= (unsigned)dg << (8 * f + 4 * u);
+      inv[f][u] = in ? inv_nn<T>(6 - dg) : T(0);
+    }
+  // the row beyond the halo rows, whose red cells have the parity of the own black ones
+  const int jeu = ty == 0 ? ju - 1 : (ty == rows - 1 ? ju + 1 : ju), jew = mwrap(jeu, g.n1, g.bc1);
+  const bool ein = jew >= 0 && jew < g.n1;
+  const int je = ein ? jew : 0;
+  const unsigned ew = je * g.hn2 + m0;
+  T inve[2][2];
+  unsigned pke = 0;
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dg = diag_jk(g, je, 2 * (m0 + u) + (f ? 1 - s0 : s0), false, 0);
+      pke |= (unsigned)dg << (8 * f + 4 * u);
+      inve[f][u] = ein ? inv_nn<T>(6 - dg) : T(0);
+    }
+  // counts of parity index f at plane i: as tabulated, one less at a wall of
+  // axis 0, 0 outside (near, known to the compiler: the plane may be such)
+  auto counts = [&](auto near, int i, int f, const T (&tab)[2][2], unsigned packed, bool inside, T (&c)[2]) {
+    c[0] = tab[f][0];
+    c[1] = tab[f][1];
+    if (decltype(near)::value && g.bc0 && (i <= 0 || i >= g.n0 - 1)) {
+      const bool out = !inside || i < 0 || i >= g.n0;
+      c[0] = out ? T(0) : inv_nn<T>(5 - (int)((packed >> (8 * f)) & 15));
+      c[1] = out ? T(0) : inv_nn<T>(5 - (int)((packed >> (8 * f + 4)) & 15));
+    }
+  };
+  auto count = [&](auto near, int i, int f, T (&c)[2]) { counts(near, i, f, inv, pk, in, c); };
+  auto plane = [&](int i) {  // a plane's offset; past a wall the nearest plane, whose counts are 0
+    if (i < 0) i = g.bc0 ? 0 : i + g.n0;
+    if (i >= g.n0) i = g.bc0 ? g.n0 - 1 : i - g.n0;
+    return i * P;
+  };
+  auto ldr = [&](long long o) { return ld2<T>(br + o, rw * (unsigned)sizeof(TB)); };
+  auto lde = [&](long long o) { return ld2<T>(br + o, ew * (unsigned)sizeof(TB)); };
+  auto ldk = [&](long long o) { return ld2<T>(bk + o, rw * (unsigned)sizeof(TB)); };
+  // offsets of the planes k + 2 and k + 3, and of k, advanced by addition
+  long long o2 = plane(i0 + 1), o3 = plane(i0 + 2), ok = (i0 - 2) * P;
+  auto first = [&](V2<T> v, const T (&c)[2]) { return V2<T>{mul_rn(mul_rn(th2, v.x), c[0]), mul_rn(mul_rn(th2, v.y), c[1])}; };
+  // a pair into an LDS plane, with the row's ends (periodic: the other end)
+  auto put = [&](T *t, const V2<T> &v) {
+    T *r = t + ty * W + m0;
+    r[1] = v.x;
+    r[2] = v.y;
+    if (tx == 0) t[ty * W + g.hn2 + 1] = g.bc2 ? T(0) : v.x;
+    if (tx == BX - 1) t[ty * W] = g.bc2 ? T(0) : v.y;
+  };
+  const bool first_row = ty == 0, last_row = ty == rows - 1;
+  const int up = first_row ? 0 : -W, dn = last_row ? 0 : W;
+  // relaxed pair: prev, next along axis 0, the LDS plane t (e in place of the
+  // row beyond the halo rows), parity s of its cells
+  auto relax = [&](const V2<T> &p, const V2<T> &n, const T *t, const V2<T> &e, int s, const V2<T> &bv, const T (&c)[2]) {
+    const T *r = t + ty * W + m0;
+    const T ux = first_row ? e.x : r[1 + up], uy = first_row ? e.y : r[2 + up];
+    const T dx = last_row ? e.x : r[1 + dn], dy = last_row ? e.y : r[2 + dn];
+    const T sx = p.x + n.x + ux + dx + r[s] + r[1 + s];
+    const T sy = p.y + n.y + uy + dy + r[1 + s] + r[2 + s];
+    return V2<T>{T(fma(th2, bv.x, sx) * c[0]), T(fma(th2, bv.y, sy) * c[1])};
+  };
+  // Plane k (parity index f of the black cells there, which is that of the red
+  // ones at k - 1 and k + 1).  Operands are loaded two planes before their use
+  // (few waves fit a compute unit): q holds b_red of plane k at k & 7, bb and be
+  // b_black and the red right-hand side of the row beyond at k & 3; r0 and kk the
+  // first red and the black values at k & 3.  All indices are known to the
+  // compiler, eight planes per turn, so everything stays in registers.
+  V2<T> q[8], bb[4], be[4], r0[4], kk[4];
+  auto body = [&](auto near, int k, int u, int f, T *R) {
+    T *K = R + TS;
+    T c[2], ck[2];
+    count(near, k + 1, f, c);
+    r0[(u + 1) & 3] = first(q[(u + 1) & 7], c);
+    const int s = f ? 1 - s0 : s0;  // parity of the cells of index f
+    count(near, k, f, ck);
+    counts(near, k, f, inve, pke, ein, c);
+    const V2<T> e = first(be[u & 3], c);
+    kk[u & 3] = relax(r0[(u + 3) & 3], r0[(u + 1) & 3], R, e, s, bb[u & 3], ck);
+    if (k > i0) {
+      count(near, k - 1, f, c);
+      const V2<T> v = relax(kk[(u + 2) & 3], kk[u & 3], K, e, s, q[(u + 7) & 7], c);
+      if (store) st2<T>(x + ok - P, rw * (unsigned)sizeof(T), v.x, v.y);
+    }
+  };
+  auto step = [&](int k, int u, int f) {
+    q[(u + 3) & 7] = ldr(o3);
+    bb[(u + 2) & 3] = ldk(o2);
+    be[(u + 2) & 3] = lde(o2);
+    o2 = o3;
+    const int nx = k + 4;
+    if (nx == (g.bc0 ? 0 : g.n0)) o3 = 0;
+    else if (nx > 0 && nx < g.n0 + (g.bc0 ? 0 : 8)) o3 += P;
+    ok += P;
+    T *R = lds + (f ? 2 * TS : 0);
+    put(R, r0[u & 3]);
+    put(R + TS, kk[(u + 3) & 3]);
+    __syncthreads();
+    if (g.bc0 && (k <= 1 || k >= g.n0 - 2)) body(std::true_type{}, k, u, f, R);
+    else body(std::false_type{}, k, u, f, R);
+  };
+  // before the march, which starts at plane i0 - 1 (u = 0; its black values are
+  // the first needed): parity index 0 is that of the red cells at i0, so of
+  // those at i0 - 2 and of the black ones at i0 - 1
+  T c[2];
+  const V2<T> qm = ldr(plane(i0 - 2));
+  q[0] = ldr(plane(i0 - 1));
+  q[1] = ldr(plane(i0));
+  bb[0] = ldk(plane(i0 - 1));
+  be[0] = lde(plane(i0 - 1));
+  q[2] = ldr(plane(i0 + 1));
+  bb[1] = ldk(plane(i0));
+  be[1] = lde(plane(i0));
+  kk[2] = kk[3] = V2<T>{T(0), T(0)};
+  count(std::true_type{}, i0 - 2, 0, c);
+  r0[3] = first(qm, c);
+  count(std::true_type{}, i0 - 1, 1, c);
+  r0[0] = first(q[0], c);
+  for (int k = i0 - 1;;) {
+    step(k, 0, 0);
+    if (++k > i1) break;
+    step(k, 1, 1);
+    if (++k > i1) break;
+    step(k, 2, 0);
+    if (++k > i1) break;
+    step(k, 3, 1);
+    if (++k > i1) break;
+    step(k, 4, 0);
+    if (++k > i1) break;
+    step(k, 5, 1);
+    if (++k > i1) break;
+    step(k, 6, 0);
+    if (++k > i1) break;
+    step(k, 7, 1);
+    if (++k > i1) break;
+  }
+}
+
+template <typename TB>
+hipError_t mg_smooth_first2(const Geo &g, float *x, const TB *b, hipStream_t s) {
+  if (!mg_first2_fits(g)) return hipErrorInvalidValue;
+  const First2Shape f = first2_shape(g);
+  hipEvent_t e0, e1;
+  probe_ext_take(&e0, &e1);
+  const size_t lds = 4 * sizeof(float) * f.rows * (g.hn2 + 2);
+  const dim3 block(f.bx, f.rows);
+  if (f.bx * f.rows <= 512)
+    hipExtLaunchKernelGGL((k_first2<float, TB, 512>), f.grid, block, lds, s, e0, e1, 0, g, x, b, g.h2, f.chunk);
+  else
+    hipExtLaunchKernelGGL((k_first2<float, TB, 1024>), f.grid, block, lds, s, e0, e1, 0, g, x, b, g.h2, f.chunk);
+  return hipGetLastError();
+}
+template hipError_t mg_smooth_first2<float>(const Geo &, float *, const float *, hipStream_t);
+template hipError_t mg_smooth_first2<double>(const Geo &, float *, const double *, hipStream_t);
+
 template <typename T, typename TB>
 hipError_t mg_smooth_first(const Geo &g, T *x, const TB *b, bool store_red, hipStream_t s) {
   MarchShape M = march_shape(g, 1);

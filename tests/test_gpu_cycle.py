@@ -15,7 +15,7 @@ from oracle import mac as omac
 from paper_2501_15314_amd import workloads as wl
 
 from .conftest import gpu_available
-from .gpu_helpers import rel
+from .gpu_helpers import mg_tile_cells, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -94,13 +94,18 @@ P, N, F = wl.BC_PERIODIC, wl.BC_NOSLIP, wl.BC_FREESLIP
     ((24, 36, 28), 18, (2, 2)),    # cut tiles, then a coarse solve of 12 x 18 x 14
     ((16, 16, 16), 8, (2, 0)),     # no sweep after the prolongation
     ((16, 16, 16), 16, (2, 1)),    # the coarse solve by itself
+    ((20, 32, 16), 8, (2, 1)),     # marched levels below: rows of 8, 16 and 24 entries
+    ((32, 24, 48), 12, (2, 1)),
+    ((32, 32, 288), 18, (2, 1)),   # and of 144, in workgroups of 576 threads
 ])
 @pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
-def test_cycle_against_arrays(n, coarsest, sweeps, bc, precision):
+@pytest.mark.parametrize("tiles", [None, 0])  # small levels as tiles, or all of them marched
+def test_cycle_against_arrays(n, coarsest, sweeps, bc, precision, tiles):
     h = 1.0 / 32
     cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=bc, nu=0.02, dt=0.005, precision=precision, mg_coarsest=coarsest,
                     mg_pre=sweeps[0], mg_post=sweeps[1], mg_coarse_sweeps=0)
-    sim = Sim(cfg, 1)
+    with mg_tile_cells(tiles):
+        sim = Sim(cfg, 1)
     b = np.random.default_rng(n[0] + n[2]).standard_normal(n)
     b -= b.mean()
     z = sim.apply("precond", b).cpu().numpy()

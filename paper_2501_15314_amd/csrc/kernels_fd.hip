@@ -14,7 +14,7 @@
 // A pass is C = A D with A an n x n eigenvector matrix (Q or Q^T, bfloat16,
 // rows contiguous along the reduction index, read from L2) and D the grid
 // lines of the pass: a workgroup stages 64 lines (n x 64, bfloat16) in LDS
-// and its four wavefronts produce all n outputs of them with
+// and its eight wavefronts produce all n outputs of them with
 // v_mfma_f32_16x16x32_bf16 (16 x 16 tiles, float32 accumulation), written
 // back through LDS in 16-byte pieces.  The first and the last pass read /
 // write the solver's red/black split layout directly.
@@ -33,7 +33,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int FD_COLS = 64;  // grid lines per workgroup
-constexpr int FD_T = 256;    // four wavefronts
+// Eight wavefronts: the workgroups of a pass are resident all at once and spend
+// most of their time on the loads of their lines, which more threads issue
+// sooner (160 x 160 x 240: passes along z 15.8 -> 13.9 us, along y 13.7 and
+// 13.9, the fused one 23.1 -> 22.7; 32 lines and four wavefronts 17.2, 15.5 and
+// 22.8, as every workgroup reads the whole matrix; the matrix held in registers
+// from before the loads 14.6, 13.8 and 26.4).
+constexpr int FD_T = 512;
+constexpr int FD_W = FD_T / 64;
 
 __device__ __forceinline__ unsigned int to_bf16(float x) {
   unsigned int u = __float_as_uint(x);
@@ -78,7 +85,7 @@ __device__ __forceinline__ void stage(const FdPass &P, const TI *vsplit, unsigne
   if (SRC == SRC_ROWS) {
     // task: 8 columns x 4 rows; four 16-byte row reads, transposed into eight
     // 8-byte LDS writes
-    constexpr int BT = 2;
+    constexpr int BT = 1;
     const int ntask = 8 * (nk >> 2);
     for (int e0 = 0; e0 < ntask; e0 += BT * FD_T) {
       uint4 r[BT][4];
@@ -110,7 +117,7 @@ __device__ __forceinline__ void stage(const FdPass &P, const TI *vsplit, unsigne
       }
     }
   } else if (SRC == SRC_LINES) {
-    constexpr int BT = 8;
+    constexpr int BT = 4;
     const int n8 = nk >> 3, nr = n >> 3, ntask = FD_COLS * n8;
     for (int e0 = 0; e0 < ntask; e0 += BT * FD_T) {
       uint4 v[BT];
@@ -175,7 +182,7 @@ __device__ __forceinline__ void stage(const FdPass &P, const TI *vsplit, unsigne
 // transform, scaling by 1 / (lam_x + lam_y + lam_z) and back transform, the
 // scaled modes going through LDS between the two products.
 template <int SRC, int DST, int MAXT, typename TI, typename TO>
-__global__ void __launch_bounds__(FD_T, MAXT == 4 ? 4 : 2) k_fd_pass(FdPass P, const TI *vsplit, TO *zsplit) {
+__global__ void __launch_bounds__(FD_T, 4) k_fd_pass(FdPass P, const TI *vsplit, TO *zsplit) {
   constexpr bool ORIENT_C = DST == DST_ROWS || DST == DST_ROWS_FUSED;
   extern __shared__ unsigned short Ds[];  // [FD_COLS][ldsk]
   // k is zero padded to nk (a multiple of 64: the k loop takes two steps of
@@ -204,7 +211,7 @@ __global__ void __launch_bounds__(FD_T, MAXT == 4 ? 4 : 2) k_fd_pass(FdPass P, c
         // clamped addresses instead of a condition, so that the wait for these
         // loads falls at their use: rows beyond n produce outputs that are
         // dropped, and k beyond n meets the zero padding of Ds
-        const int row = 16 * (wv + 4 * q) + l16, kq = k0 + 8 * lq;
+        const int row = 16 * (wv + FD_W * q) + l16, kq = k0 + 8 * lq;
         dst[q] = *(const bf16x8 *)&A[(long long)min(row, n - 1) * n + min(kq, n - 8)];
       }
     };
@@ -239,7 +246,7 @@ __global__ void __launch_bounds__(FD_T, MAXT == 4 ? 4 : 2) k_fd_pass(FdPass P, c
     // still hold the zero padding of the staging)
 #pragma unroll
     for (int q = 0; q < MAXT; ++q) {
-      const int t = wv + 4 * q;
+      const int t = wv + FD_W * q;
       if (t >= ntiles) continue;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -269,7 +276,7 @@ __global__ void __launch_bounds__(FD_T, MAXT == 4 ? 4 : 2) k_fd_pass(FdPass P, c
   const int ldo = ORIENT_C ? FD_COLS + 8 : n16 + 8;
 #pragma unroll
   for (int q = 0; q < MAXT; ++q) {
-    const int t = wv + 4 * q;
+    const int t = wv + FD_W * q;
     if (t >= ntiles) continue;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -328,8 +335,8 @@ __global__ void __launch_bounds__(FD_T, MAXT == 4 ? 4 : 2) k_fd_pass(FdPass P, c
 
 template <int SRC, int DST, typename TI, typename TO>
 hipError_t run_pass(const FdPass &P, int batch, const TI *v, TO *z, hipStream_t s) {
-  // each of the four wavefronts owns every fourth 16-row output tile: up to
-  // 4 tiles (64 float32 accumulators per lane) for n <= 256, 8 for n <= 512
+  // each of the eight wavefronts owns every eighth 16-row output tile: up to
+  // 2 tiles (32 float32 accumulators per lane) for n <= 256, 4 for n <= 512
   const int n16 = (P.n + 15) & ~15, nk = (P.n + 63) & ~63;
   if (P.n % 8 || P.ncols % 8 || n16 > 512) return hipErrorInvalidValue;
   // staging [64][nk + 8]; epilogue [n16][72] (rows) or [64][n16 + 8] (lines)
@@ -339,9 +346,9 @@ hipError_t run_pass(const FdPass &P, int batch, const TI *v, TO *z, hipStream_t 
                                                                                   : (size_t)FD_COLS * (n16 + 8));
   dim3 grid((P.ncols + FD_COLS - 1) / FD_COLS, 1, batch);
   if (n16 <= 256)
-    hipLaunchKernelGGL((k_fd_pass<SRC, DST, 4, TI, TO>), grid, dim3(FD_T), lds, s, P, v, z);
+    hipLaunchKernelGGL((k_fd_pass<SRC, DST, 2, TI, TO>), grid, dim3(FD_T), lds, s, P, v, z);
   else
-    hipLaunchKernelGGL((k_fd_pass<SRC, DST, 8, TI, TO>), grid, dim3(FD_T), lds, s, P, v, z);
+    hipLaunchKernelGGL((k_fd_pass<SRC, DST, 4, TI, TO>), grid, dim3(FD_T), lds, s, P, v, z);
   return hipGetLastError();
 }
 

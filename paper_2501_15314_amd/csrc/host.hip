@@ -742,6 +742,13 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
   auto half_bytes = [&](int l) { return cells(l) * (0.5 * t + 0.5 * tb(l) + 0.5 * t); };
   auto restrict_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
   auto prolong_bytes = [&](int l) { return cells(l) * t + cells(l + 1) * t; };
+  // the prolongation and the black half sweep after it run as one pass, where
+  // bytes bound them: at 256^3 25.2 us against 34.5 for the two, at 128^3 10.2
+  // against 10.6, and the calls there gain nothing
+  auto black_prolong = [&](int l) {
+    return std::is_same_v<T, float> && c.mg_post > 0 && mg_first2_fits(s->lv[l].g) && cells(l) > 128.0 * 128.0 * 128.0;
+  };
+  auto prolong_black_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
   // tile levels: b read, x written, the coarse b written; the red half of x,
   // b and the coarse x read, x written
   auto tile_down_bytes = [&](int l) { return cells(l) * (tb(l) + t) + cells(l + 1) * t; };
@@ -760,7 +767,8 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
       b += tiled(l) ? tile_down_bytes(l) + tile_up_bytes(l)
                     : first_bytes(l, c.mg_pre == 1) + (2.0 * (c.mg_pre - 1) - first_two(l)) * half_bytes(l) +
                           restrict_bytes(l) +
-                          prolong_bytes(l) + 2.0 * c.mg_post * half_bytes(l);
+                          (black_prolong(l) ? prolong_black_bytes(l) - half_bytes(l) : prolong_bytes(l)) +
+                          2.0 * c.mg_post * half_bytes(l);
     return b;
   }());
   auto coarse_solve = [&](const Geo &g, auto *b, T *x) -> sim_status {
@@ -837,12 +845,18 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
                                 c.mg_post, st)));
         return SIM_OK;
       }
+      // (prolongation, then black) in one pass where the level takes it
+      const bool two = black_prolong(l);
       {
-        ProbeExt pr(PR_PROLONG, st, prolong_bytes(l));
-        CKH(mg_prolong<T>(g, x, s->lv[l + 1].g, (const T *)s->lv[l + 1].x, st));
+        ProbeExt pr(PR_PROLONG, st, two ? prolong_black_bytes(l) : prolong_bytes(l));
+        if constexpr (std::is_same_v<T, float>) {
+          if (two) CKH(mg_prolong_black(g, x, b, s->lv[l + 1].g, (const float *)s->lv[l + 1].x, st));
+        }
+        if (!two) CKH(mg_prolong<T>(g, x, s->lv[l + 1].g, (const T *)s->lv[l + 1].x, st));
       }
       for (int q = 0; q < c.mg_post; ++q)
         for (int color = 1; color >= 0; --color) {
+          if (two && q == 0 && color == 1) continue;
           ProbeExt pr(PR_SMOOTH, st, half_bytes(l));
           CKH((mg_smooth<T, TBl>(g, x, b, color, st)));
         }

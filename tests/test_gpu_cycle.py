@@ -112,3 +112,19 @@ def test_cycle_against_arrays(n, coarsest, sweeps, bc, precision, tiles):
     sim.close()
     ref = _cycle(b, h, bc, coarsest, *sweeps)
     assert rel(z - z.mean(), ref - ref.mean()) < (1e-12 if precision == wl.PREC_FP64 else 1e-4)
+
+
+@pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
+def test_cycle_on_a_large_level(bc):
+    # above 128^3 cells the prolongation and the black half sweep run as one
+    # pass; the last row tile is cut
+    n, h, coarsest = (144, 128, 128), 1.0 / 128, 9
+    cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=bc, nu=0.02, dt=0.005, precision=wl.PREC_FP32MG,
+                    mg_coarsest=coarsest, mg_coarse_sweeps=0)
+    sim = Sim(cfg, 1)
+    b = np.random.default_rng(7).standard_normal(n)
+    b -= b.mean()
+    z = sim.apply("precond", b).cpu().numpy()
+    sim.close()
+    ref = _cycle(b, h, bc, coarsest, cfg.mg_pre, cfg.mg_post)
+    assert rel(z - z.mean(), ref - ref.mean()) < 1e-4

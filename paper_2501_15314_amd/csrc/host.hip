@@ -742,13 +742,19 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
   auto half_bytes = [&](int l) { return cells(l) * (0.5 * t + 0.5 * tb(l) + 0.5 * t); };
   auto restrict_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
   auto prolong_bytes = [&](int l) { return cells(l) * t + cells(l + 1) * t; };
-  // the prolongation and the black half sweep after it run as one pass, where
-  // bytes bound them: at 256^3 25.2 us against 34.5 for the two, at 128^3 10.2
-  // against 10.6, and the calls there gain nothing
-  auto black_prolong = [&](int l) {
-    return std::is_same_v<T, float> && c.mg_post > 0 && mg_first2_fits(s->lv[l].g) && cells(l) > 128.0 * 128.0 * 128.0;
+  // Levels above 128^3 cells, where bytes bound the passes, run the last black
+  // half sweep of the descent with the restriction, and the prolongation with
+  // the black half sweep after it, in one pass each (at 256^3 31.2 us against
+  // 39.3 for the two, and 25.2 against 34.5; at 128^3 10.3 against 10.2 and 10.2
+  // against 10.6).  The black values of the first are lost: the second, or its
+  // two passes, form them anew.
+  auto large = [&](int l) {
+    return std::is_same_v<T, float> && mg_first2_fits(s->lv[l].g) && cells(l) > 128.0 * 128.0 * 128.0;
   };
+  auto black_prolong = [&](int l) { return large(l) && c.mg_post > 0; };
   auto prolong_black_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
+  auto black_restrict = [&](int l) { return large(l) && c.mg_pre > 1 && c.mg_post > 0; };
+  auto black_restrict_bytes = [&](int l) { return cells(l) * (0.5 * t + tb(l)) + cells(l + 1) * t; };
   // tile levels: b read, x written, the coarse b written; the red half of x,
   // b and the coarse x read, x written
   auto tile_down_bytes = [&](int l) { return cells(l) * (tb(l) + t) + cells(l + 1) * t; };
@@ -766,7 +772,7 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
     for (int l = 0; l < lsub; ++l)
       b += tiled(l) ? tile_down_bytes(l) + tile_up_bytes(l)
                     : first_bytes(l, c.mg_pre == 1) + (2.0 * (c.mg_pre - 1) - first_two(l)) * half_bytes(l) +
-                          restrict_bytes(l) +
+                          (black_restrict(l) ? black_restrict_bytes(l) - half_bytes(l) : restrict_bytes(l)) +
                           (black_prolong(l) ? prolong_black_bytes(l) - half_bytes(l) : prolong_bytes(l)) +
                           2.0 * c.mg_post * half_bytes(l);
     return b;
@@ -816,12 +822,16 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
       for (int q = 1; q < c.mg_pre; ++q)
         for (int color = 0; color < 2; ++color) {
           if (two && q == 1 && color == 0) continue;
+          if (black_restrict(l) && q == c.mg_pre - 1 && color == 1) continue;
           ProbeExt pr(PR_SMOOTH, st, half_bytes(l));
           CKH((mg_smooth<T, TBl>(g, x, b, color, st)));
         }
       T *bnext = (T *)s->lv[l + 1].b;
-      ProbeExt pr(PR_RESTRICT, st, restrict_bytes(l));
-      CKH((mg_restrict<T, TBl>(g, x, b, s->lv[l + 1].g, bnext, st)));
+      ProbeExt pr(PR_RESTRICT, st, black_restrict(l) ? black_restrict_bytes(l) : restrict_bytes(l));
+      if constexpr (std::is_same_v<T, float>) {
+        if (black_restrict(l)) CKH(mg_black_restrict(g, (const float *)x, b, s->lv[l + 1].g, bnext, st));
+      }
+      if (!black_restrict(l)) CKH((mg_restrict<T, TBl>(g, x, b, s->lv[l + 1].g, bnext, st)));
       return SIM_OK;
     };
     sim_status rc = l == 0 ? pre(v) : pre((const T *)s->lv[l].b);

@@ -112,6 +112,10 @@ hipError_t mg_smooth_first(const Geo &g, T *x, const TB *b, bool store_red, hipS
 bool mg_first2_fits(const Geo &g);
 template <typename TB>
 hipError_t mg_smooth_first2(const Geo &g, float *x, const TB *b, hipStream_t s);
+// the last black half sweep of a descent (black values not stored) and the
+// restriction after it, likewise
+template <typename TB>
+hipError_t mg_black_restrict(const Geo &g, const float *x, const TB *b, const Geo &gc, float *bc, hipStream_t s);
 // the prolongation (red values not stored) and the black half sweep after it, likewise
 template <typename TB>
 hipError_t mg_prolong_black(const Geo &g, float *x, const TB *b, const Geo &gc, const float *xc, hipStream_t s);

@@ -670,6 +670,176 @@ __global__ void __launch_bounds__(NT, 4) k_prolong_black(Geo g, T *x, const TB *
   }
 }
 
+// The last black half sweep of the descent and the restriction in one pass: the
+// black values feed the red residuals and are not stored, since the ascent
+// relaxes them anew from the red ones.  The two passes move 101 + 109 MB at
+// 256^3 in float32, this one 109.
+//
+// The march of k_first2 with the red values loaded: at plane k it forms
+// black(k), then the residuals of the red cells at k - 1, summed over pairs of
+// planes and, through LDS, pairs of rows (a workgroup stores whole pairs: its
+// stored rows and its chunk start at even places and are even in number).
+//
+// Bounded as k_first2.  Both passes before and this one after, float32, us:
+// 256^3 39.3 / 31.2, 384^3 141 / 88, 128^3 10.2 / 10.3.
+template <typename T, typename TB, int NT>
+__global__ void __launch_bounds__(NT, 4) k_black_restrict(Geo g, const T *x, const TB *b, Geo gc, T *bc, double h2,
+                                                          int chunk) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  const int BX = blockDim.x, rows = blockDim.y, W = g.hn2 + 2, TS = rows * W;
+  T *lds = (T *)lds_raw;        // [buffer][red, black][rows][W]
+  T *pair = lds + 4 * TS;       // [rows][BX][2]
+  const int tx = threadIdx.x, ty = threadIdx.y, m0 = 2 * tx;
+  const int ju = blockIdx.x * (rows - 2) - 1 + ty, jw = mwrap(ju, g.n1, g.bc1);
+  const bool in = jw >= 0 && jw < g.n1;
+  const int j = in ? jw : 0;
+  const bool store = ty > 0 && ty < rows - 1 && ju < g.n1;
+  const int i0 = blockIdx.y * chunk, i1 = min(i0 + chunk, g.n0);
+  const long long P = (long long)g.n1 * g.hn2, PC = (long long)gc.n1 * gc.hn2;
+  const unsigned rw = j * g.hn2 + m0, cw = (unsigned)((j >> 1) * gc.hn2 + (m0 >> 1)) * sizeof(T);
+  const T th2 = (T)h2, ih2 = (T)(1.0 / g.h2);
+  const TB *bk = b + g.half;
+  const int s0 = (i0 + j) & 1;  // parity of the red cells at plane i0
+  // by parity of k: reciprocal counts (0 outside the grid) and counts
+  T inv[2][2], nn[2][2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int dg = diag_jk(g, j, 2 * (m0 + u) + (f ? 1 - s0 : s0), false, 0);
+      inv[f][u] = in ? inv_nn<T>(6 - dg) : T(0);
+      nn[f][u] = (T)(6 - dg);
+    }
+  // the row beyond a halo row
+  const int jeu = ty == 0 ? ju - 1 : (ty == rows - 1 ? ju + 1 : ju), jew = mwrap(jeu, g.n1, g.bc1);
+  const bool ein = jew >= 0 && jew < g.n1;
+  const unsigned ew = (ein ? jew : 0) * g.hn2 + m0;
+  auto plane = [&](int i) {  // a plane's offset; past a wall the nearest one
+    if (i < 0) i = g.bc0 ? 0 : i + g.n0;
+    if (i >= g.n0) i = g.bc0 ? g.n0 - 1 : i - g.n0;
+    return i * P;
+  };
+  auto outside = [&](int i) { return g.bc0 && (i < 0 || i >= g.n0); };
+  auto ldx = [&](long long o) { return ld2<T>(x + o, rw * (unsigned)sizeof(T)); };
+  auto lde = [&](long long o) { return ld2<T>(x + o, ew * (unsigned)sizeof(T)); };
+  auto ldr = [&](long long o) { return ld2<T>(b + o, rw * (unsigned)sizeof(TB)); };
+  auto ldk = [&](long long o) { return ld2<T>(bk + o, rw * (unsigned)sizeof(TB)); };
+  auto put = [&](T *t, const V2<T> &v) {
+    T *r = t + ty * W + m0;
+    r[1] = v.x;
+    r[2] = v.y;
+    if (tx == 0) t[ty * W + g.hn2 + 1] = g.bc2 ? T(0) : v.x;
+    if (tx == BX - 1) t[ty * W] = g.bc2 ? T(0) : v.y;
+  };
+  const bool first_row = ty == 0, last_row = ty == rows - 1;
+  const int up = first_row ? 0 : -W, dn = last_row ? 0 : W;
+  auto sums = [&](const V2<T> &p, const V2<T> &n, const T *t, const V2<T> &e, int s) {
+    const T *r = t + ty * W + m0;
+    const T ux = first_row ? e.x : r[1 + up], uy = first_row ? e.y : r[2 + up];
+    const T dx = last_row ? e.x : r[1 + dn], dy = last_row ? e.y : r[2 + dn];
+    return V2<T>{p.x + n.x + ux + dx + r[s] + r[1 + s], p.y + n.y + uy + dy + r[1 + s] + r[2 + s]};
+  };
+  // as in k_first2; xr: red values of plane k at k & 7, br: b_red of plane k - 1
+  // and bb, be: b_black and the row beyond of plane k, all at k & 3
+  V2<T> xr[8], br[4], bb[4], be[4], kk[4];
+  T acc[2] = {T(0), T(0)};
+  long long o1 = plane(i0), o2 = plane(i0 + 1), o3 = plane(i0 + 2);
+  // the coarse values of the plane pair that ends at plane i: rows of even place
+  // (odd ty) add their partner's sums
+  auto emit = [&](int i) {
+    if (!store || !(ty & 1)) return;
+    const T *q = pair + ((ty + 1) * BX + tx) * 2;
+    const T v0 = (acc[0] + q[0]) * (T)0.125, v1 = (acc[1] + q[1]) * (T)0.125;
+    const int I = i >> 1;
+    const bool odd = (I + (j >> 1)) & 1;  // colour of (I, J, K)
+    T *o = bc + I * PC;
+    *(T *)((char *)o + cw) = odd ? v1 : v0;
+    *(T *)((char *)(o + gc.half) + cw) = odd ? v0 : v1;
+  };
+  // k = i0 - 1 + u (mod 8); f: parity index of the black cells at k, and the buffer
+  auto step = [&](int k, int u, int f) {
+    xr[(u + 3) & 7] = ldx(o3);
+    bb[(u + 2) & 3] = ldk(o2);
+    be[(u + 2) & 3] = lde(o2);
+    br[(u + 2) & 3] = ldr(o1);
+    o1 = o2;
+    o2 = o3;
+    const int nx = k + 4;
+    if (nx == (g.bc0 ? 0 : g.n0)) o3 = 0;
+    else if (nx > 0 && nx < g.n0 + (g.bc0 ? 0 : 8)) o3 += P;
+    T *R = lds + (f ? 2 * TS : 0), *K = R + TS;
+    V2<T> &xn = xr[(u + 1) & 7];
+    if (outside(k + 1) || !in) xn = V2<T>{T(0), T(0)};
+    put(R, xr[u & 7]);
+    put(K, kk[(u + 3) & 3]);
+    __syncthreads();
+    const int s = f ? 1 - s0 : s0;
+    if (!f) {  // plane k - 1 is even and starts a pair; the one that ended at k - 2 has its partners' sums in LDS
+      if (k > i0 + 1) emit(k - 2);
+      acc[0] = acc[1] = T(0);
+    }
+    V2<T> e = be[u & 3];
+    if (!ein || outside(k)) e = V2<T>{T(0), T(0)};
+    T c0 = inv[f][0], c1 = inv[f][1];
+    if (g.bc0 && (k <= 0 || k >= g.n0 - 1)) {
+      const bool out = !in || outside(k);
+      c0 = out ? T(0) : inv_nn<T>((int)nn[f][0] - 1);
+      c1 = out ? T(0) : inv_nn<T>((int)nn[f][1] - 1);
+    }
+    const V2<T> sb = sums(xr[(u + 7) & 7], xn, R, e, s);
+    kk[u & 3] = V2<T>{T(fma(th2, bb[u & 3].x, sb.x) * c0), T(fma(th2, bb[u & 3].y, sb.y) * c1)};
+    if (k > i0) {
+      const V2<T> sr = sums(kk[(u + 2) & 3], kk[u & 3], K, e, s), xv = xr[(u + 7) & 7], bv = br[u & 3];
+      const bool wall = g.bc0 && (k - 1 == 0 || k == g.n0);
+      const T n0 = wall ? nn[f][0] - T(1) : nn[f][0], n1 = wall ? nn[f][1] - T(1) : nn[f][1];
+      acc[0] += fma(-fma(n0, xv.x, -sr.x), ih2, bv.x);  // pc_resid
+      acc[1] += fma(-fma(n1, xv.y, -sr.y), ih2, bv.y);
+      if (f && store && !(ty & 1)) {  // plane k - 1 ends a pair
+        T *q = pair + (ty * BX + tx) * 2;
+        q[0] = acc[0];
+        q[1] = acc[1];
+      }
+    }
+  };
+  // before the march, which starts at plane i0 - 1 (u = 0, black parity index 0)
+  {
+    V2<T> xm = ldx(plane(i0 - 2)), xc = ldx(plane(i0 - 1));
+    xr[1] = ldx(plane(i0));
+    bb[0] = ldk(plane(i0 - 1));
+    be[0] = lde(plane(i0 - 1));
+    br[0] = ldr(plane(i0 - 2));
+    xr[2] = ldx(plane(i0 + 1));
+    bb[1] = ldk(plane(i0));
+    be[1] = lde(plane(i0));
+    br[1] = ldr(plane(i0 - 1));
+    if (outside(i0 - 2) || !in) xm = V2<T>{T(0), T(0)};
+    if (outside(i0 - 1) || !in) xc = V2<T>{T(0), T(0)};
+    xr[7] = xm;
+    xr[0] = xc;
+    kk[2] = kk[3] = V2<T>{T(0), T(0)};
+  }
+  for (int k = i0 - 1;;) {
+    step(k, 0, 0);
+    if (++k > i1) break;
+    step(k, 1, 1);
+    if (++k > i1) break;
+    step(k, 2, 0);
+    if (++k > i1) break;
+    step(k, 3, 1);
+    if (++k > i1) break;
+    step(k, 4, 0);
+    if (++k > i1) break;
+    step(k, 5, 1);
+    if (++k > i1) break;
+    step(k, 6, 0);
+    if (++k > i1) break;
+    step(k, 7, 1);
+    if (++k > i1) break;
+  }
+  __syncthreads();
+  emit(i1 - 1);
+}
+
 template <typename TB>
 hipError_t mg_smooth_first2(const Geo &g, float *x, const TB *b, hipStream_t s) {
   if (!mg_first2_fits(g)) return hipErrorInvalidValue;
@@ -704,6 +874,26 @@ hipError_t mg_prolong_black(const Geo &g, float *x, const TB *b, const Geo &gc, 
 }
 template hipError_t mg_prolong_black<float>(const Geo &, float *, const float *, const Geo &, const float *, hipStream_t);
 template hipError_t mg_prolong_black<double>(const Geo &, float *, const double *, const Geo &, const float *, hipStream_t);
+template <typename TB>
+hipError_t mg_black_restrict(const Geo &g, const float *x, const TB *b, const Geo &gc, float *bc, hipStream_t s) {
+  if (!mg_first2_fits(g)) return hipErrorInvalidValue;
+  First2Shape f = first2_shape(g);
+  f.chunk = (f.chunk + 1) & ~1;  // whole pairs of planes
+  f.grid.y = (g.n0 + f.chunk - 1) / f.chunk;
+  hipEvent_t e0, e1;
+  probe_ext_take(&e0, &e1);
+  const size_t lds = sizeof(float) * f.rows * (4 * (g.hn2 + 2) + 2 * f.bx);
+  const dim3 block(f.bx, f.rows);
+  if (f.bx * f.rows <= 512)
+    hipExtLaunchKernelGGL((k_black_restrict<float, TB, 512>), f.grid, block, lds, s, e0, e1, 0, g, x, b, gc, bc, g.h2,
+                          f.chunk);
+  else
+    hipExtLaunchKernelGGL((k_black_restrict<float, TB, 1024>), f.grid, block, lds, s, e0, e1, 0, g, x, b, gc, bc, g.h2,
+                          f.chunk);
+  return hipGetLastError();
+}
+template hipError_t mg_black_restrict<float>(const Geo &, const float *, const float *, const Geo &, float *, hipStream_t);
+template hipError_t mg_black_restrict<double>(const Geo &, const float *, const double *, const Geo &, float *, hipStream_t);
 template hipError_t mg_smooth_first2<float>(const Geo &, float *, const float *, hipStream_t);
 template hipError_t mg_smooth_first2<double>(const Geo &, float *, const double *, hipStream_t);
 

@@ -381,14 +381,14 @@ sim_status sim_schur_spectrum(sim_t sim, int32_t exact, const double *d_v0, int3
  * (IBSCHUR_MG_TILE_CELLS in the environment at sim_create sets that bound;
  * 0: no tile levels). */
 enum {
-  SIM_PROBE_SMOOTH = 0,             /* red-black Gauss-Seidel half sweep, plane-march levels */
-  SIM_PROBE_SMOOTH_FIRST = 1,       /* first sweep from zero, plane-march levels */
-  SIM_PROBE_RESTRICT = 2,           /* residual + restriction, plane-march levels */
-  SIM_PROBE_PROLONG = 3,            /* prolongation + correction, plane-march levels */
+  SIM_PROBE_SMOOTH = 0,             /* red-black Gauss-Seidel half sweep launched by itself, plane-march levels */
+  SIM_PROBE_SMOOTH_FIRST = 1,       /* first sweep from zero, plane-march levels; in float32 with the red half sweep after it */
+  SIM_PROBE_RESTRICT = 2,           /* residual + restriction, plane-march levels; in float32 above 128^3 cells with the black half sweep before it */
+  SIM_PROBE_PROLONG = 3,            /* prolongation + correction, plane-march levels; in float32 above 128^3 cells with the black half sweep after it */
   SIM_PROBE_LAPLACIAN = 4,          /* L z inside the S~ product */
-  SIM_PROBE_SPREAD_DIV = 5,         /* D W q on the active tiles */
+  SIM_PROBE_SPREAD_DIV = 5,         /* D W q on the active tiles (float64 form: the region sums of the coupling product) */
   SIM_PROBE_SPREAD_FACE = 6,        /* W q on the active tiles */
-  SIM_PROBE_INTERP_GRAD = 7,        /* W^T G z */
+  SIM_PROBE_INTERP_GRAD = 7,        /* W^T G z (float64 form: the coupling product D W c^-1 W^T G z up to its region sums) */
   SIM_PROBE_INTERP_FACE = 8,        /* W^T u */
   SIM_PROBE_MULTIDOT = 9,           /* Gram-Schmidt dot products */
   SIM_PROBE_UPDATE_NORM = 10,       /* Gram-Schmidt update and norm */

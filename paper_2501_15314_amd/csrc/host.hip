@@ -191,7 +191,7 @@ struct Carver {
 
 // The float64 form runs the coupling term on the matrix cores
 // (kernels_couple.hip: 36 + 13 us for an S~ product's pair at 256^3 with
-// 144000 points; 32 + 68 us from the touch lists).  The forms with float32
+// 144000 points; 22 + 57 us from the touch lists).  The forms with float32
 // or bfloat16 arithmetic inside keep the list kernels, bit for bit: their
 // roundings turn a last-bit change of a right-hand side into one near the
 // size of the solve's tolerance.

@@ -33,9 +33,10 @@
 // Bound by load latency and instruction issue, not bytes: 144000 points in a
 // 256^3 grid (about 25 MB) take 36 us for the product and 13 us for the
 // region sums, 300 points in 32^3 5.9 + 4.6 us; from the touch lists, which
-// stage a point about six times, 32 + 68 us and 7.3 + 6.7 us.  Points are
-// split into workgroups of 64 and not looped over: 55 us with one workgroup
-// per tile.
+// stage a point about six times, 22 + 57 us (32 + 68 us and 7.3 + 6.7 us
+// when this kernel was written, before the list kernels got faster).  Points
+// are split into workgroups of 64 and not looped over: 55 us with one
+// workgroup per tile.
 #include <hip/hip_ext.h>
 
 #include "internal.h"

@@ -42,16 +42,55 @@ __device__ __forceinline__ void ld_pair(const TV *p, double &a, double &b) {
   }
 }
 
+// wave_sum of NV values at once, in the order of its butterfly: at each step a
+// lane keeps half of its values and hands the other half to its partner, so
+// NV values take about NV + 5 exchanges, not 6 NV.  Afterwards v[0] is the sum
+// of value `i` of the lane, if i < NV (lanes that are left without one: NV).
+template <int M, int O, int NV>
+__device__ __forceinline__ void wave_sums_step(double (&v)[NV], int lane, int &i, int &held) {
+  constexpr int H = (M + 1) / 2;
+  if constexpr (M == 1) {
+    v[0] += __shfl_xor(v[0], O, 64);
+  } else {
+    const bool up = lane & O;
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+      const double hi = q + H < M ? v[q + H] : 0.0;
+      const double keep = up ? hi : v[q], give = up ? v[q] : hi;
+      v[q] = keep + __shfl_xor(give, O, 64);
+    }
+    i += up ? H : 0;
+    held = up ? held - H : held < H ? held : H;
+  }
+  if constexpr (O > 1) wave_sums_step<H, O / 2>(v, lane, i, held);
+}
+template <int NV>
+__device__ __forceinline__ int wave_sums(double (&v)[NV], int lane) {
+  static_assert(NV <= 64);
+  int i = 0, held = NV;
+  wave_sums_step<NV, 32>(v, lane, i, held);
+  return held > 0 ? i : NV;
+}
+
 // The number of vectors is a template parameter (1 .. MD_MAX): the loop over
 // them unrolls completely, so every load of a grid-stride step is issued
-// before the first product waits on one
+// before the first product waits on one.
+//
+// Bounded by the bytes of the vectors on a large grid (5.2 to 6.6 TB/s at 256^3)
+// and on a small one by the sums at the end of a workgroup: with a butterfly
+// of six exchanges for each vector 13 float64 vectors of 32^3 took 10.5 us,
+// with the shared one and no sums where there are no entries 3.8.
 template <typename TV, typename TW, int NV>
 __global__ void __launch_bounds__(RED_T) k_multidot(const TW *w, const TV *V, long long stride, long long n,
                                                     double *part) {
+  const long long n2 = n >> 1;
+  if ((long long)blockIdx.x * RED_T >= n2) {  // a grid with fewer entries than threads
+    if (threadIdx.x < NV) part[(long long)blockIdx.x * NV + threadIdx.x] = 0.0;
+    return;
+  }
   double acc[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-  const long long n2 = n >> 1;
   for (long long t = (long long)blockIdx.x * RED_T + threadIdx.x; t < n2; t += (long long)gridDim.x * RED_T) {
     double2 wv;
     ld_pair(w + 2 * t, wv.x, wv.y);
@@ -62,12 +101,8 @@ __global__ void __launch_bounds__(RED_T) k_multidot(const TW *w, const TV *V, lo
     for (int i = 0; i < NV; ++i) acc[i] += wv.x * a[i] + wv.y * b[i];
   }
   __shared__ double sh[4][NV];
-  int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    double v = wave_sum(acc[i]);
-    if (ln == 0) sh[wv][i] = v;
-  }
+  const int wv = threadIdx.x >> 6, i = wave_sums(acc, threadIdx.x & 63);
+  if (i < NV) sh[wv][i] = acc[0];
   __syncthreads();
   if (threadIdx.x < NV)
     part[(long long)blockIdx.x * NV + threadIdx.x] =
@@ -190,6 +225,8 @@ template hipError_t multidot<double, double>(const double *, const double *, lon
 // out[i] = sum_b part[b][i] over nblk blocks (chunked layout of multidot);
 // with host != null the sums are also written to that pinned host buffer
 // (read by the host after the stream is synchronised, no separate copy)
+// Bounded by the latency of one round of loads and the write to the host:
+// 3.0 -> 2.3 us with a thread's loads in flight together.
 __global__ void __launch_bounds__(RED_T) k_finalize(const double *part, int nblk, int nv, double *out,
                                                     double *host) {
   int i = blockIdx.x;
@@ -198,7 +235,16 @@ __global__ void __launch_bounds__(RED_T) k_finalize(const double *part, int nblk
   const double *pc = part + (long long)c0 * nblk;
   int col = i - c0;
   double v = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += RED_T) v += pc[(long long)b * nc + col];
+  for (int b = threadIdx.x; b < nblk; b += 4 * RED_T) {  // four loads in flight; the sums in their order
+    double t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = b + q * RED_T;
+      t[q] = pc[(long long)(c < nblk ? c : b) * nc + col];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v += b + q * RED_T < nblk ? t[q] : 0.0;
+  }
   __shared__ double sh[4];
   v = block_reduce(v, sh);
   if (threadIdx.x == 0) {

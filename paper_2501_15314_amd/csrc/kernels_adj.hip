@@ -30,49 +30,52 @@ __device__ __forceinline__ bool in_box(const Geo &g, const int x[3]) {
   return true;
 }
 
+// Sixteen lanes per point: lane (t0, t1) takes the W nodes along axis 2 of each
+// component, and a butterfly over the sixteen adds their sums.  Bounded by the
+// latency of the gathers: with one thread per point, which took its 192 nodes
+// one after the other, 10000 points in 128^3 cells took 70 us; now 17.
 template <int KER>
-__global__ void k_interp_dx(Geo g, int K, const double *X, const double *a3, const double *b, double scale,
-                            double *out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
+__global__ void __launch_bounds__(256) k_interp_dx(Geo g, int K, const double *X, const double *a3, const double *b,
+                                                   double scale, double *out) {
+  const int k = blockIdx.x * 16 + (threadIdx.x >> 4), lane = threadIdx.x & 15, t0 = lane >> 2, t1 = lane & 3;
+  if (k >= K) return;  // all sixteen lanes of the point
   constexpr int W = KerWidth<KER>::W;
   const double inv_h = 1.0 / g.h;
   const long long N = 2 * g.half;
   const double x[3] = {X[3 * k], X[3 * k + 1], X[3 * k + 2]};
   double ge[3] = {0.0, 0.0, 0.0};
-  for (int d = 0; d < 3; ++d) {
-    double w[3][4], dw[3][4];
-    int i0[3];
-    for (int a = 0; a < 3; ++a) {
-      double s;
-      i0[a] = support_start<KER>(x[a], inv_h, a == d, s);
-      for (int t = 0; t < W; ++t) {
-        const double r = s - (double)(i0[a] + t);
-        w[a][t] = phi<KER>(r);
-        dw[a][t] = dphi<KER>(r) * inv_h;
+  if (t0 < W && t1 < W) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      int i0[3];
+      double s[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) i0[a] = support_start<KER>(x[a], inv_h, a == d, s[a]);
+      const int i = wrapi(i0[0] + t0, g.n0), j = wrapi(i0[1] + t1, g.n1);
+      double v[W];
+#pragma unroll
+      for (int t2 = 0; t2 < W; ++t2) v[t2] = a3[d * N + sidx(g, i, j, wrapi(i0[2] + t2, g.n2))];
+      const double r0 = s[0] - (double)(i0[0] + t0), r1 = s[1] - (double)(i0[1] + t1);
+      const double w0 = phi<KER>(r0), w1 = phi<KER>(r1), d0 = dphi<KER>(r0) * inv_h, d1 = dphi<KER>(r1) * inv_h;
+      const double bd = b[3 * k + d];
+      double sw = 0.0, sd = 0.0;
+#pragma unroll
+      for (int t2 = 0; t2 < W; ++t2) {
+        const double r2 = s[2] - (double)(i0[2] + t2);
+        sw += v[t2] * phi<KER>(r2);
+        sd += v[t2] * (dphi<KER>(r2) * inv_h);
       }
+      ge[0] += bd * (d0 * w1 * sw);
+      ge[1] += bd * (w0 * d1 * sw);
+      ge[2] += bd * (w0 * w1 * sd);
     }
-    const double *ad = a3 + d * N;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int t0 = 0; t0 < W; ++t0) {
-      const int i = wrapi(i0[0] + t0, g.n0);
-      for (int t1 = 0; t1 < W; ++t1) {
-        const int j = wrapi(i0[1] + t1, g.n1);
-        for (int t2 = 0; t2 < W; ++t2) {
-          const int kk = wrapi(i0[2] + t2, g.n2);
-          const double v = ad[sidx(g, i, j, kk)];
-          s0 += v * dw[0][t0] * w[1][t1] * w[2][t2];
-          s1 += v * w[0][t0] * dw[1][t1] * w[2][t2];
-          s2 += v * w[0][t0] * w[1][t1] * dw[2][t2];
-        }
-      }
-    }
-    const double bd = b[3 * k + d];
-    ge[0] += bd * s0;
-    ge[1] += bd * s1;
-    ge[2] += bd * s2;
   }
-  for (int e = 0; e < 3; ++e) out[3 * k + e] += scale * ge[e];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) ge[e] += __shfl_xor(ge[e], o, 16);
+  }
+  if (lane < 3) out[3 * k + lane] += scale * (lane == 0 ? ge[0] : lane == 1 ? ge[1] : ge[2]);
 }
 
 // F_{a,d}(x) is zero through a wall: x_a = n_a - 1 on a wall axis a.
@@ -80,18 +83,17 @@ __device__ __forceinline__ bool flux_open(const Geo &g, int a, const int x[3]) {
   return !(geo_bc(g, a) && x[a] == geo_n(g, a) - 1);
 }
 
-__global__ void k_conv_adj(Geo g, const double *u3, const double *r3, double *out3) {
-  RowPos p;
-  if (!row_pos(g, p)) return;
+// component m at row position p
+template <int m>
+__device__ __forceinline__ double conv_adj(const Geo &g, const RowPos &p, const double *u3, const double *r3) {
   const long long N = 2 * g.half;
-  const int m = p.comp;
   const int y[3] = {p.i, p.j, p.k};
   double acc = 0.0;
   if (!(geo_bc(g, m) && y[m] == 0)) {
-    const double h = g.h;
     const double *um = u3 + m * N, *rm = r3 + m * N;
     // (1) a = d = m: F = C^2, C(x) = (u_m(x) + u_m(x + e_m)) / 2,
-    //     psi(x) = (r_m(x) - r_m(x + e_m)) / h; u_m(y) enters C(y), C(y - e_m)
+    //     psi(x) = r_m(x) - r_m(x + e_m) (over h); u_m(y) enters C(y), C(y - e_m)
+#pragma unroll
     for (int q = 0; q < 2; ++q) {
       int x[3] = {y[0], y[1], y[2]};
       x[m] -= q;
@@ -99,15 +101,17 @@ __global__ void k_conv_adj(Geo g, const double *u3, const double *r3, double *ou
       int xp[3] = {x[0], x[1], x[2]};
       xp[m] += 1;
       const double C = 0.5 * (fetch3(um, g, x) + fetch3(um, g, xp));
-      const double psi = (fetch3(rm, g, x) - fetch3(rm, g, xp)) / h;
+      const double psi = fetch3(rm, g, x) - fetch3(rm, g, xp);
       acc += 2.0 * C * 0.5 * psi;
     }
+#pragma unroll
     for (int o = 1; o < 3; ++o) {
       const int a = (m + o) % 3;
       // (2) d = m, flux along a: F = E1 E2, E1(x) = (u_m(x) + u_m(x + e_a)) / 2,
       //     E2(x) = (u_a(x + e_a) + u_a(x + e_a - e_m)) / 2,
-      //     psi(x) = (r_m(x) - r_m(x + e_a)) / h; u_m(y) enters E1(y), E1(y - e_a)
+      //     psi(x) = r_m(x) - r_m(x + e_a) (over h); u_m(y) enters E1(y), E1(y - e_a)
       const double *ua = u3 + a * N;
+#pragma unroll
       for (int q = 0; q < 2; ++q) {
         int x[3] = {y[0], y[1], y[2]};
         x[a] -= q;
@@ -117,15 +121,16 @@ __global__ void k_conv_adj(Geo g, const double *u3, const double *r3, double *ou
         int xam[3] = {xa[0], xa[1], xa[2]};
         xam[m] -= 1;
         const double E2 = 0.5 * (fetch3(ua, g, xa) + fetch3(ua, g, xam));
-        const double psi = (fetch3(rm, g, x) - fetch3(rm, g, xa)) / h;
+        const double psi = fetch3(rm, g, x) - fetch3(rm, g, xa);
         acc += 0.5 * E2 * psi;
       }
       // (3) component d = a, flux along m: F = E1 E2 with E1(x) = (u_d(x) + u_d(x + e_m)) / 2,
       //     E2(x) = (u_m(x + e_m) + u_m(x + e_m - e_d)) / 2,
-      //     psi(x) = (r_d(x) - r_d(x + e_m)) / h; u_m(y) enters E2 at
+      //     psi(x) = r_d(x) - r_d(x + e_m) (over h); u_m(y) enters E2 at
       //     x = y - e_m and x = y - e_m + e_d
       const int d = a;
       const double *ud = u3 + d * N, *rd = r3 + d * N;
+#pragma unroll
       for (int q = 0; q < 2; ++q) {
         int x[3] = {y[0], y[1], y[2]};
         x[m] -= 1;
@@ -134,12 +139,23 @@ __global__ void k_conv_adj(Geo g, const double *u3, const double *r3, double *ou
         int xm[3] = {x[0], x[1], x[2]};
         xm[m] += 1;
         const double E1 = 0.5 * (fetch3(ud, g, x) + fetch3(ud, g, xm));
-        const double psi = (fetch3(rd, g, x) - fetch3(rd, g, xm)) / h;
+        const double psi = fetch3(rd, g, x) - fetch3(rd, g, xm);
         acc += 0.5 * E1 * psi;
       }
     }
   }
-  out3[m * N + p.e] = acc;
+  return acc / g.h;  // the differences' 1 / h, once
+}
+
+// The component is that of the workgroup, so that the axes are constants.
+// Bounded by the index arithmetic of its 22 gathers: 128^3 cells take 206 us,
+// and took 318 with positions indexed along a variable axis and each
+// difference divided by h.
+__global__ void k_conv_adj(Geo g, const double *u3, const double *r3, double *out3) {
+  RowPos p;
+  if (!row_pos(g, p)) return;
+  const double v = p.comp == 0 ? conv_adj<0>(g, p, u3, r3) : p.comp == 1 ? conv_adj<1>(g, p, u3, r3) : conv_adj<2>(g, p, u3, r3);
+  out3[p.comp * 2 * g.half + p.e] = v;
 }
 
 }  // namespace
@@ -147,7 +163,7 @@ __global__ void k_conv_adj(Geo g, const double *u3, const double *r3, double *ou
 hipError_t interp_dx(int ker, const Geo &g, int K, const double *X, const double *a3, const double *b, double scale,
                      double *out, hipStream_t s) {
   if (K == 0) return hipSuccess;
-  dim3 grid((K + 127) / 128), block(128);
+  dim3 grid((K + 15) / 16), block(256);
   if (ker == KER_PESKIN4)
     hipLaunchKernelGGL(k_interp_dx<KER_PESKIN4>, grid, block, 0, s, g, K, X, a3, b, scale, out);
   else

@@ -315,18 +315,21 @@ constexpr int FIRST2_WAVES = 16;  // wavefronts on a compute unit (its registers
 bool mg_first2_fits(const Geo &g) {
   return g.hn2 % 2 == 0 && g.hn2 <= 256 && g.n1 >= 16 && g.n0 >= 4 && g.half < (1LL << 31);  // 32-bit byte offsets on the coarse grid
 }
-static First2Shape first2_shape(const Geo &g) {
+// pairs: a workgroup's stored rows and planes are whole pairs
+static First2Shape first2_shape(const Geo &g, bool pairs) {
   First2Shape s;
   s.bx = g.hn2 / 2;
   s.rows = 512 / s.bx;
   if (s.rows < 8) s.rows = 8;
   if (s.rows > 16) s.rows = 16;
+  if (pairs) s.rows &= ~1;
   const int ty = (g.n1 + s.rows - 3) / (s.rows - 2);
   // one round of workgroups on the 256 compute units, if that leaves them a
   // few planes each: the planes before and after a chunk are computed again
   const int slots = 256 * (FIRST2_WAVES / ((s.bx * s.rows + 63) / 64)), nch = slots / ty > 0 ? slots / ty : 1;
   s.chunk = (g.n0 + nch - 1) / nch;
   if (s.chunk < 2) s.chunk = 2;
+  if (pairs) s.chunk = (s.chunk + 1) & ~1;
   s.grid = dim3(ty, (g.n0 + s.chunk - 1) / s.chunk);
   return s;
 }
@@ -678,7 +681,8 @@ __global__ void __launch_bounds__(NT, 4) k_prolong_black(Geo g, T *x, const TB *
 // The march of k_first2 with the red values loaded: at plane k it forms
 // black(k), then the residuals of the red cells at k - 1, summed over pairs of
 // planes and, through LDS, pairs of rows (a workgroup stores whole pairs: its
-// stored rows and its chunk start at even places and are even in number).
+// stored rows and its chunk start at even places and are even in number, which
+// takes a row off a workgroup of 9, 11, 13 or 15).
 //
 // Bounded as k_first2.  Both passes before and this one after, float32, us:
 // 256^3 39.3 / 31.2, 384^3 141 / 88, 128^3 10.2 / 10.3.
@@ -843,7 +847,7 @@ __global__ void __launch_bounds__(NT, 4) k_black_restrict(Geo g, const T *x, con
 template <typename TB>
 hipError_t mg_smooth_first2(const Geo &g, float *x, const TB *b, hipStream_t s) {
   if (!mg_first2_fits(g)) return hipErrorInvalidValue;
-  const First2Shape f = first2_shape(g);
+  const First2Shape f = first2_shape(g, false);
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
   const size_t lds = 4 * sizeof(float) * f.rows * (g.hn2 + 2);
@@ -857,7 +861,7 @@ hipError_t mg_smooth_first2(const Geo &g, float *x, const TB *b, hipStream_t s) 
 template <typename TB>
 hipError_t mg_prolong_black(const Geo &g, float *x, const TB *b, const Geo &gc, const float *xc, hipStream_t s) {
   if (!mg_first2_fits(g)) return hipErrorInvalidValue;
-  First2Shape f = first2_shape(g);
+  First2Shape f = first2_shape(g, false);
   f.chunk = (f.chunk + 1) & ~1;  // chunks start at even planes
   f.grid.y = (g.n0 + f.chunk - 1) / f.chunk;
   hipEvent_t e0, e1;
@@ -877,9 +881,9 @@ template hipError_t mg_prolong_black<double>(const Geo &, float *, const double 
 template <typename TB>
 hipError_t mg_black_restrict(const Geo &g, const float *x, const TB *b, const Geo &gc, float *bc, hipStream_t s) {
   if (!mg_first2_fits(g)) return hipErrorInvalidValue;
-  First2Shape f = first2_shape(g);
-  f.chunk = (f.chunk + 1) & ~1;  // whole pairs of planes
-  f.grid.y = (g.n0 + f.chunk - 1) / f.chunk;
+  const First2Shape f = first2_shape(g, true);
+  // pairs of planes and rows stay inside one workgroup
+  if (g.n0 % 2 || g.n1 % 2 || f.rows % 2 || f.chunk % 2) return hipErrorInvalidValue;
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
   const size_t lds = sizeof(float) * f.rows * (4 * (g.hn2 + 2) + 2 * f.bx);

@@ -379,7 +379,9 @@ sim_status sim_schur_spectrum(sim_t sim, int32_t exact, const double *d_v0, int3
  * multigrid level runs either the plane-march kernels (the first five
  * classes) or, at most 64^3 cells by default, the two tile kernels
  * (IBSCHUR_MG_TILE_CELLS in the environment at sim_create sets that bound;
- * 0: no tile levels). */
+ * 0: no tile levels).  In float32 a plane-march level runs some neighbouring
+ * passes as one, with the same bits (IBSCHUR_MG_FUSED=0 in the environment at
+ * sim_create: none). */
 enum {
   SIM_PROBE_SMOOTH = 0,             /* red-black Gauss-Seidel half sweep launched by itself, plane-march levels */
   SIM_PROBE_SMOOTH_FIRST = 1,       /* first sweep from zero, plane-march levels; in float32 with the red half sweep after it */

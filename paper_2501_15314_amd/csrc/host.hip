@@ -77,6 +77,7 @@ struct sim_s {
   long long ntiles = 0;
   int Kmax = 0, K = 0, nb = 0;
   bool fp32 = false;
+  bool mg_fused = true;  // mg_fused_setting() at sim_create
   int ker = 0;
   double c = 0.5;
   double t = 0.0;
@@ -225,6 +226,13 @@ long long mg_tile_cells_setting() {
   char *end = nullptr;
   const long long v = strtoll(e, &end, 10);
   return (end && *end == '\0' && v >= 0) ? v : MG_TILE_CELLS_DEFAULT;
+}
+// IBSCHUR_MG_FUSED=0 in the environment at sim_create: the marched levels of a
+// float32 cycle run every half sweep, restriction and prolongation as a pass of
+// its own; the fused ones give the same bits.
+bool mg_fused_setting() {
+  const char *e = getenv("IBSCHUR_MG_FUSED");
+  return !(e && e[0] == '0');
 }
 // Whether level l of the hierarchy dims (3 entries per level) runs as a tile
 // level: a V-cycle preconditioner, a next level of half the edges, edges that
@@ -738,7 +746,8 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
   auto coarse_bytes = [&](int l) { return cells(l) * (tb(l) + t); };  // b read, x written
   auto first_bytes = [&](int l, bool store_red) { return cells(l) * (tb(l) + (store_red ? t : 0.5 * t)); };
   // the first black and the red half sweep after it run as one pass
-  auto first_two = [&](int l) { return std::is_same_v<T, float> && c.mg_pre > 1 && mg_first2_fits(s->lv[l].g); };
+  auto fused = [&](int l) { return std::is_same_v<T, float> && s->mg_fused && mg_first2_fits(s->lv[l].g); };
+  auto first_two = [&](int l) { return fused(l) && c.mg_pre > 1; };
   auto half_bytes = [&](int l) { return cells(l) * (0.5 * t + 0.5 * tb(l) + 0.5 * t); };
   auto restrict_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
   auto prolong_bytes = [&](int l) { return cells(l) * t + cells(l + 1) * t; };
@@ -748,9 +757,7 @@ sim_status vcycle(sim_t s, const TV *v, T *z) {
   // 39.3 for the two, and 25.2 against 34.5; at 128^3 10.3 against 10.2 and 10.2
   // against 10.6).  The black values of the first are lost: the second, or its
   // two passes, form them anew.
-  auto large = [&](int l) {
-    return std::is_same_v<T, float> && mg_first2_fits(s->lv[l].g) && cells(l) > 128.0 * 128.0 * 128.0;
-  };
+  auto large = [&](int l) { return fused(l) && cells(l) > 128.0 * 128.0 * 128.0; };
   auto black_prolong = [&](int l) { return large(l) && c.mg_post > 0; };
   auto prolong_black_bytes = [&](int l) { return cells(l) * (t + 0.5 * tb(l)) + cells(l + 1) * t; };
   auto black_restrict = [&](int l) { return large(l) && c.mg_pre > 1 && c.mg_post > 0; };
@@ -1803,6 +1810,7 @@ sim_status sim_create(const sim_config *cfg, void *d_workspace, size_t bytes, in
   s->ntiles = (long long)s->nt0 * s->nt1 * s->nt2;
   s->Kmax = (int)max_points;
   s->fp32 = cfg->precision == SIM_PREC_FP32MG;
+  s->mg_fused = mg_fused_setting();
   s->ker = cfg->delta;
   s->c = cfg->lump_c;
   if (hipHostMalloc((void **)&s->hpin, 64 * 1024) != hipSuccess) {

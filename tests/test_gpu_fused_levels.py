@@ -5,7 +5,12 @@ restriction's pairing takes one off among them, and in workgroups of more than
 512 threads.
 
 Oracle: the array cycle of test_gpu_cycle, at its tolerance for float32 (a few
-hundred roundings of numbers no larger than the result by a factor of ten)."""
+hundred roundings of numbers no larger than the result by a factor of ten); and
+the separate passes, which give every cell the same operations in the same
+order: the same bits."""
+import contextlib
+import os
+
 import numpy as np
 import pytest
 
@@ -29,9 +34,23 @@ def _config(n, bc, coarsest, sweeps):
 
 def _precond(cfg, b):
     sim = Sim(cfg, 1)
-    z = sim.apply("precond", b).cpu().numpy()
+    sim.probe("smooth")
+    z, half_sweeps = sim.apply("precond", b).cpu().numpy(), sim.probe_read("smooth")[0]  # launched by themselves
     sim.close()
-    return z
+    return z, half_sweeps
+
+
+@contextlib.contextmanager
+def _separate_passes():
+    old = os.environ.get("IBSCHUR_MG_FUSED")
+    os.environ["IBSCHUR_MG_FUSED"] = "0"
+    try:
+        yield
+    finally:
+        if old is None:
+            del os.environ["IBSCHUR_MG_FUSED"]
+        else:
+            os.environ["IBSCHUR_MG_FUSED"] = old
 
 
 @pytest.mark.parametrize("n,coarsest,sweeps", [
@@ -46,5 +65,52 @@ def test_cycle_by_row_length(n, coarsest, sweeps, bc):
     b = np.random.default_rng(n[2]).standard_normal(n)
     b -= b.mean()
     cfg = _config(n, bc, coarsest, sweeps)
-    z, ref = _precond(cfg, b), _cycle(b, cfg.h, bc, coarsest, *sweeps)
+    z, ref = _precond(cfg, b)[0], _cycle(b, cfg.h, bc, coarsest, *sweeps)
     assert rel(z - z.mean(), ref - ref.mean()) < 1e-4
+
+
+@pytest.mark.parametrize("n,coarsest,sweeps", [
+    ((96, 112, 224), 14, (2, 1)),
+    ((96, 112, 208), 104, (2, 1)),   # 9 rows by threads, above one exact coarse solve
+    ((112, 128, 176), 88, (2, 1)),   # 11 rows
+    ((128, 112, 160), 10, (3, 2)),
+    ((112, 112, 192), 12, (2, 2)),
+    ((144, 128, 128), 9, (2, 1)),    # 16 rows
+    ((80, 96, 320), 20, (2, 1)),
+    ((48, 96, 512), 16, (2, 1)),     # 8 rows of 128 threads
+    ((144, 128, 128), 9, (1, 1)),    # of the fused passes only the prolongation's
+    ((144, 128, 128), 9, (2, 0)),    # only the first one
+    ((64, 64, 96), 12, (2, 1)),      # levels of at most 128^3 cells: the first one
+    ((32, 32, 288), 18, (2, 1)),
+])
+@pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
+def test_fused_passes_give_the_bits_of_separate_ones(n, coarsest, sweeps, bc):
+    b = np.random.default_rng(n[2]).standard_normal(n)
+    b -= b.mean()
+    cfg = _config(n, bc, coarsest, sweeps)
+    z, few = _precond(cfg, b)
+    with _separate_passes():
+        ref, all_ = _precond(cfg, b)
+    assert np.array_equal(z, ref) and few < all_
+
+
+@pytest.mark.parametrize("bc", [(P, P, P), (N, P, F)])
+def test_fused_passes_in_a_solve(bc):
+    # the cycle on the float32 vectors of the Krylov iteration
+    n, K, radius = (96, 112, 224), 600, 0.2
+    cfg = _config(n, bc, 14, (2, 1))
+    cfg.lump_c, cfg.krylov_rtol = wl.lump_constant(cfg.delta, cfg.h, K, radius), 1e-8
+    body = wl.Body(center=np.array([0.37, 0.44, 0.9]), vel=np.zeros(3), omega=np.zeros(3), radius=radius, n_points=K)
+    rp, rf = wl.random_schur_rhs(3, n, K)
+
+    def solve():
+        sim = Sim(cfg, K)
+        sim.set_bodies([body], wl.fibonacci_offsets(K, radius))
+        p, phi, st = sim.solve_schur(rp, rf)
+        sim.close()
+        return p.cpu().numpy(), phi.cpu().numpy(), st.iters
+
+    got = solve()
+    with _separate_passes():
+        ref = solve()
+    assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1]) and got[2] == ref[2]

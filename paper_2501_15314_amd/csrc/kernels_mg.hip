@@ -326,7 +326,12 @@ static First2Shape first2_shape(const Geo &g, bool pairs) {
   const int ty = (g.n1 + s.rows - 3) / (s.rows - 2);
   // one round of workgroups on the 256 compute units, if that leaves them a
   // few planes each: the planes before and after a chunk are computed again
-  const int slots = 256 * (FIRST2_WAVES / ((s.bx * s.rows + 63) / 64)), nch = slots / ty > 0 ? slots / ty : 1;
+  // (the wavefronts of a workgroup go round the four SIMDs, so five take the
+  // room of eight: 256 x 256 x 80 cells with 15 wavefronts on a compute unit
+  // counted on 98.5 us a cycle, with 10 82.0; the passes one by one 91.6)
+  int waves = (s.bx * s.rows + 63) / 64;
+  if (waves > 4) waves = (waves + 3) & ~3;
+  const int slots = 256 * (FIRST2_WAVES / waves), nch = slots / ty > 0 ? slots / ty : 1;
   s.chunk = (g.n0 + nch - 1) / nch;
   if (s.chunk < 2) s.chunk = 2;
   if (pairs) s.chunk = (s.chunk + 1) & ~1;

@@ -73,6 +73,7 @@ def test_cycle_by_row_length(n, coarsest, sweeps, bc):
     ((96, 112, 224), 14, (2, 1)),
     ((96, 112, 208), 104, (2, 1)),   # 9 rows by threads, above one exact coarse solve
     ((112, 128, 176), 88, (2, 1)),   # 11 rows
+    ((128, 256, 80), 128, (2, 1)),   # 16 rows of 20 threads: five wavefronts
     ((128, 112, 160), 10, (3, 2)),
     ((112, 112, 192), 12, (2, 2)),
     ((144, 128, 128), 9, (2, 1)),    # 16 rows

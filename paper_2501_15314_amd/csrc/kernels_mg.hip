@@ -303,6 +303,11 @@ __global__ void __launch_bounds__(256) k_prolong(Geo gf, T *xf, Geo gc, const T 
 // passes) and after, us: 128^3 12.5 / 10.1, 256^3 41.2 / 29.9, 384^3 136 / 82.
 // In float64 its registers leave half the wavefronts or spill (256^3: 76.7
 // before, 75.6 one plane ahead, 192 two ahead), so that form keeps two passes.
+// With a float64 right-hand side the float32 form holds it two planes ahead only
+// with spills, which pay in workgroups of more than 512 threads: a cycle with this
+// pass less one with the two separate ones, one and two planes ahead, us:
+// 256 x 256 x 64 -0.8 / +1.7, 256^3 -5.9 / -4.3, rows of 384 -4.3 / -23.9, of 512
+// -22.7 / -44.0.
 // Chunks of 16 planes in one and a third rounds of workgroups took 34.4 us at
 // 256^3, and neighbouring row tiles on one XCD no less than spread ones.
 struct First2Shape {
@@ -341,6 +346,8 @@ static First2Shape first2_shape(const Geo &g, bool pairs) {
 
 template <typename T, typename TB, int NT>
 __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, double h2, int chunk) {
+  // planes that operands are loaded ahead of their use
+  constexpr int AH = sizeof(TB) == 4 || NT > 512 ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const int BX = blockDim.x, rows = blockDim.y, W = g.hn2 + 2, TS = rows * W;
   T *lds = (T *)lds_raw;  // [buffer][red, black][rows][W]
@@ -402,8 +409,8 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
   auto ldr = [&](long long o) { return ld2<T>(br + o, rw * (unsigned)sizeof(TB)); };
   auto lde = [&](long long o) { return ld2<T>(br + o, ew * (unsigned)sizeof(TB)); };
   auto ldk = [&](long long o) { return ld2<T>(bk + o, rw * (unsigned)sizeof(TB)); };
-  // offsets of the planes k + 2 and k + 3, and of k, advanced by addition
-  long long o2 = plane(i0 + 1), o3 = plane(i0 + 2), ok = (i0 - 2) * P;
+  // offsets of the planes k + AH and k + AH + 1, and of k, advanced by addition
+  long long o2 = plane(i0 - 1 + AH), o3 = plane(i0 + AH), ok = (i0 - 2) * P;
   auto first = [&](V2<T> v, const T (&c)[2]) { return V2<T>{mul_rn(mul_rn(th2, v.x), c[0]), mul_rn(mul_rn(th2, v.y), c[1])}; };
   // a pair into an LDS plane, with the row's ends (periodic: the other end)
   auto put = [&](T *t, const V2<T> &v) {
@@ -426,7 +433,7 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
     return V2<T>{T(fma(th2, bv.x, sx) * c[0]), T(fma(th2, bv.y, sy) * c[1])};
   };
   // Plane k (parity index f of the black cells there, which is that of the red
-  // ones at k - 1 and k + 1).  Operands are loaded two planes before their use
+  // ones at k - 1 and k + 1).  Operands are loaded AH planes before their use
   // (few waves fit a compute unit): q holds b_red of plane k at k & 7, bb and be
   // b_black and the red right-hand side of the row beyond at k & 3; r0 and kk the
   // first red and the black values at k & 3.  All indices are known to the
@@ -449,11 +456,11 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
     }
   };
   auto step = [&](int k, int u, int f) {
-    q[(u + 3) & 7] = ldr(o3);
-    bb[(u + 2) & 3] = ldk(o2);
-    be[(u + 2) & 3] = lde(o2);
+    q[(u + AH + 1) & 7] = ldr(o3);
+    bb[(u + AH) & 3] = ldk(o2);
+    be[(u + AH) & 3] = lde(o2);
     o2 = o3;
-    const int nx = k + 4;
+    const int nx = k + AH + 2;
     if (nx == (g.bc0 ? 0 : g.n0)) o3 = 0;
     else if (nx > 0 && nx < g.n0 + (g.bc0 ? 0 : 8)) o3 += P;
     ok += P;
@@ -473,9 +480,11 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
   q[1] = ldr(plane(i0));
   bb[0] = ldk(plane(i0 - 1));
   be[0] = lde(plane(i0 - 1));
-  q[2] = ldr(plane(i0 + 1));
-  bb[1] = ldk(plane(i0));
-  be[1] = lde(plane(i0));
+  if (AH == 2) {
+    q[2] = ldr(plane(i0 + 1));
+    bb[1] = ldk(plane(i0));
+    be[1] = lde(plane(i0));
+  }
   kk[2] = kk[3] = V2<T>{T(0), T(0)};
   count(std::true_type{}, i0 - 2, 0, c);
   r0[3] = first(qm, c);

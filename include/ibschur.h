@@ -385,7 +385,7 @@ sim_status sim_schur_spectrum(sim_t sim, int32_t exact, const double *d_v0, int3
 enum {
   SIM_PROBE_SMOOTH = 0,             /* red-black Gauss-Seidel half sweep launched by itself, plane-march levels */
   SIM_PROBE_SMOOTH_FIRST = 1,       /* first sweep from zero, plane-march levels; in float32 with the red half sweep after it */
-  SIM_PROBE_RESTRICT = 2,           /* residual + restriction, plane-march levels; in float32 above 128^3 cells with the black half sweep before it */
+  SIM_PROBE_RESTRICT = 2,           /* residual + restriction, plane-march levels; in float32 above 128^3 cells (float64 right-hand side: from 192^3) with the black half sweep before it */
   SIM_PROBE_PROLONG = 3,            /* prolongation + correction, plane-march levels; in float32 above 128^3 cells with the black half sweep after it */
   SIM_PROBE_LAPLACIAN = 4,          /* L z inside the S~ product */
   SIM_PROBE_SPREAD_DIV = 5,         /* D W q on the active tiles (float64 form: the region sums of the coupling product) */

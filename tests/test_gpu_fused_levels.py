@@ -53,14 +53,17 @@ def _separate_passes():
             os.environ["IBSCHUR_MG_FUSED"] = old
 
 
-@pytest.mark.parametrize("n,coarsest,sweeps", [
-    ((96, 112, 224), 14, (2, 1)),   # 9 rows by threads, 8 with whole pairs
-    ((112, 96, 224), 14, (3, 2)),
-    ((128, 112, 160), 10, (2, 2)),  # 12 rows
-    ((112, 112, 192), 12, (2, 1)),  # 10 rows
-    ((80, 96, 320), 20, (2, 1)),    # 8 rows of 80 threads
+# the caller's float64 right-hand side takes the fused restriction from 192^3
+# cells on
+@pytest.mark.parametrize("n,coarsest,sweeps,bc", [
+    ((192, 176, 224), 14, (2, 1), (P, P, P)),  # 9 rows by threads, 8 with whole pairs
+    ((192, 176, 224), 14, (2, 1), (N, P, F)),
+    ((176, 192, 224), 14, (3, 2), (F, N, N)),
+    ((256, 192, 160), 16, (2, 2), (N, P, F)),  # 12 rows
+    ((224, 192, 192), 14, (2, 1), (F, N, N)),  # 10 rows
+    ((160, 160, 320), 20, (2, 1), (P, P, P)),  # 8 rows of 80 threads
+    ((160, 160, 320), 20, (2, 1), (N, P, F)),
 ])
-@pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
 def test_cycle_by_row_length(n, coarsest, sweeps, bc):
     b = np.random.default_rng(n[2]).standard_normal(n)
     b -= b.mean()
@@ -69,39 +72,42 @@ def test_cycle_by_row_length(n, coarsest, sweeps, bc):
     assert rel(z - z.mean(), ref - ref.mean()) < 1e-4
 
 
-@pytest.mark.parametrize("n,coarsest,sweeps", [
-    ((96, 112, 224), 14, (2, 1)),
-    ((96, 112, 208), 104, (2, 1)),   # 9 rows by threads, above one exact coarse solve
-    ((112, 128, 176), 88, (2, 1)),   # 11 rows
-    ((128, 256, 80), 128, (2, 1)),   # 16 rows of 20 threads: five wavefronts
-    ((128, 112, 160), 10, (3, 2)),
-    ((112, 112, 192), 12, (2, 2)),
-    ((144, 128, 128), 9, (2, 1)),    # 16 rows
-    ((80, 96, 320), 20, (2, 1)),
-    ((48, 96, 512), 16, (2, 1)),     # 8 rows of 128 threads
-    ((144, 128, 128), 9, (1, 1)),    # of the fused passes only the prolongation's
-    ((144, 128, 128), 9, (2, 0)),    # only the first one
-    ((64, 64, 96), 12, (2, 1)),      # levels of at most 128^3 cells: the first one
-    ((32, 32, 288), 18, (2, 1)),
+@pytest.mark.parametrize("n,coarsest,sweeps,saved", [  # saved: half sweeps without a launch of their own, at least
+    ((192, 176, 224), 14, (2, 1), 3),
+    ((256, 160, 208), 128, (2, 1), 3),  # 9 rows by threads, above one exact coarse solve
+    ((224, 224, 176), 112, (2, 1), 3),  # 11 rows
+    ((256, 352, 80), 176, (2, 1), 3),   # 16 rows of 20 threads: five wavefronts
+    ((256, 192, 160), 16, (3, 2), 3),
+    ((224, 192, 192), 14, (2, 2), 3),
+    ((256, 256, 128), 16, (2, 1), 3),   # 16 rows
+    ((160, 160, 320), 20, (2, 1), 3),
+    ((128, 128, 512), 32, (2, 1), 3),   # 8 rows of 128 threads
+    ((144, 128, 128), 9, (2, 1), 2),    # all but the restriction's
+    ((96, 112, 224), 14, (2, 1), 2),
+    ((144, 128, 128), 9, (1, 1), 1),    # only the prolongation's
+    ((144, 128, 128), 9, (2, 0), 1),    # only the first one
+    ((64, 64, 96), 12, (2, 1), 1),      # levels of at most 128^3 cells: the first one
+    ((32, 32, 288), 18, (2, 1), 1),
 ])
 @pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
-def test_fused_passes_give_the_bits_of_separate_ones(n, coarsest, sweeps, bc):
+def test_fused_passes_give_the_bits_of_separate_ones(n, coarsest, sweeps, saved, bc):
     b = np.random.default_rng(n[2]).standard_normal(n)
     b -= b.mean()
     cfg = _config(n, bc, coarsest, sweeps)
     z, few = _precond(cfg, b)
     with _separate_passes():
         ref, all_ = _precond(cfg, b)
-    assert np.array_equal(z, ref) and few < all_
+    assert np.array_equal(z, ref) and all_ - few >= saved
 
 
+@pytest.mark.parametrize("n,coarsest", [((96, 112, 224), 14), ((80, 96, 320), 20), ((144, 128, 128), 9)])
 @pytest.mark.parametrize("bc", [(P, P, P), (N, P, F)])
-def test_fused_passes_in_a_solve(bc):
+def test_fused_passes_in_a_solve(n, coarsest, bc):
     # the cycle on the float32 vectors of the Krylov iteration
-    n, K, radius = (96, 112, 224), 600, 0.2
-    cfg = _config(n, bc, 14, (2, 1))
+    K, radius = 600, 0.2
+    cfg = _config(n, bc, coarsest, (2, 1))
     cfg.lump_c, cfg.krylov_rtol = wl.lump_constant(cfg.delta, cfg.h, K, radius), 1e-8
-    body = wl.Body(center=np.array([0.37, 0.44, 0.9]), vel=np.zeros(3), omega=np.zeros(3), radius=radius, n_points=K)
+    body = wl.Body(center=np.array([0.3, 0.37, 0.6]), vel=np.zeros(3), omega=np.zeros(3), radius=radius, n_points=K)
     rp, rf = wl.random_schur_rhs(3, n, K)
 
     def solve():

@@ -92,11 +92,12 @@ __device__ __forceinline__ void st2(T *p, unsigned off, T a, T b) {
 // a / d for a divisor whose correctly rounded reciprocal r = 1 / d is at hand:
 // one fused remainder step gives the correctly rounded quotient (Markstein's
 // theorem; a and the quotient normal numbers), the same bits as the division
-// at 3 operations instead of about 10.  Infinite quotients stay infinite.
+// at 3 operations instead of about 10.  Infinite quotients, whose remainder is
+// infinite or NaN, stay infinite.
 template <typename T>
 __device__ __forceinline__ T div_by(T a, T d, T r) {
   const T q = a * r, e = fma(-q, d, a);
-  return e == e ? fma(e, r, q) : q;
+  return __builtin_isfinite(e) ? fma(e, r, q) : q;
 }
 
 // Coordinate wrap for periodic axes; -1 if outside a wall box.

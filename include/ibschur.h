@@ -388,7 +388,7 @@ enum {
   SIM_PROBE_RESTRICT = 2,           /* residual + restriction, plane-march levels; in float32 above 128^3 cells (float64 right-hand side: from 192^3) with the black half sweep before it */
   SIM_PROBE_PROLONG = 3,            /* prolongation + correction, plane-march levels; in float32 above 128^3 cells with the black half sweep after it */
   SIM_PROBE_LAPLACIAN = 4,          /* L z inside the S~ product */
-  SIM_PROBE_SPREAD_DIV = 5,         /* D W q on the active tiles (float64 form: the region sums of the coupling product) */
+  SIM_PROBE_SPREAD_DIV = 5,         /* D W q on the active tiles (float64 form, unless its points are scattered: the region sums of the coupling product) */
   SIM_PROBE_SPREAD_FACE = 6,        /* W q on the active tiles */
   SIM_PROBE_INTERP_GRAD = 7,        /* W^T G z (float64 form: the coupling product D W c^-1 W^T G z up to its region sums) */
   SIM_PROBE_INTERP_FACE = 8,        /* W^T u */

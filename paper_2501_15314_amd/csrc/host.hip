@@ -107,6 +107,7 @@ struct sim_s {
   int2 *PARTS = nullptr;
   double *REGION = nullptr;
   int nitems = 0;
+  bool couple = false;  // these carry the coupling term of the last placement, not the touch lists
   int nnz = 0;           // launch count of NZT
   int ntouch = 0;
   BodyDev *BODIES = nullptr;
@@ -192,7 +193,8 @@ struct Carver {
 
 // The float64 form runs the coupling term on the matrix cores
 // (kernels_couple.hip: 36 + 13 us for an S~ product's pair at 256^3 with
-// 144000 points; 22 + 57 us from the touch lists).  The forms with float32
+// 144000 points; 22 + 57 us from the touch lists), unless a placement scatters
+// the points over too many tiles (couple_pays).  The forms with float32
 // or bfloat16 arithmetic inside keep the list kernels, bit for bit: their
 // roundings turn a last-bit change of a right-hand side into one near the
 // size of the solve's tolerance.
@@ -646,6 +648,7 @@ sim_status place_and_bin(sim_t s, const std::vector<BodyDev> &bd) {
   memcpy(&M, (int *)s->hpin + 1, sizeof(int));
   s->nitems = 0;
   if (cpl) memcpy(&s->nitems, (int *)s->hpin + 2, sizeof(int));
+  s->couple = cpl && couple_pays(s->K, nz, s->nitems, na);
   if (M > s->tl_cap) return fail(s, SIM_EDEVICE, "touch list overflow");
   CKH(touch_tiles(s->ker, s->g, s->nt0, s->nt1, s->nt2, na, nullptr, s->ACTIVE, s->TSTART, s->XS, nullptr,
                   s->TLSTART, s->TLIST, st));
@@ -684,12 +687,12 @@ Coupling coupling(const sim_s *s) {
 
 // out = alpha W^T G z + beta y and out += alpha D W q, float64
 hipError_t points_grad(sim_t s, const double *z, double alpha, const double *y, double beta, double *out) {
-  if (couple_on_matrix_cores(&s->cfg)) return couple_interp(s->g, coupling(s), z, alpha, y, beta, out, s->st);
+  if (s->couple) return couple_interp(s->g, coupling(s), z, alpha, y, beta, out, s->st);
   return interp_grad<double>(s->ker, s->g, s->nt1, s->nt2, s->nnz, s->NZT, s->TSTART, s->XS, z, alpha, y, beta, out,
                              s->st);
 }
 hipError_t points_spread_div(sim_t s, const double *q, double alpha, double *out) {
-  if (couple_on_matrix_cores(&s->cfg)) return couple_spread(s->g, coupling(s), q, alpha, out, s->st);
+  if (s->couple) return couple_spread(s->g, coupling(s), q, alpha, out, s->st);
   return band_apply(s->ker, true, s->g, s->nt1, s->nt2, s->nactive, s->ACTIVE, s->TLSTART, s->TLIST, s->XS, q, alpha,
                     out, s->st);
 }
@@ -718,7 +721,7 @@ sim_status schur_matvec(sim_t s, const T *z, TW *w) {
     CKH((lap_apply<T, TW>(s->g, z, w, s->st)));
   }
   if constexpr (std::is_same<T, double>::value) {
-    if (couple_on_matrix_cores(&s->cfg)) {
+    if (s->couple) {
       CKH(couple_product(s->g, coupling(s), z, -1.0 / s->c, w, s->st));
       return SIM_OK;
     }

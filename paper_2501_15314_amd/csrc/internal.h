@@ -279,6 +279,7 @@ struct Coupling {
 };
 long long couple_max_items(long long K, long long ntiles);
 size_t couple_region_bytes(long long K, long long ntiles);
+bool couple_pays(long long K, long long tiles, long long items, long long active);
 // the workgroups of the n non-empty tiles listed in tiles (tile-index order),
 // their count in *total; parts holds count 0 for every tile before
 hipError_t couple_items(int n, const int *tiles, const int *tstart, int4 *items, int2 *parts, int *total,

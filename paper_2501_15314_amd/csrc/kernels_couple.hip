@@ -108,6 +108,23 @@ size_t couple_region_bytes(long long K, long long ntiles) {
   return sizeof(double) * CR3 * (size_t)(m < CBATCH ? m : CBATCH);
 }
 
+// Whether these kernels beat the touch-list ones on a placement of K points in
+// `tiles` point tiles, cut into `items` workgroups, whose supports reach
+// `active` tiles.  They pay for every workgroup whatever its points (a region
+// staged, written and read back) and for the active tiles once a batch; the
+// lists for every active tile more, and for the pairs of point and tile.  The
+// costs in ns are a fit to products of a large grid; measured, these kernels and
+// the lists, us: spheres of 144000 points in 256^3 cells 49 / 79; scattered
+// points in 64^3 cells, 1000 16.2 / 17.9, 20000 34.8 / 32.1, 100000 48 / 65; in
+// 128^3, 10000 79 / 103, 100000 253 / 169, 1000000 388 / 531; in 256^3, 10000 158 /
+// 232, 100000 (six batches) 2102 / 883, 1000000 (16) 5899 / 1454.
+bool couple_pays(long long K, long long tiles, long long items, long long active) {
+  const long long batches = items > 0 ? (items + CBATCH - 1) / CBATCH : 1;
+  const double here = 6.3 * items + 0.12 * K + (0.8 + 1.1 * (batches - 1)) * active;
+  const double lists = 1.55 * tiles + 0.4 * K + 2.75 * active;
+  return here <= lists;
+}
+
 //   CP_PRODUCT: region = D W W^T G z (times h), z a cell field
 //   CP_INTERP:  out = alpha W^T G z + beta y
 //   CP_SPREAD:  region = D W q (times h)

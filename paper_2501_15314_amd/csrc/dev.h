@@ -27,7 +27,8 @@ struct Geo {
   int n0, n1, n2, hn2;
   long long half;   // n0*n1*hn2
   int bc0, bc1, bc2;  // 0 periodic, 1 no-slip wall, 2 free-slip wall (Neumann for cell fields)
-  int mbx, mby, mch;  // workgroup shape and planes per workgroup of the plane-marching kernels (make_geo)
+  // workgroup shape of the plane-marching kernels, planes per workgroup of those on one field and on three (make_geo)
+  int mbx, mby, mch, mch3;
   double h, h2;     // cell width and its square
 };
 

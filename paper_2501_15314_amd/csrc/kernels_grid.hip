@@ -46,6 +46,11 @@ Geo make_geo(int n0, int n1, int n2, int bc0, int bc1, int bc2, double h, int ma
   const long long xy = (long long)((g.hn2 + 2 * g.mbx - 1) / (2 * g.mbx)) * (g.n1 / g.mby);
   g.mch = MARCH_CH;
   while (g.mch > 1 && xy * ((g.n0 + g.mch - 1) / g.mch) < march_min_blocks) g.mch >>= 1;
+  // one plane pays three planes' loads, and all that a march finds before it
+  // starts, for itself: a launch on three fields takes two if that leaves it
+  // three quarters of those workgroups (float64 momentum solve with one and with
+  // two: 80^3 cells 401 / 336 us, 96^3 498 / 416)
+  g.mch3 = g.mch == 1 && 4 * xy * ((g.n0 + 1) / 2) >= march_min_blocks ? 2 : g.mch;
   g.h = h; g.h2 = h * h;
   return g;
 }

@@ -2,7 +2,7 @@
 //
 // A workgroup owns a tile of BY rows (axis 1) x 2*BX in-row indices m
 // (axis 2, two per thread, accessed as 2-vectors) and marches over a chunk of
-// planes along axis 0 (Geo::mbx, mby, mch).  The x-neighbours of a cell come from a
+// planes along axis 0 (Geo::mbx, mby, mch, mch3).  The x-neighbours of a cell come from a
 // register window over three planes, the y- and z-neighbours from an LDS copy
 // of the current plane with a one-cell halo.  BX divides hn2/2 and BY divides
 // n1, so no workgroup is partial and every halo cell is loaded.
@@ -47,7 +47,8 @@ inline MarchShape march_shape(const Geo &g, int ncomp) {
   s.bx = g.mbx;
   s.by = g.mby;
   s.block = dim3(s.bx, s.by, 1);
-  int nch = (g.n0 + g.mch - 1) / g.mch;
+  const int len = ncomp == 3 ? g.mch3 : g.mch;
+  int nch = (g.n0 + len - 1) / len;
   s.grid = dim3(g.hn2 / (2 * s.bx), g.n1 / s.by, nch * ncomp);
   return s;
 }
@@ -139,7 +140,8 @@ __device__ __forceinline__ MarchBlock march_block(bool xcd) {
 struct MarchPos {
   int tx, ty, m0, j, i0, i1, comp, mbase, jbase;
 };
-__device__ __forceinline__ MarchPos march_pos(const Geo &g, bool xcd) {
+// len: planes per workgroup
+__device__ __forceinline__ MarchPos march_pos(const Geo &g, int len, bool xcd) {
   MarchPos p;
   const MarchBlock mb = march_block(xcd);
   p.tx = threadIdx.x;
@@ -148,7 +150,6 @@ __device__ __forceinline__ MarchPos march_pos(const Geo &g, bool xcd) {
   p.jbase = mb.y * blockDim.y;
   p.m0 = p.mbase + 2 * threadIdx.x;
   p.j = p.jbase + threadIdx.y;
-  const int len = g.mch;
   int nch = (g.n0 + len - 1) / len;
   p.comp = mb.z / nch;
   int ch = mb.z - p.comp * nch;
@@ -307,7 +308,7 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
   constexpr bool FIRSTM = MODE == SW_FIRST || MODE == SW_HFIRST || MODE == SW_FIRST1;
   constexpr bool HELMM = MODE == SW_HELM || MODE == SW_HFIRST;
   __shared__ T tile[2][MARCH_TILE];
-  const MarchPos p = march_pos(g, HELMM);
+  const MarchPos p = march_pos(g, HELMM ? g.mch3 : g.mch, HELMM);
   const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
   const int d = p.comp, c = FIRSTM ? 1 : color;
   const long long N = 2 * g.half;
@@ -501,7 +502,7 @@ __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double 
   constexpr int NB = sizeof(T) == 4 ? 2 : 1;  // LDS buffers: two spare a barrier, but in float64 cost residency
   __shared__ T tile[NB][2][MARCH_TILE];       // [buffer][colour]
   __shared__ double red[4];
-  const MarchPos p = march_pos(g, true);  // chunk-per-XCD order (L z at 256^3: 46.2 -> 42.9 us)
+  const MarchPos p = march_pos(g, HELMM ? g.mch3 : g.mch, true);  // chunk-per-XCD order (L z at 256^3: 46.2 -> 42.9 us)
   const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
   const int d = p.comp;
   const long long N = 2 * g.half;

@@ -176,8 +176,12 @@ hipError_t lap_apply(const Geo &g, const T *x, TY *y, hipStream_t s) {
   MarchShape M = march_shape(g, 1);
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);  // the events of an enclosing ProbeExt, if any
-  hipExtLaunchKernelGGL((k_apply2<T, TY, AP_LAP>), M.grid, M.block, 0, s, e0, e1, 0, g, x, nullptr, y, 0.0, 0.0,
-                        (double *)nullptr);
+  if (M.bx == 1)
+    hipExtLaunchKernelGGL((k_apply2<T, TY, AP_LAP, true>), M.grid, M.block, 0, s, e0, e1, 0, g, x, nullptr, y, 0.0, 0.0,
+                          (double *)nullptr);
+  else
+    hipExtLaunchKernelGGL((k_apply2<T, TY, AP_LAP, false>), M.grid, M.block, 0, s, e0, e1, 0, g, x, nullptr, y, 0.0, 0.0,
+                          (double *)nullptr);
   return hipGetLastError();
 }
 template hipError_t lap_apply<float, double>(const Geo &, const float *, double *, hipStream_t);
@@ -335,7 +339,10 @@ template <typename TR>
 hipError_t helm_resid(const Geo &g, double a0, double nu, const double *x3, const double *b3, TR *r3,
                       double *part, int *nblocks, hipStream_t s) {
   MarchShape M = march_shape(g, 3);
-  hipLaunchKernelGGL((k_apply2<double, TR, AP_HRESID>), M.grid, M.block, 0, s, g, x3, b3, r3, a0, nu / g.h2, part);
+  if (M.bx == 1)
+    hipLaunchKernelGGL((k_apply2<double, TR, AP_HRESID, true>), M.grid, M.block, 0, s, g, x3, b3, r3, a0, nu / g.h2, part);
+  else
+    hipLaunchKernelGGL((k_apply2<double, TR, AP_HRESID, false>), M.grid, M.block, 0, s, g, x3, b3, r3, a0, nu / g.h2, part);
   *nblocks = (int)(M.grid.x * M.grid.y * M.grid.z);
   return hipGetLastError();
 }
@@ -353,9 +360,7 @@ template <typename T, typename TB>
 hipError_t helm_sor(const Geo &g, double a0, double nu, double omega, T *x3, const TB *b3, int color,
                     hipStream_t s) {
   MarchShape M = march_shape(g, 3);
-  hipLaunchKernelGGL((k_sweep<T, TB, SW_HELM>), M.grid, M.block, 0, s, g, x3, b3, color, g.h2, a0, nu / g.h2,
-                     omega);
-  return hipGetLastError();
+  return sweep_launch<T, TB, SW_HELM>(M, g, x3, b3, color, a0, nu / g.h2, omega, s, nullptr, nullptr);
 }
 template hipError_t helm_sor<float, float>(const Geo &, double, double, double, float *, const float *, int,
                                            hipStream_t);
@@ -367,8 +372,7 @@ template hipError_t helm_sor<double, double>(const Geo &, double, double, double
 template <typename T>
 hipError_t helm_sor_first(const Geo &g, double a0, double nu, double omega, T *x3, const T *b3, hipStream_t s) {
   MarchShape M = march_shape(g, 3);
-  hipLaunchKernelGGL((k_sweep<T, T, SW_HFIRST>), M.grid, M.block, 0, s, g, x3, b3, 1, g.h2, a0, nu / g.h2, omega);
-  return hipGetLastError();
+  return sweep_launch<T, T, SW_HFIRST>(M, g, x3, b3, 1, a0, nu / g.h2, omega, s, nullptr, nullptr);
 }
 template hipError_t helm_sor_first<float>(const Geo &, double, double, double, float *, const float *, hipStream_t);
 template hipError_t helm_sor_first<double>(const Geo &, double, double, double, double *, const double *,

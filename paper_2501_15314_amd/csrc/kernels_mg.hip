@@ -58,7 +58,7 @@ __device__ __forceinline__ T nb_sum(const Geo &g, const T *x, int i, int j, int 
 // The chunk of planes per workgroup is even, so a pair never splits.
 __host__ __device__ inline int restrict_chunk(const Geo &gf) { return gf.mch < 2 ? 2 : gf.mch; }
 
-template <typename T, typename TB>
+template <typename T, typename TB, bool THIN>
 __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB *bf, Geo gc, T *bc) {
   __shared__ T tile[2][MARCH_TILE];
   __shared__ T pair[256][2];
@@ -77,8 +77,9 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
   const unsigned rw = p.j * gf.hn2 + p.m0;
   // coarse row J at in-row index K / 2 (K = m0 is even): the same place in both colour planes
   const unsigned cw = (unsigned)((p.j >> 1) * gc.hn2 + (p.m0 >> 1)) * sizeof(T);
-  const MarchEdge e = march_edge(gf, p, BX, BY, [&](int q) { tile[0][q] = tile[1][q] = T(0); });
-  const unsigned eoff = (unsigned)(e.jr * gf.hn2 + e.mr) * sizeof(T), coff = (unsigned)(p.j * gf.hn2 + e.mc) * sizeof(T);
+  const MarchEdge e = march_edge<THIN>(gf, p, BX, BY, [&](int q) { tile[0][q] = tile[1][q] = T(0); });
+  const unsigned eoff = (unsigned)(e.jr * gf.hn2 + e.mr) * sizeof(T), coff = (unsigned)(p.j * gf.hn2 + e.mc) * sizeof(T),
+                 toff = (unsigned)(p.j * gf.hn2 + e.mt) * sizeof(T);
   const T ih2 = (T)(1.0 / gf.h2);
   // number of neighbours inside the grid, for the parities of even (i0) and odd planes
   const int s0 = p.j & 1;
@@ -90,12 +91,13 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
   const int z0 = gf.bc0 ? 0 : -2, z1 = gf.bc0 ? gf.n0 - 1 : -2;  // planes at a wall of axis 0
   struct Ops {
     V2<T> hr, x, b, w;
-    T hc;
+    T hc, ht;
   };
   auto fetch = [&](Ops &o) {
     const T *bp = blk + at.nxt;
     o.hr = ld2<T>(bp, eoff);
     o.hc = ldo(bp, coff);
+    if (THIN) o.ht = ldo(bp, toff);
     o.x = ld2<T>(red + at.nxt, rw * (unsigned)sizeof(T));
     o.b = ld2<T>(bf + at.nxt, rw * (unsigned)sizeof(TB));
     o.w = ld2<T>(blk + at.win, rw * (unsigned)sizeof(T));
@@ -126,7 +128,7 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
       t[e.rslot + 1] = o.hr.y;
     }
     if (e.cslot >= 0) t[e.cslot] = o.hc;
-    if (e.thin && e.mthin >= 0) trow[3] = blk[at.cur + p.j * gf.hn2 + e.mthin];
+    if (THIN && e.tslot >= 0) t[e.tslot] = o.ht;
     __syncthreads();
     wn = i == z1 ? V2<T>{T(0), T(0)} : o.w;
     if (f == 0) {
@@ -921,22 +923,15 @@ hipError_t mg_smooth_first(const Geo &g, T *x, const TB *b, bool store_red, hipS
   // launched with the events of an enclosing ProbeExt, if any (as the three below)
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
-  if (store_red)
-    hipExtLaunchKernelGGL((k_sweep<T, TB, SW_FIRST>), M.grid, M.block, 0, s, e0, e1, 0, g, x, b, 1, g.h2, 0.0, 0.0,
-                          1.0);
-  else
-    hipExtLaunchKernelGGL((k_sweep<T, TB, SW_FIRST1>), M.grid, M.block, 0, s, e0, e1, 0, g, x, b, 1, g.h2, 0.0, 0.0,
-                          1.0);
-  return hipGetLastError();
+  if (store_red) return sweep_launch<T, TB, SW_FIRST>(M, g, x, b, 1, 0.0, 0.0, 1.0, s, e0, e1);
+  return sweep_launch<T, TB, SW_FIRST1>(M, g, x, b, 1, 0.0, 0.0, 1.0, s, e0, e1);
 }
 template <typename T, typename TB>
 hipError_t mg_smooth(const Geo &g, T *x, const TB *b, int color, hipStream_t s) {
   MarchShape M = march_shape(g, 1);
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
-  hipExtLaunchKernelGGL((k_sweep<T, TB, SW_POISSON>), M.grid, M.block, 0, s, e0, e1, 0, g, x, b, color, g.h2, 0.0,
-                        0.0, 1.0);
-  return hipGetLastError();
+  return sweep_launch<T, TB, SW_POISSON>(M, g, x, b, color, 0.0, 0.0, 1.0, s, e0, e1);
 }
 
 template <typename T, typename TB>
@@ -948,7 +943,10 @@ hipError_t mg_restrict(const Geo &gf, const T *xf, const TB *bf, const Geo &gc, 
   if (gf.n0 % 2 || M.block.y % 2 || len % 2) return hipErrorInvalidValue;
   hipEvent_t e0, e1;
   probe_ext_take(&e0, &e1);
-  hipExtLaunchKernelGGL((k_restrict<T, TB>), M.grid, M.block, 0, s, e0, e1, 0, gf, xf, bf, gc, bc);
+  if (M.bx == 1)
+    hipExtLaunchKernelGGL((k_restrict<T, TB, true>), M.grid, M.block, 0, s, e0, e1, 0, gf, xf, bf, gc, bc);
+  else
+    hipExtLaunchKernelGGL((k_restrict<T, TB, false>), M.grid, M.block, 0, s, e0, e1, 0, gf, xf, bf, gc, bc);
   return hipGetLastError();
 }
 template <typename T>

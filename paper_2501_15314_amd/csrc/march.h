@@ -27,6 +27,8 @@
 // 7.3 / 5.3, 10.3 / 7.5; momentum half sweep at 256^3 float32 66.2 / 65.9, its
 // first sweep 108 / 76.5.
 #pragma once
+#include <hip/hip_ext.h>
+
 #include <type_traits>
 
 #include "internal.h"
@@ -138,7 +140,7 @@ __device__ __forceinline__ MarchBlock march_block(bool xcd) {
 
 // Per-block geometry of a march.
 struct MarchPos {
-  int tx, ty, m0, j, i0, i1, comp, mbase, jbase;
+  int tx, ty, m0, j, i0, i1, comp;
 };
 // len: planes per workgroup
 __device__ __forceinline__ MarchPos march_pos(const Geo &g, int len, bool xcd) {
@@ -146,10 +148,8 @@ __device__ __forceinline__ MarchPos march_pos(const Geo &g, int len, bool xcd) {
   const MarchBlock mb = march_block(xcd);
   p.tx = threadIdx.x;
   p.ty = threadIdx.y;
-  p.mbase = mb.x * blockDim.x * 2;
-  p.jbase = mb.y * blockDim.y;
-  p.m0 = p.mbase + 2 * threadIdx.x;
-  p.j = p.jbase + threadIdx.y;
+  p.m0 = 2 * (mb.x * blockDim.x + threadIdx.x);
+  p.j = mb.y * blockDim.y + threadIdx.y;
   int nch = (g.n0 + len - 1) / len;
   p.comp = mb.z / nch;
   int ch = mb.z - p.comp * nch;
@@ -164,27 +164,25 @@ __device__ __forceinline__ MarchPos march_pos(const Geo &g, int len, bool xcd) {
 // What does not change along the march -- offsets, LDS slots, whether the
 // cells lie outside a wall box (they are 0: `zero` stores that once for both
 // LDS buffers) -- is found here, without a division.  BY >= 2 (n1 is even and
-// so is BY); a tile one pair wide (BX == 1) has both columns at one thread,
-// which brings the right one by itself (`thin`).  Every thread loads: those
+// so is BY); a tile one pair wide (BX == 1: rows of 4 cells, or whose quarter is
+// a prime above 64) has both columns at one thread, which brings the right one
+// too, in kernels of their own (THIN).  Every thread loads: those
 // that bring nothing share an address of their row, so that the loads are not
 // under a condition (the compiler waits for all outstanding loads where a
 // conditional one may or may not be among them, which serialises the march).
 struct MarchEdge {
   int rslot, cslot;   // LDS slots of the row pair and the column cell, -1: none
   int jr, mr, mc;     // row and in-row index of the pair, in-row index of the column cell
-  bool thin;
-  int mthin;  // in-row index of the right column cell of a thin tile, -1: outside
+  int mt, tslot;      // in-row index and slot of the right column cell of a thin tile
 };
-template <class Z>
+template <bool THIN, class Z>
 __device__ __forceinline__ MarchEdge march_edge(const Geo &g, const MarchPos &p, int BX, int BY, Z zero) {
   MarchEdge e;
   const int W2 = 2 * BX + 2;
-  const bool lastr = p.ty == BY - 1, lastc = BX > 1 && p.tx == BX - 1;
-  e.rslot = e.cslot = -1;
-  e.jr = p.j;
-  e.mr = e.mc = p.m0 - 2 * p.tx;
-  e.thin = BX == 1;
-  e.mthin = 0;
+  const bool lastr = p.ty == BY - 1, lastc = !THIN && p.tx == BX - 1;
+  e.rslot = e.cslot = e.tslot = -1;
+  e.jr = THIN ? p.j - p.ty : p.j;  // in a thin tile the first row's for all, or each lane's would be a transaction
+  e.mr = e.mc = e.mt = p.m0 - 2 * p.tx;
   if (p.ty == 0 || lastr) {
     const int jj = mwrap(lastr ? p.j + 1 : p.j - 1, g.n1, g.bc1);
     const int slot = (lastr ? BY + 1 : 0) * W2 + 2 * p.tx + 1;
@@ -207,9 +205,14 @@ __device__ __forceinline__ MarchEdge march_edge(const Geo &g, const MarchPos &p,
       zero(slot);
     }
   }
-  if (e.thin) {
-    e.mthin = mwrap(p.m0 + 2, g.hn2, g.bc2);
-    if (e.mthin < 0) zero((p.ty + 1) * W2 + 2 * BX + 1);
+  if (THIN) {
+    const int mm = mwrap(p.m0 + 2, g.hn2, g.bc2), slot = (p.ty + 1) * W2 + 3;
+    if (mm >= 0) {
+      e.mt = mm;
+      e.tslot = slot;
+    } else {
+      zero(slot);
+    }
   }
   return e;
 }
@@ -223,10 +226,6 @@ __device__ __forceinline__ int diag_jk(const Geo &g, int jj, int kk, bool helm, 
   const int e1 = (jj == 0) + (jj == g.n1 - 1), e2 = (kk == 0) + (kk == g.n2 - 1);
   if (!helm) return (g.bc1 ? e1 : 0) + (g.bc2 ? e2 : 0);
   return 4 + (g.bc1 && d != 1 ? wall_ghost_diag(g.bc1) * e1 : 0) + (g.bc2 && d != 2 ? wall_ghost_diag(g.bc2) * e2 : 0);
-}
-__device__ __forceinline__ int diag_i(const Geo &g, int i, bool helm, int d) {
-  const int e = (i == 0) + (i == g.n0 - 1);
-  return helm ? 2 + ((g.bc0 && d != 0) ? wall_ghost_diag(g.bc0) * e : 0) : (g.bc0 ? e : 0);
 }
 // a normal wall face of momentum component d (held at 0), axes 1 and 2
 __device__ __forceinline__ bool wall_jk(const Geo &g, int jj, int kk, int d) {
@@ -302,7 +301,7 @@ struct CellRec {
 //               own colour).
 enum { SW_POISSON = 0, SW_FIRST = 1, SW_HELM = 2, SW_HFIRST = 3, SW_FIRST1 = 4 };
 
-template <typename T, typename TB, int MODE>
+template <typename T, typename TB, int MODE, bool THIN>
 __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int color, double h2, double a0,
                                                double nuh2, double omega) {
   constexpr bool FIRSTM = MODE == SW_FIRST || MODE == SW_HFIRST || MODE == SW_FIRST1;
@@ -321,8 +320,9 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
   const TO *osrc = FIRSTM ? (const TO *)(b + d * N + (long long)(1 - c) * g.half) : (const TO *)oth;
   const unsigned rw = p.j * g.hn2 + p.m0;  // this thread's two cells within a plane
   const T th2 = (T)h2, ta0 = (T)a0, tnu = (T)nuh2, tom = (T)omega;
-  const MarchEdge e = march_edge(g, p, BX, BY, [&](int q) { tile[0][q] = tile[1][q] = T(0); });
-  const unsigned eoff = (unsigned)(e.jr * g.hn2 + e.mr) * sizeof(TO), coff = (unsigned)(p.j * g.hn2 + e.mc) * sizeof(TO);
+  const MarchEdge e = march_edge<THIN>(g, p, BX, BY, [&](int q) { tile[0][q] = tile[1][q] = T(0); });
+  const unsigned eoff = (unsigned)(e.jr * g.hn2 + e.mr) * sizeof(TO), coff = (unsigned)(p.j * g.hn2 + e.mc) * sizeof(TO),
+                 toff = (unsigned)(p.j * g.hn2 + e.mt) * sizeof(TO);
 
   // Own cells at plane i have k = 2 m + s, s = (c + i + j) & 1; the
   // other-colour cells of the same row 1 - s, those of the rows beside it s.
@@ -341,8 +341,8 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
     return r;
   };
   const int di0 = HELMM ? 2 : 0;
-  CellRec<T> ro[2][2], rr[2][2], rc[2];  // own row (either colour), row pair, column cell
-  unsigned pk = 0, pkr = 0, pkc = 0;     // their counts of axes 1 and 2, 4 bits each
+  CellRec<T> ro[2][2], rr[2][2], rc[2], rt[2];  // own row (either colour), row pair, column cells
+  unsigned pk = 0, pkr = 0, pkc = 0, pkt = 0;    // their counts of axes 1 and 2, 4 bits each
 #pragma unroll
   for (int f = 0; f < 2; ++f) {
     const int s = f ? 1 - s0 : s0;
@@ -363,6 +363,12 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
       const int dc = diag_jk(g, p.j, k, HELMM, d);
       pkc |= (unsigned)dc << (4 * f);
       rc[f] = rec(di0 + dc, HELMM && wall_jk(g, p.j, k, d));
+      if (THIN) {
+        const int kt = 2 * e.mt + s;
+        const int dt = diag_jk(g, p.j, kt, HELMM, d);
+        pkt |= (unsigned)dt << (4 * f);
+        rt[f] = rec(di0 + dt, HELMM && wall_jk(g, p.j, kt, d));
+      }
     }
   }
   // planes at a wall of axis 0: where the tabulated records do not hold (e0,
@@ -404,11 +410,12 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
   };
   struct Ops {
     V2<T> hr, b, x, w;  // halo row pair, own right-hand side and value, other colour at the next plane
-    T hc;               // halo column cell
+    T hc, ht;           // halo column cells
   };
   auto fetch = [&](Ops &o) {
     o.hr = ld2<T>(osrc + at.nxt, eoff);
     o.hc = (T)ldo(osrc + at.nxt, coff);
+    if (THIN) o.ht = (T)ldo(osrc + at.nxt, toff);
     o.b = ld2<T>(bown + at.nxt, rw * (unsigned)sizeof(TB));
     if (MODE == SW_HELM) o.x = ld2<T>((const T *)own + at.nxt, rw * (unsigned)sizeof(T));
     o.w = ld2<T>(osrc + at.win, rw * (unsigned)sizeof(TO));
@@ -426,12 +433,13 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
     trow[1] = wc.x;
     trow[2] = wc.y;
     V2<T> hr = o.hr;
-    T hc = o.hc;
+    T hc = o.hc, ht = THIN ? o.ht : T(0);
     if (FIRSTM) {
       const Pair qr = at_plane(i, rr[f], pkr, 8 * f), qc = at_plane(i, rc, pkc, 0);
       hr.x = oxf(hr.x, qr.r[0]);
       hr.y = oxf(hr.y, qr.r[1]);
       hc = oxf(hc, qc.r[1 - f]);
+      if (THIN) ht = oxf(ht, at_plane(i, rt, pkt, 0).r[1 - f]);
     }
     if (e.rslot >= 0) {
       t[e.rslot] = hr.x;
@@ -439,15 +447,7 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
     }
     if (e.cslot >= 0) t[e.cslot] = hc;
     const int s = f ? 1 - s0 : s0;
-    if (e.thin && e.mthin >= 0) {
-      T v = (T)osrc[at.cur + p.j * g.hn2 + e.mthin];
-      if (FIRSTM) {
-        const int k = 2 * e.mthin + 1 - s;
-        v = oxf(v, rec(diag_i(g, i, HELMM, d) + diag_jk(g, p.j, k, HELMM, d),
-                       HELMM && (wall_jk(g, p.j, k, d) || (d == 0 && g.bc0 && i == 0))));
-      }
-      trow[3] = v;
-    }
+    if (THIN && e.tslot >= 0) t[e.tslot] = ht;
     __syncthreads();
     wn = i == z1 ? V2<T>{T(0), T(0)} : owin(i + 1 < g.n0 ? i + 1 : 0, o.w, f);
     const Pair q = at_plane(i, ro[f], pk, 8 * f);
@@ -488,6 +488,18 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
   }
 }
 
+template <typename T, typename TB, int MODE>
+hipError_t sweep_launch(const MarchShape &M, const Geo &g, T *x, const TB *b, int color, double a0, double nuh2,
+                        double omega, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (M.bx == 1)
+    hipExtLaunchKernelGGL((k_sweep<T, TB, MODE, true>), M.grid, M.block, 0, s, e0, e1, 0, g, x, b, color, g.h2, a0, nuh2,
+                          omega);
+  else
+    hipExtLaunchKernelGGL((k_sweep<T, TB, MODE, false>), M.grid, M.block, 0, s, e0, e1, 0, g, x, b, color, g.h2, a0, nuh2,
+                          omega);
+  return hipGetLastError();
+}
+
 // Operators on both colours at once: every thread owns the four cells of
 // row (i, j) stored at in-row indices m0, m0+1 of both colour planes.
 //   AP_LAP:    y = L x  (x of type T, y double) for the pressure Laplacian;
@@ -495,7 +507,7 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
 //              type TR), plus per-block partial sums of r^2 into part.
 enum { AP_LAP = 0, AP_HRESID = 1 };
 
-template <typename T, typename TR, int MODE>
+template <typename T, typename TR, int MODE, bool THIN>
 __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double *b, TR *out, double a0, double nuh2,
                                                 double *part) {
   constexpr bool HELMM = MODE == AP_HRESID;
@@ -510,11 +522,12 @@ __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double 
   const double *bg = b ? b + d * N : nullptr;
   TR *og = out + d * N;
   const unsigned rw = p.j * g.hn2 + p.m0;  // this thread's cells within a plane
-  const MarchEdge e = march_edge(g, p, BX, BY, [&](int q) {
+  const MarchEdge e = march_edge<THIN>(g, p, BX, BY, [&](int q) {
 #pragma unroll
     for (int z = 0; z < NB; ++z) tile[z][0][q] = tile[z][1][q] = T(0);
   });
-  const unsigned eoff = (unsigned)(e.jr * g.hn2 + e.mr) * sizeof(T), coff = (unsigned)(p.j * g.hn2 + e.mc) * sizeof(T);
+  const unsigned eoff = (unsigned)(e.jr * g.hn2 + e.mr) * sizeof(T), coff = (unsigned)(p.j * g.hn2 + e.mc) * sizeof(T),
+                 toff = (unsigned)(p.j * g.hn2 + e.mt) * sizeof(T);
   // coefficient of the cell itself, inside the grid: for parity index f and
   // cell u (the cells of colour 0 at plane i0 have k = 2 m + s0)
   const int s0 = (p.i0 + p.j) & 1, di0 = HELMM ? 2 : 0;
@@ -551,7 +564,7 @@ __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double 
   const int die = HELMM ? 2 + wall_ghost_diag(g.bc0) : 1;
   struct Ops {
     V2<T> hr[2];
-    T hc[2];
+    T hc[2], ht[2];
     V2<double> b[2];
     Win w;
   };
@@ -561,6 +574,7 @@ __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double 
       const T *xp = xg + q * g.half + at.nxt;
       o.hr[q] = ld2<T>(xp, eoff);
       o.hc[q] = ldo(xp, coff);
+      if (THIN) o.ht[q] = ldo(xp, toff);
       if (MODE == AP_HRESID) o.b[q] = ld2<double>(bg + q * g.half + at.nxt, rw * (unsigned)sizeof(double));
     }
     o.w = win_ld(at.win);
@@ -581,7 +595,7 @@ __global__ void __launch_bounds__(256) k_apply2(Geo g, const T *x, const double 
         t[e.rslot + 1] = o.hr[q].y;
       }
       if (e.cslot >= 0) t[e.cslot] = o.hc[q];
-      if (e.thin && e.mthin >= 0) t[rowb + 3] = xg[q * g.half + at.cur + p.j * g.hn2 + e.mthin];
+      if (THIN && e.tslot >= 0) t[e.tslot] = o.ht[q];
     }
     __syncthreads();
     wn = i == z1 ? none : o.w;

@@ -29,8 +29,16 @@ static void march_tile(Geo &g) {
   const int q = g.hn2 / 2 > 0 ? g.hn2 / 2 : 1;
   g.mbx = q % 64 == 0 ? 64 : (q % 32 == 0 ? 32 : (q < 64 ? q : 64));
   while (q % g.mbx) --g.mbx;
-  g.mby = 256 / g.mbx;
-  while (g.n1 % g.mby || (g.mby % 2 && g.n1 % 2 == 0)) --g.mby;
+  auto rows = [&](int most) {
+    while (g.n1 % most || (most % 2 && g.n1 % 2 == 0)) --most;
+    return most;
+  };
+  g.mby = rows(256 / g.mbx);
+  // one pair wide, where every lane is a row and a memory transaction of its
+  // own: half a wavefront, if the grid has such a divisor (float64 momentum solve
+  // on 64 x 64 x 268 cells in workgroups of 64, 32 and 16 rows 829, 786 and 873 us, on
+  // 128 x 128 x 268 of 128, 32 and 16 3050, 2859 and 2965)
+  if (g.mbx == 1 && rows(32) >= 16) g.mby = rows(32);
 }
 
 Geo make_geo(int n0, int n1, int n2, int bc0, int bc1, int bc2, double h, int march_min_blocks) {

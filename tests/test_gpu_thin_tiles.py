@@ -39,8 +39,9 @@ def test_cycle_with_rows_of_four_cells(bc, sweeps, precision):
 
 
 @pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
-def test_stencils_in_chunks_of_eight_planes(bc):
-    n, h = (20, 24, 284), 1.0 / 16
+@pytest.mark.parametrize("n", [(20, 24, 284), (20, 64, 268), (16, 76, 292)])  # 24, 32 (two tiles) and 76 rows
+def test_stencils_in_chunks_of_eight_planes(n, bc):
+    h = 1.0 / 16
     cfg = wl.Config(n=n, length=tuple(x * h for x in n), bc=bc, nu=0.02, dt=0.01, precision=wl.PREC_FP64,
                     precond=wl.PRECOND_FASTDIAG_EXACT, helm_rtol=1e-12)
     sim = make_sim(cfg, 0, "full")

@@ -178,17 +178,24 @@ template <int KER> __device__ __forceinline__ double dphi(double r) {
 }
 template <int KER> struct KerWidth { static constexpr int W = (KER == KER_PESKIN4) ? 4 : 3; };
 
-// First node index and offset of a point's support along one axis.  Nodes of
-// a velocity component along its own axis are faces (offset 0), otherwise
-// cell centres (offset 1/2).  r_t = s - (i0 + t) is the distance to node t in
-// cell widths.
+// A point's place along one axis in cell widths, from the first node.  Nodes of
+// a velocity component along its own axis are faces (offset 0), otherwise cell
+// centres (offset 1/2).  The fused form written out: whatever spreads or
+// interpolates, or finds the tiles that a support reaches, has to round it
+// alike, or W and its transpose part company.
+__device__ __forceinline__ double axis_place(double x, double inv_h, bool face) {
+  return fma(x, inv_h, face ? -0.0 : -0.5);
+}
+
+// First node index of a point's support along one axis, and its place.
+// r_t = s - (i0 + t) is the distance to node t in cell widths.
 template <int KER> __device__ __forceinline__ int support_start(double x, double inv_h, bool face, double &s) {
-  s = x * inv_h - (face ? 0.0 : 0.5);
+  s = axis_place(x, inv_h, face);
   return KER == KER_PESKIN4 ? (int)floor(s) - 1 : (int)floor(s + 0.5) - 1;
 }
 
 // All weights of a point along one axis from one square root.  With
-// s = x/h - offset (offset 0 for face nodes, 1/2 for centre nodes):
+// s = x/h - offset (axis_place):
 //   4-point: nodes floor(s)-1 .. floor(s)+2, f = s - floor(s),
 //            q = sqrt(1 + 4f - 4f^2) (the same radicand for all four nodes),
 //            w = ((3-2f-q)/8, (3-2f+q)/8, (1+2f+q)/8, (1+2f-q)/8);
@@ -200,9 +207,7 @@ template <int KER> __device__ __forceinline__ int support_start(double x, double
 // the float64 square root and its refinement.
 template <int KER, typename TA = double>
 __device__ __forceinline__ int axis_weights(double x, double inv_h, bool face, TA w[4]) {
-  // the fused form written out: every kernel that spreads or interpolates has
-  // to round s alike, or W and its transpose part company
-  const double s = fma(x, inv_h, face ? -0.0 : -0.5);
+  const double s = axis_place(x, inv_h, face);
   if (KER == KER_PESKIN4) {
     double fl = floor(s);
     TA f = (TA)(s - fl);

@@ -90,26 +90,6 @@ __device__ __forceinline__ T inv_nn(int nn) {
   return r;
 }
 
-// Number of neighbours of a cell that exist (walls remove one per side); the
-// diagonal of L = G^T G is nnb / h^2.
-__device__ __forceinline__ int cell_nnb(const Geo &g, int i, int j, int k) {
-  int n = 6;
-  if (g.bc0) n -= (i == 0) + (i == g.n0 - 1);
-  if (g.bc1) n -= (j == 0) + (j == g.n1 - 1);
-  if (g.bc2) n -= (k == 0) + (k == g.n2 - 1);
-  return n;
-}
-
-// Pressure-cell arithmetic of the multigrid cycle, with its fused
-// multiply-adds written out so that the plane-march kernels and the
-// tile-level kernels round every cell the same way:
-//   pc_first:  the Gauss-Seidel value h^2 b / nn of a first sweep from
-//              x = 0 (products rounded one at a time, never fused into a
-//              later sum);
-//   pc_relax:  Gauss-Seidel value (h^2 b + sum of neighbours) / nn;
-//   pc_resid:  residual b - (nn x - sum of neighbours) / h^2;
-//   blend34:   3/4 near + 1/4 far, one axis of cell-centred trilinear
-//              interpolation.
 // a product that no later sum may take in (__fmul_rn is a plain product to the
 // compiler, which fuses it where the sum follows directly)
 template <typename T>
@@ -117,17 +97,28 @@ __device__ __forceinline__ T mul_rn(T a, T b) {
 #pragma clang fp contract(off)
   return a * b;
 }
+// Pressure-cell arithmetic of the multigrid cycle, with its fused
+// multiply-adds written out so that every kernel that runs a part of the cycle
+// rounds a cell the same way (inv: inv_nn of the neighbours nn, 0 for a cell
+// outside the grid):
+//   pc_first:  the Gauss-Seidel value h^2 b / nn of a first sweep from
+//              x = 0 (products rounded one at a time, never fused into a
+//              later sum);
+//   pc_relax:  Gauss-Seidel value (h^2 b + sum of neighbours) / nn;
+//   pc_resid:  residual b - (nn x - sum of neighbours) / h^2;
+//   blend34:   3/4 near + 1/4 far, one axis of cell-centred trilinear
+//              interpolation.
 template <typename T>
-__device__ __forceinline__ T pc_first(T h2, T b, int nn) {
-  return mul_rn(mul_rn(h2, b), inv_nn<T>(nn));
+__device__ __forceinline__ T pc_first(T h2, T b, T inv) {
+  return mul_rn(mul_rn(h2, b), inv);
 }
 template <typename T>
-__device__ __forceinline__ T pc_relax(T h2, T b, T sum, int nn) {
-  return fma(h2, b, sum) * inv_nn<T>(nn);
+__device__ __forceinline__ T pc_relax(T h2, T b, T sum, T inv) {
+  return fma(h2, b, sum) * inv;
 }
 template <typename T>
-__device__ __forceinline__ T pc_resid(T b, T x, T sum, int nn, T ih2) {
-  return fma(-fma((T)nn, x, -sum), ih2, b);
+__device__ __forceinline__ T pc_resid(T b, T x, T sum, T nn, T ih2) {
+  return fma(-fma(nn, x, -sum), ih2, b);
 }
 template <typename T>
 __device__ __forceinline__ T blend34(T near, T far) {

@@ -6,10 +6,10 @@
 // Determinism.  No floating-point atomics are used.  Points are sorted into
 // tiles in canonical order (tile, original index).  Interpolation reduces
 // each point's stencil in a fixed butterfly order.  Spreading is done per
-// active tile by one workgroup: a wavefront per velocity component walks the
-// candidate points of the 27 neighbouring tiles in a fixed order, and for
-// each point its 64 stencil nodes are 64 distinct lanes adding into distinct
-// LDS cells, so every grid value is summed in the same order on every run.
+// active tile by one workgroup from the tile's touch list, whose points have
+// a fixed order: eight half-wavefronts add every eighth of them into registers,
+// a lane to its own columns of faces, and the eight partial sums of a face are
+// added in order, so every grid value is summed in the same order on every run.
 #include <hip/hip_ext.h>
 
 #include "internal.h"

@@ -18,33 +18,6 @@
 
 namespace ibs {
 
-__device__ __forceinline__ bool row_pos1m(const Geo &g, int color, RowPos &p) {
-  p.m = blockIdx.x * blockDim.x + threadIdx.x;
-  p.j = blockIdx.y * blockDim.y + threadIdx.y;
-  p.i = blockIdx.z;
-  p.comp = 0;
-  p.c = color;
-  if (p.m >= g.hn2 || p.j >= g.n1) return false;
-  p.k = 2 * p.m + ((p.c + p.i + p.j) & 1);
-  p.e = (long long)p.c * g.half + ((long long)p.i * g.n1 + p.j) * g.hn2 + p.m;
-  return true;
-}
-
-template <typename T>
-__device__ __forceinline__ T nb_sum(const Geo &g, const T *x, int i, int j, int k, int c, int m) {
-  const T *o = x + (long long)(1 - c) * g.half;
-  T s = T(0);
-  int t;
-  t = nbr(i, -1, g.n0, g.bc0); if (t >= 0) s += o[((long long)t * g.n1 + j) * g.hn2 + m];
-  t = nbr(i, 1, g.n0, g.bc0);  if (t >= 0) s += o[((long long)t * g.n1 + j) * g.hn2 + m];
-  t = nbr(j, -1, g.n1, g.bc1); if (t >= 0) s += o[((long long)i * g.n1 + t) * g.hn2 + m];
-  t = nbr(j, 1, g.n1, g.bc1);  if (t >= 0) s += o[((long long)i * g.n1 + t) * g.hn2 + m];
-  long long row = ((long long)i * g.n1 + j) * g.hn2;
-  t = nbr(k, -1, g.n2, g.bc2); if (t >= 0) s += o[row + (t >> 1)];
-  t = nbr(k, 1, g.n2, g.bc2);  if (t >= 0) s += o[row + (t >> 1)];
-  return s;
-}
-
 // Coarse right-hand side: the average of the fine residual over the eight
 // children.  The last half sweep relaxed the black cells, whose residual is
 // therefore zero; only the four red children contribute: in fine planes 2I
@@ -142,7 +115,7 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
       const T sum = (u ? wp.y : wp.x) + (u ? wn.y : wn.x) + trow[u + 1 - W2] + trow[u + 1 + W2] + trow[u + s] +
                     trow[u + 1 + s];
       const T nn = edge ? nt[f][u] - T(1) : nt[f][u];
-      acc[u] += fma(-fma(nn, u ? o.x.y : o.x.x, -sum), ih2, u ? o.b.y : o.b.x);  // pc_resid
+      acc[u] += pc_resid(u ? o.b.y : o.b.x, u ? o.x.y : o.x.x, sum, nn, ih2);
     }
     if (f == 1 && (p.ty & 1)) {
       pair[tid][0] = acc[0];
@@ -413,7 +386,7 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
   auto ldk = [&](long long o) { return ld2<T>(bk + o, rw * (unsigned)sizeof(TB)); };
   // offsets of the planes k + AH and k + AH + 1, and of k, advanced by addition
   long long o2 = plane(i0 - 1 + AH), o3 = plane(i0 + AH), ok = (i0 - 2) * P;
-  auto first = [&](V2<T> v, const T (&c)[2]) { return V2<T>{mul_rn(mul_rn(th2, v.x), c[0]), mul_rn(mul_rn(th2, v.y), c[1])}; };
+  auto first = [&](V2<T> v, const T (&c)[2]) { return V2<T>{pc_first(th2, v.x, c[0]), pc_first(th2, v.y, c[1])}; };
   // a pair into an LDS plane, with the row's ends (periodic: the other end)
   auto put = [&](T *t, const V2<T> &v) {
     T *r = t + ty * W + m0;
@@ -432,7 +405,7 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
     const T dx = last_row ? e.x : r[1 + dn], dy = last_row ? e.y : r[2 + dn];
     const T sx = p.x + n.x + ux + dx + r[s] + r[1 + s];
     const T sy = p.y + n.y + uy + dy + r[1 + s] + r[2 + s];
-    return V2<T>{T(fma(th2, bv.x, sx) * c[0]), T(fma(th2, bv.y, sy) * c[1])};
+    return V2<T>{pc_relax(th2, bv.x, sx, c[0]), pc_relax(th2, bv.y, sy, c[1])};
   };
   // Plane k (parity index f of the black cells there, which is that of the red
   // ones at k - 1 and k + 1).  Operands are loaded AH planes before their use
@@ -653,7 +626,7 @@ __global__ void __launch_bounds__(NT, 4) k_prolong_black(Geo g, T *x, const TB *
     const T sx = p.x + n.x + q[1 + up] + q[1 + dn] + q[s] + q[1 + s];
     const T sy = p.y + n.y + q[2 + up] + q[2 + dn] + q[1 + s] + q[2 + s];
     if (store)
-      st2<T>(xk + ok, rw * (unsigned)sizeof(T), fma(th2, bb[u & 3].x, sx) * c0, fma(th2, bb[u & 3].y, sy) * c1);
+      st2<T>(xk + ok, rw * (unsigned)sizeof(T), pc_relax(th2, bb[u & 3].x, sx, c0), pc_relax(th2, bb[u & 3].y, sy, c1));
   };
   {
     const int I = i0 / 2;
@@ -807,13 +780,13 @@ __global__ void __launch_bounds__(NT, 4) k_black_restrict(Geo g, const T *x, con
       c1 = out ? T(0) : inv_nn<T>((int)nn[f][1] - 1);
     }
     const V2<T> sb = sums(xr[(u + 7) & 7], xn, R, e, s);
-    kk[u & 3] = V2<T>{T(fma(th2, bb[u & 3].x, sb.x) * c0), T(fma(th2, bb[u & 3].y, sb.y) * c1)};
+    kk[u & 3] = V2<T>{pc_relax(th2, bb[u & 3].x, sb.x, c0), pc_relax(th2, bb[u & 3].y, sb.y, c1)};
     if (k > i0) {
       const V2<T> sr = sums(kk[(u + 2) & 3], kk[u & 3], K, e, s), xv = xr[(u + 7) & 7], bv = br[u & 3];
       const bool wall = g.bc0 && (k - 1 == 0 || k == g.n0);
       const T n0 = wall ? nn[f][0] - T(1) : nn[f][0], n1 = wall ? nn[f][1] - T(1) : nn[f][1];
-      acc[0] += fma(-fma(n0, xv.x, -sr.x), ih2, bv.x);  // pc_resid
-      acc[1] += fma(-fma(n1, xv.y, -sr.y), ih2, bv.y);
+      acc[0] += pc_resid(bv.x, xv.x, sr.x, n0, ih2);
+      acc[1] += pc_resid(bv.y, xv.y, sr.y, n1, ih2);
       if (f && store && !(ty & 1)) {  // plane k - 1 ends a pair
         T *q = pair + (ty * BX + tx) * 2;
         q[0] = acc[0];
@@ -1119,7 +1092,7 @@ __device__ __forceinline__ void tile_sweep(T (*sx)[TL_ROW * R * R], const TileRo
   if (w.box(lo)) {
     const Quad<T> sum = tile_sums<T, R>(sx[1 - c], w, c, x[1 - c]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[c].v[e] = fma(th2, b[c].v[e], sum.v[e]) * w.inv[c][e];  // pc_relax
+    for (int e = 0; e < 4; ++e) x[c].v[e] = pc_relax(th2, b[c].v[e], sum.v[e], w.inv[c][e]);
     *(Quad<T> *)(sx[c] + w.q) = x[c];
   }
   __syncthreads();
@@ -1154,7 +1127,7 @@ __global__ void __launch_bounds__(tile_threads(tile_edge(PRE))) k_tile_down(Geo 
   for (int c = 0; c < 2; ++c) bb[c] = tile_load<T>(b + c * g.half, w.off);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    xx[0].v[e] = w.inv[0][e] != T(0) ? mul_rn(mul_rn(th2, bb[0].v[e]), w.inv[0][e]) : T(0);  // pc_first
+    xx[0].v[e] = w.inv[0][e] != T(0) ? pc_first(th2, bb[0].v[e], w.inv[0][e]) : T(0);
     xx[1].v[e] = T(0);
   }
 #pragma unroll
@@ -1173,7 +1146,7 @@ __global__ void __launch_bounds__(tile_threads(tile_edge(PRE))) k_tile_down(Geo 
     T r[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      r[e] = pc_resid(bb[0].v[e], xx[0].v[e], sum.v[e], w.nn01 - ax.walls(2, w.u2(ax, 0, e)), ih2);
+      r[e] = pc_resid(bb[0].v[e], xx[0].v[e], sum.v[e], (T)(w.nn01 - ax.walls(2, w.u2(ax, 0, e))), ih2);
     T *p = rs + ((w.r0 - H) * TL_TS + w.r1 - H) * TC + 2 * w.h;
     st2<T>(p, 0, w.h ? r[0] : r[2], w.h ? r[1] : r[3]);
   }
@@ -1813,7 +1786,7 @@ __global__ void __launch_bounds__(NT) k_subcycle(Geo gf, Geo gc, const TB *bin, 
     if (live) {
       const Quad<T> sum = sums(c, xx[1 - c]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) xx[c].v[e] = fma(h2, bb[c].v[e], sum.v[e]) * inv[c].v[e];
+      for (int e = 0; e < 4; ++e) xx[c].v[e] = pc_relax(h2, bb[c].v[e], sum.v[e], inv[c].v[e]);
       put(c, xx[c]);
     }
     __syncthreads();
@@ -1821,7 +1794,7 @@ __global__ void __launch_bounds__(NT) k_subcycle(Geo gf, Geo gc, const TB *bin, 
   // the first half sweep from x = 0
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    xx[0].v[e] = pre > 0 ? mul_rn(mul_rn(h2, bb[0].v[e]), inv[0].v[e]) : T(0);
+    xx[0].v[e] = pre > 0 ? pc_first(h2, bb[0].v[e], inv[0].v[e]) : T(0);
     xx[1].v[e] = T(0);
   }
 #pragma unroll
@@ -1843,7 +1816,7 @@ __global__ void __launch_bounds__(NT) k_subcycle(Geo gf, Geo gc, const TB *bin, 
       for (int c = 0; c < 2; ++c) {
         const Quad<T> sum = sums(c, xx[1 - c]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[c].v[e] = pc_resid(bb[c].v[e], xx[c].v[e], sum.v[e], nn(c, e), ih2);
+        for (int e = 0; e < 4; ++e) r[c].v[e] = pc_resid(bb[c].v[e], xx[c].v[e], sum.v[e], (T)nn(c, e), ih2);
       }
     }
     __syncthreads();

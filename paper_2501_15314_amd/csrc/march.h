@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
   };
   // a colour-0 value of a first sweep from its right-hand side
   auto oxf = [&](T bv, const CellRec<T> &r) -> T {
-    if (!HELMM) return mul_rn(mul_rn(th2, bv), r.inv);  // pc_first
+    if (!HELMM) return pc_first(th2, bv, r.inv);
     const T v = tom * div_by(bv, r.den, r.inv);
     return r.wall ? T(0) : v;
   };
@@ -459,7 +459,7 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, T *x, const TB *b, int col
       const T bv = u ? o.b.y : o.b.x;
       const CellRec<T> &r = q.r[u];
       if (!HELMM) {
-        out[u] = fma(th2, bv, sum) * r.inv;  // pc_relax
+        out[u] = pc_relax(th2, bv, sum, r.inv);
       } else {
         const T xv = MODE == SW_HELM ? (u ? o.x.y : o.x.x) : T(0);
         const T gs = div_by<T>(fma(tnu, sum, bv), r.den, r.inv);

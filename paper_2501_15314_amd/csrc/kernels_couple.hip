@@ -36,7 +36,8 @@
 // stage a point about six times, 22 + 57 us (32 + 68 us and 7.3 + 6.7 us
 // when this kernel was written, before the list kernels got faster).  Points
 // are split into workgroups of 64 and not looped over: 55 us with one
-// workgroup per tile.
+// workgroup per tile.  Points scattered through a volume go to the touch lists
+// (couple_pays).
 #include <hip/hip_ext.h>
 
 #include "internal.h"
@@ -101,7 +102,7 @@ hipError_t couple_items(int n, const int *tiles, const int *tstart, int4 *items,
 }
 long long couple_max_items(long long K, long long ntiles) { return (K < ntiles ? K : ntiles) + K / CPTS; }
 // The region buffer holds at most CBATCH items (64 MiB); a product over more
-// items (points scattered over that many tiles) runs in batches of as many.
+// items (surfaces through that many tiles) runs in batches of as many.
 constexpr int CBATCH = 16384;
 size_t couple_region_bytes(long long K, long long ntiles) {
   const long long m = couple_max_items(K, ntiles);

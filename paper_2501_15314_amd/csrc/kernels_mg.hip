@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
   __shared__ T tile[2][MARCH_TILE];
   __shared__ T pair[256][2];
   const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
-  MarchPos p;
+  MarchPos p{};
   p.tx = threadIdx.x;
   p.ty = threadIdx.y;
   p.m0 = 2 * (blockIdx.x * BX + p.tx);
@@ -273,9 +273,13 @@ __global__ void __launch_bounds__(256) k_prolong(Geo gf, T *xf, Geo gc, const T 
 // the others in LDS (two buffers, one barrier per plane).  A cell outside a
 // wall box has a reciprocal count of 0 and so stays 0.
 //
-// Bounded by the latency of a plane's loads (two planes ahead) and its barrier
-// with two workgroups of 8 wavefronts on a compute unit: float32, before (both
-// passes) and after, us: 128^3 12.5 / 10.1, 256^3 41.2 / 29.9, 384^3 136 / 82.
+// Bounded by bytes on a large level: at 384^3 it moves 465 MB of HBM traffic at
+// 5.7 TB/s, where 340 MB are what it asks for -- a workgroup of 8 rows stores 6,
+// and its first and last row bring one more row each from beyond.  On a level
+// that the last-level cache holds, by the latency of a plane's loads (two planes
+// ahead) and its barrier with two workgroups of 8 wavefronts on a compute unit.
+// float32, before (both passes) and after, us: 128^3 12.5 / 10.1, 256^3 41.2 / 29.9,
+// 384^3 136 / 82.
 // In float64 its registers leave half the wavefronts or spill (256^3: 76.7
 // before, 75.6 one plane ahead, 192 two ahead), so that form keeps two passes.
 // With a float64 right-hand side the float32 form holds it two planes ahead only
@@ -495,8 +499,9 @@ __global__ void __launch_bounds__(NT, 4) k_first2(Geo g, T *x, const TB *b, doub
 // is that of its place in the unrolled loop, and every second plane brings the
 // blend of one more coarse plane.
 //
-// Bounded as k_first2.  Both passes before and this one after, float32, us:
-// 256^3 34.5 / 25.2, 384^3 115 / 73, 128^3 10.6 / 10.2.
+// Bounded as k_first2: 151 MB counted for 109 at 256^3, 6.0 TB/s; 471 for 368 at
+// 384^3, 6.4.  Both passes before and this one after, float32, us: 256^3 34.5 / 25.2,
+// 384^3 115 / 73, 128^3 10.6 / 10.2.
 template <typename T, typename TB, int NT>
 __global__ void __launch_bounds__(NT, 4) k_prolong_black(Geo g, T *x, const TB *b, Geo gc, const T *xc, double h2,
                                                          int chunk) {
@@ -673,8 +678,10 @@ __global__ void __launch_bounds__(NT, 4) k_prolong_black(Geo g, T *x, const TB *
 // stored rows and its chunk start at even places and are even in number, which
 // takes a row off a workgroup of 9, 11, 13 or 15).
 //
-// Bounded as k_first2.  Both passes before and this one after, float32, us:
-// 256^3 39.3 / 31.2, 384^3 141 / 88, 128^3 10.2 / 10.3.
+// Bounded as k_first2, and it reads most of all, three arrays with their halo rows:
+// 180 MB counted for 109 at 256^3, 5.8 TB/s; 535 for 368 at 384^3, 6.1.  Both
+// passes before and this one after, float32, us: 256^3 39.3 / 31.2, 384^3 141 / 88,
+// 128^3 10.2 / 10.3.
 template <typename T, typename TB, int NT>
 __global__ void __launch_bounds__(NT, 4) k_black_restrict(Geo g, const T *x, const TB *b, Geo gc, T *bc, double h2,
                                                           int chunk) {

@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(256) k_restrict(Geo gf, const T *xf, const TB 
   __shared__ T tile[2][MARCH_TILE];
   __shared__ T pair[256][2];
   const int BX = blockDim.x, BY = blockDim.y, W2 = 2 * BX + 2;
-  MarchPos p{};
+  MarchPos p;
   p.tx = threadIdx.x;
   p.ty = threadIdx.y;
   p.m0 = 2 * (blockIdx.x * BX + p.tx);

@@ -77,8 +77,9 @@ def test_cycle_by_row_length(n, coarsest, sweeps, bc):
     ((256, 160, 208), 128, (2, 1), 3),  # 9 rows by threads, above one exact coarse solve
     ((224, 224, 176), 112, (2, 1), 3),  # 11 rows
     ((256, 352, 80), 176, (2, 1), 3),   # 16 rows of 20 threads: five wavefronts
-    ((256, 192, 160), 16, (3, 2), 3),
-    ((224, 192, 192), 14, (2, 2), 3),
+    ((256, 192, 160), 16, (3, 2), 3),   # 12 rows
+    ((224, 256, 144), 128, (2, 1), 3),  # 14 rows
+    ((224, 192, 192), 14, (2, 2), 3),   # 10 rows
     ((256, 256, 128), 16, (2, 1), 3),   # 16 rows
     ((160, 160, 320), 20, (2, 1), 3),
     ((128, 128, 512), 32, (2, 1), 3),   # 8 rows of 128 threads

@@ -1,6 +1,6 @@
 """The fused passes of a large float32 level (first black and red half sweeps,
 last black half sweep and restriction, prolongation and black half sweep) on
-row lengths that give their workgroups 8 to 14 rows, an odd number before the
+row lengths that give their workgroups 8 to 16 rows, an odd number before the
 restriction's pairing takes one off among them, and in workgroups of more than
 512 threads.
 
@@ -89,6 +89,8 @@ def test_cycle_by_row_length(n, coarsest, sweeps, bc):
     ((144, 128, 128), 9, (2, 0), 1),    # only the first one
     ((64, 64, 96), 12, (2, 1), 1),      # levels of at most 128^3 cells: the first one
     ((32, 32, 288), 18, (2, 1), 1),
+    ((128, 16, 256), 16, (2, 1), 1),    # a grid of as few rows as a workgroup may wrap
+    ((96, 24, 160), 20, (3, 2), 1),
 ])
 @pytest.mark.parametrize("bc", [(P, P, P), (N, P, F), (F, N, N)])
 def test_fused_passes_give_the_bits_of_separate_ones(n, coarsest, sweeps, saved, bc):
